@@ -227,6 +227,33 @@ inline void row_blocks(int nx, int &nib, int &bs) {
   bs = (per + 63) / 64 * 64;
 }
 
+// Chunks of a marching kernel (column sweeps, the fused Z/X pass, the source
+// step): n zones in chunks of at least `least` and at most `most`, `each`
+// workers (waves or workgroups) per chunk, of which `slots` run at once.  A
+// launch takes about rounds x (zones of a chunk + over), with `over` the zones
+// a chunk reads beside its own; of the fewest chunks, and the most that fit
+// each of the next whole rounds, the cheapest is taken.
+inline int fill_chunks(int n, int most, int least, long each, long slots, int over) {
+  const int lo = (n + most - 1) / most, hi = n / least > lo ? n / least : lo;
+  auto rounds = [&](long k) { return (each * k - 1) / slots + 1; };
+  const long r0 = rounds(lo);
+  int best = lo;
+  long cost = r0 * ((n + lo - 1) / lo + over);
+  for (long r = r0; r < r0 + 8; r++) {
+    const long fit = r * slots / each;
+    if (fit <= lo) continue;
+    const int k = fit < hi ? (int)fit : hi;
+    const long c = rounds(k) * ((n + k - 1) / k + over);
+    if (c < cost) {
+      cost = c;
+      best = k;
+    }
+    if (k == hi) break;
+  }
+  return best;
+}
+constexpr int CHIP_CUS = 256; // compute units of the chip
+
 // Order-preserving integer image of a non-negative double (for atomic min/max).
 __device__ inline unsigned long long dbits(double x) { return (unsigned long long)__double_as_longlong(x); }
 

@@ -127,7 +127,8 @@ struct Zv {
 template <typename F, bool D3, int GEO, bool ADI>
 __device__ __forceinline__ void source_body(Mesh m, StateT<F> s, const double *__restrict__ dtp,
                                                   F *__restrict__ vx2, F *__restrict__ vy2, F *__restrict__ vz2,
-                                                  F *__restrict__ e2, int nbx, int nby, unsigned bid_, unsigned nbk_) {
+                                                  F *__restrict__ e2, int nbx, int nby, int zlen, unsigned bid_,
+                                                  unsigned nbk_) {
   constexpr int TY = tile_rows<F, D3, GEO, ADI>(), NB = D3 ? 2 : 1;
   constexpr bool KI = keep_inv<F, TY, NB, GEO == FARGO_SPHERICAL>();
   __shared__ Lds<F, TY, NB, GEO == FARGO_SPHERICAL, KI> L;
@@ -145,7 +146,8 @@ __device__ __forceinline__ void source_body(Mesh m, StateT<F> s, const double *_
   // 2D meshes keep Y fastest over the whole mesh (G = nby), which measured
   // faster for the former.
   const int G = TY == 16 || (D3 && sizeof(F) == 4) ? 4 : nby;
-  const unsigned Lb = xcd_remap(bid_, nbk_), gsz = (unsigned)(G * nbx);
+  const unsigned Lc = xcd_remap(bid_, nbk_), ntile = (unsigned)(nbx * nby), gsz = (unsigned)(G * nbx);
+  const unsigned zc = D3 ? Lc / ntile : 0u, Lb = D3 ? Lc % ntile : Lc;
   const unsigned grp = Lb / gsz, idx = Lb % gsz, gy = (unsigned)min(G, nby - (int)grp * G);
   const int ty = (int)(grp * (unsigned)G + idx % gy), tx = (int)(idx / gy);
   const int i0 = tx * TX, jt0 = m.j0 + ty * TY;
@@ -445,8 +447,8 @@ __device__ __forceinline__ void source_body(Mesh m, StateT<F> s, const double *_
     __syncthreads();
     if (act) zones(0, 0, 0, ZPart{}, e_old);
   } else {
-  // ---- 3D march over the active planes k0 .. kn-1
-  const int k0 = m.k0, kn = m.kn;
+  // ---- 3D march over the workgroup's active planes k0 .. kn-1
+  const int k0 = m.k0 + (int)zc * zlen, kn = min(k0 + zlen, m.kn);
   // Z window of the thread's column at the top of interval kk:
   //   Z1, Z2 = records of planes kk+1, kk+2; vzk = v_z of plane kk;
   //   A[0..2] = v'_z of faces kk .. kk+2, IZ likewise; Q[0..2] = q_z of
@@ -550,8 +552,8 @@ __device__ __forceinline__ void source_body(Mesh m, StateT<F> s, const double *_
 template <typename F, bool D3, int GEO, bool ADI>
 __global__ __launch_bounds__((src_threads<F, D3, GEO, ADI>()), (src_waves<F, D3, GEO, ADI>())) void k_source(
     Mesh m, StateT<F> s, const double *__restrict__ dtp, F *__restrict__ vx2, F *__restrict__ vy2,
-    F *__restrict__ vz2, F *__restrict__ e2, int nbx, int nby) {
-  source_body<F, D3, GEO, ADI>(m, s, dtp, vx2, vy2, vz2, e2, nbx, nby, blockIdx.x, gridDim.x);
+    F *__restrict__ vz2, F *__restrict__ e2, int nbx, int nby, int zlen) {
+  source_body<F, D3, GEO, ADI>(m, s, dtp, vx2, vy2, vz2, e2, nbx, nby, zlen, blockIdx.x, gridDim.x);
 }
 
 // Ghost zones (Y ghost rows of every plane, and Z ghost planes of the active
@@ -605,7 +607,7 @@ __global__ __launch_bounds__((src_threads<F, D3, GEO, ADI>()), (src_waves<F, D3,
   const uint2 t = many_block(tab);
   if (t.x == MANY_NONE) return;
   const SourceArgs<F> a = many_args<SourceArgs<F>>(args, t.x);
-  source_body<F, D3, GEO, ADI>(a.m, a.s, a.dt, a.vx2, a.vy2, a.vz2, a.e2, a.nbx, a.nby, t.y, a.nb);
+  source_body<F, D3, GEO, ADI>(a.m, a.s, a.dt, a.vx2, a.vy2, a.vz2, a.e2, a.nbx, a.nby, 1, t.y, a.nb);
 }
 template <typename F>
 __global__ __launch_bounds__(256) void k_source_ghosts_many(const void *args, const uint2 *tab) {
@@ -623,18 +625,41 @@ int src_rows(const Mesh &m) {
   return tall ? tile_rows<F, true, FARGO_CARTESIAN, false>() : tile_rows<F, true, FARGO_SPHERICAL, true>();
 }
 
+// workgroups of the source step that the chip holds at once
+template <typename F, bool D3, int GEO, bool ADI>
+long src_slots() {
+  int per_cu = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_source<F, D3, GEO, ADI>, src_threads<F, D3, GEO, ADI>(), 0) !=
+          hipSuccess ||
+      per_cu < 1)
+    per_cu = 1;
+  return (long)per_cu * CHIP_CUS;
+}
 } // namespace
 
 template <typename F>
 void launch_source(Launch &L, const Mesh &m, const StateT<F> &s, const double *dt, F *vx2, F *vy2, F *vz2, F *e2) {
   const int nbx = (m.nx + TX - 1) / TX, nby = (m.ny + src_rows<F>(m) - 1) / src_rows<F>(m);
-  const unsigned nb = (unsigned)nbx * (unsigned)nby;
   const unsigned ng = (unsigned)(m.nzg * (m.nyg - m.ny) + (m.d3 ? (m.nzg - m.nz) * m.ny : 0));
   prof_begin(L, K_SRC);
   auto go = [&](auto d3, auto geo, auto adi) {
     constexpr bool D3 = decltype(d3)::value, ADI = decltype(adi)::value;
     constexpr int GEO = decltype(geo)::value;
-    k_source<F, D3, GEO, ADI><<<nb, src_threads<F, D3, GEO, ADI>(), 0, L.s>>>(m, s, dt, vx2, vy2, vz2, e2, nbx, nby);
+    int zlen = 1;
+    unsigned nb = (unsigned)nbx * (unsigned)nby;
+    if constexpr (D3) {
+      // the march in chunks of planes where the tiles alone leave compute units
+      // idle, or a last round of workgroups nearly empty (a chunk reads five
+      // planes beside its own).  Box of 160 x 144 x 120 zones, 36 tiles: 311
+      // to 64 us; 501 x 167 x 43 FP32 spherical, 168 tiles on 512 slots: 147
+      // to 67 us; 1536 x 512 x 128, 1032 tiles on 256 slots: 2.52 to 2.42 ms;
+      // 2048 x 768 x 96, 1536 tiles: unchanged.
+      static const long slots = src_slots<F, D3, GEO, ADI>();
+      const int nzc = fill_chunks(m.nz, m.nz, 4, (long)nb, slots, 4);
+      zlen = (m.nz + nzc - 1) / nzc;
+      nb *= (unsigned)((m.nz + zlen - 1) / zlen);
+    }
+    k_source<F, D3, GEO, ADI><<<nb, src_threads<F, D3, GEO, ADI>(), 0, L.s>>>(m, s, dt, vx2, vy2, vz2, e2, nbx, nby, zlen);
   };
   auto by_eos = [&](auto d3, auto geo) {
     if (m.eos == FARGO_ADIABATIC) go(d3, geo, std::true_type{});

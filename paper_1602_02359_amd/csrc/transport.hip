@@ -992,32 +992,58 @@ __global__ __launch_bounds__(256) void k_vel(Mesh m, StateT<F> s, TSetT<F> T) {
   vel_body<F>(m, s, T, blockIdx.x, gridDim.x);
 }
 
-// The zones of a direction split into the fewest chunks of at most m.chunk
-// zones, of equal length (the last one shorter by less than the count), so
-// that the threads of a sweep end together.  Returns the mesh with the chunk
-// length the kernels use, and the number of chunks.
-inline Mesh balanced(const Mesh &m, int n, int &nchunk) {
-  nchunk = (n + m.chunk - 1) / m.chunk;
+// n zones split into nchunk chunks of equal length (the last one shorter by
+// less than the count), so that the threads of a sweep end together: the mesh
+// with that chunk length, and the number of chunks it takes.
+inline Mesh chunked(const Mesh &m, int n, int &nchunk) {
   Mesh mm = m;
   mm.chunk = (n + nchunk - 1) / nchunk;
+  nchunk = (n + mm.chunk - 1) / mm.chunk;
   return mm;
+}
+// The fewest chunks of at most m.chunk zones, or more where those would leave
+// the chip idle (fill_chunks; `each` workers per chunk, of which `slots` run at
+// once).  A 2D disk of 384 x 128 zones in two 64-zone chunks is swept along Y
+// by 4 workgroups (58 us); 128 chunks of one zone take 6.2 us.  3072 x 1024:
+// 77 to 47 us (5 TB/s of its 9 words a zone); the box of 160 x 144 x 120
+// zones: Z 131 to 94 us, Y 93 to 78; the FP32 Z/X pass of 501 x 167 x 43 zones
+// 258 to 153 us.  Meshes that fill the chip with chunks of m.chunk zones (2048 x
+// 768 x 96) keep them.
+constexpr int SWEEP_OVER = 2; // zones a chunk costs beside its own (1, 2 and 4 measured alike)
+inline Mesh filled(const Mesh &m, int n, long each, long slots, int &nchunk) {
+  nchunk = fill_chunks(n, m.chunk, 1, each, slots, SWEEP_OVER);
+  return chunked(m, n, nchunk);
+}
+
+// Workgroups of bs threads of a kernel that the chip holds at once.
+template <typename K>
+long block_slots(K kernel, int bs) {
+  int per_cu = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, bs, 0) != hipSuccess || per_cu < 1) per_cu = 2;
+  return (long)per_cu * CHIP_CUS;
 }
 
 template <typename F, int NQ, bool D3, bool ADI>
 void sweep_y_launch(Launch &L, const Mesh &m0, const StateT<F> &s, const TSetT<F> &out, const double *dt) {
+  constexpr auto kern = k_sweep_y<F, NQ, D3, ADI>;
+  static const long slots[4] = {block_slots(kern, 64), block_slots(kern, 128), block_slots(kern, 192),
+                                block_slots(kern, 256)};
   int nib, bs, nchunk;
-  const Mesh m = balanced(m0, m0.ny, nchunk);
-  row_blocks(m.nx, nib, bs);
-  int nrows = D3 ? m.nz + 4 : 1;
+  row_blocks(m0.nx, nib, bs);
+  const int nrows = D3 ? m0.nz + 4 : 1;
+  const Mesh m = filled(m0, m0.ny, (long)nib * nrows, slots[bs / WAVE - 1], nchunk);
   unsigned nb = (unsigned)nib * (unsigned)nchunk * (unsigned)nrows;
   k_sweep_y<F, NQ, D3, ADI><<<nb, bs, 0, L.s>>>(m, s.rho, s.vx, s.vy, s.vz, s.e, out, dt, nchunk);
 }
 
 template <typename F, int NQ>
 void sweep_z_launch(Launch &L, const Mesh &m0, const F *vz, const TSetT<F> &in, const TSetT<F> &out, const double *dt) {
+  constexpr auto kern = k_sweep_z<F, NQ>;
+  static const long slots[4] = {block_slots(kern, 64), block_slots(kern, 128), block_slots(kern, 192),
+                                block_slots(kern, 256)};
   int nib, bs, nchunk;
-  const Mesh m = balanced(m0, m0.nz, nchunk);
-  row_blocks(m.nx, nib, bs);
+  row_blocks(m0.nx, nib, bs);
+  const Mesh m = filled(m0, m0.nz, (long)nib * m0.ny, slots[bs / WAVE - 1], nchunk);
   unsigned nb = (unsigned)nib * (unsigned)nchunk * (unsigned)m.ny;
   k_sweep_z<F, NQ><<<nb, bs, 0, L.s>>>(m, vz, in, out, dt, nchunk);
 }
@@ -1070,9 +1096,10 @@ template <typename F>
 void launch_zx(Launch &L, const Mesh &m0, const F *vx2, const F *vz, const TSetT<F> &T, const TSetT<F> &Tout,
                const StateT<F> &s, const double *v0, const double *dt) {
   constexpr int U = RingLane<F>::U;
+  static const long slots[2] = {4 * block_slots(k_zx<F, 6>, 256), 4 * block_slots(k_zx<F, 7>, 256)};
   int nkc;
-  const Mesh m = balanced(m0, m0.nz, nkc);
-  const int nseg = (m.nx + U - 1) / U;
+  const int nseg = (m0.nx + U - 1) / U;
+  const Mesh m = filled(m0, m0.nz, (long)nseg * m0.ny, slots[T.nq == 7], nkc);
   const long waves = (long)nseg * m.ny * nkc;
   const unsigned nb = (unsigned)((waves + 3) / 4);
   prof_begin(L, K_ZX);
@@ -1201,8 +1228,8 @@ size_t sweep_y_args_bytes() { return sizeof(SweepYArgs<F>); }
 
 template <typename F>
 unsigned sweep_y_args(const Mesh &m0, const StateT<F> &s, const TSetT<F> &out, const double *dt, void *dst) {
-  int nchunk;
-  const Mesh m = balanced(m0, m0.ny, nchunk);
+  int nchunk = (m0.ny + m0.chunk - 1) / m0.chunk;
+  const Mesh m = chunked(m0, m0.ny, nchunk);
   const unsigned nb = (unsigned)((m.nx + MANY_BS - 1) / MANY_BS) * (unsigned)nchunk;
   *(SweepYArgs<F> *)dst = SweepYArgs<F>{m, s.rho, s.vx, s.vy, s.vz, s.e, out, dt, nchunk, nb};
   return nb;
