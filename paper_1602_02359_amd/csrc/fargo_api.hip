@@ -869,7 +869,6 @@ struct fargo_batch {
   // fused mode: the launches' argument blocks and tables in one allocation
   void *fmem = nullptr;
   ManyGrid g[9] = {};
-  ManyGrid gcfl[8] = {}; // the time-step pass by zones per thread (ceil(nx / 256), 1..7)
   int nxmax = 0;
   std::vector<int> chunk; // per disk (the sweep's chunk length, tuned per size class)
 };
@@ -975,9 +974,8 @@ struct ManyHost {
 template <typename F>
 int fused_build(fargo_batch *b) {
   const unsigned n = (unsigned)b->ctx.size();
-  ManyHost H[FU_N], HC[8];
+  ManyHost H[FU_N];
   // argument blocks packed at their exact size: the kernels index them so
-  for (auto &h : HC) h.asz = cfl_args_bytes<F>();
   H[FU_CFL].asz = cfl_args_bytes<F>();
   H[FU_DT].asz = dt_final_args_bytes();
   H[FU_SRC].asz = H[FU_SRCG].asz = source_args_bytes<F>();
@@ -994,10 +992,7 @@ int fused_build(fargo_batch *b) {
     const StateT<F> S = state_of<F>(c, &b->st[d]);
     const double *dtp = c->w.dt;
     F *v2[4] = {(F *)c->v2[0], (F *)c->v2[1], (F *)c->v2[2], (F *)c->v2[3]};
-    // the time-step pass in one launch per class of ring length (zones per
-    // thread), each with its own argument array indexed by disk
-    ManyHost &hc = HC[(m.nx + 255) / 256];
-    hc.blocks(d, cfl_args<F>(m, S, c->v0, c->ringrate, c->ringshear, c->w.err, hc.slot(d)));
+    H[FU_CFL].blocks(d, cfl_args<F>(m, S, c->v0, c->ringrate, c->ringshear, c->w.err, H[FU_CFL].slot(d)));
     H[FU_DT].blocks(d, dt_final_args(m, c->w, c->ringrate, c->ringshear, H[FU_DT].slot(d)));
     H[FU_SRC].blocks(d, source_args<F>(m, S, dtp, v2[0], v2[1], v2[2], v2[3], H[FU_SRC].slot(d)));
     H[FU_SRCG].blocks(d, source_ghosts_args<F>(m, S, v2[0], v2[1], v2[2], v2[3], H[FU_SRCG].slot(d)));
@@ -1023,7 +1018,6 @@ int fused_build(fargo_batch *b) {
   }
   size_t total = 0;
   for (auto &h : H) total += al(h.args.size()) + al(h.tab.size() * sizeof(uint2));
-  for (auto &h : HC) total += al(h.args.size()) + al(h.tab.size() * sizeof(uint2));
   if (b->fmem) (void)hipFree(b->fmem);
   b->fmem = nullptr;
   if (hipMalloc(&b->fmem, total) != hipSuccess) return FARGO_ENOMEM;
@@ -1045,10 +1039,6 @@ int fused_build(fargo_batch *b) {
     const int rc = upload(H[k], b->g[k]);
     if (rc) return rc;
   }
-  for (int k = 0; k < 8; k++) {
-    const int rc = upload(HC[k], b->gcfl[k]);
-    if (rc) return rc;
-  }
   return FARGO_OK;
 }
 
@@ -1056,8 +1046,7 @@ int fused_build(fargo_batch *b) {
 template <typename F>
 void fused_step(fargo_batch *b, Launch &L) {
   const Mesh &m0 = b->ctx[0]->m;
-  for (int k = 1; k < 8; k++)                                                      // boxes 3, 4, 6
-    if (b->gcfl[k].nblk) launch_cfl_many<F>(L, b->gcfl[k], 256 * k);
+  launch_cfl_many<F>(L, m0, b->g[FU_CFL], b->nxmax);                               // boxes 3, 4, 6
   launch_dt_final_many(L, b->g[FU_DT]);
   launch_source_many<F>(L, m0, b->g[FU_SRC], b->g[FU_SRCG]);                        // boxes 7a-7c
   if (m0.visc) launch_visc_many<F>(L, b->g[FU_VISC1], b->g[FU_VISC]);              // box 7d

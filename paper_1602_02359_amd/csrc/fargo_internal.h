@@ -404,7 +404,7 @@ template <typename R>
 unsigned cfl_args(const Mesh &m, const StateT<R> &s, double *v0, double *ringrate, double *ringshear, int *err,
                   void *dst);
 template <typename R>
-void launch_cfl_many(Launch &L, const ManyGrid &g, int nxmax);
+void launch_cfl_many(Launch &L, const Mesh &m0, const ManyGrid &g, int nxmax);
 size_t dt_final_args_bytes();
 unsigned dt_final_args(const Mesh &m, const DevWords &w, const double *ringrate, const double *ringshear, void *dst);
 void launch_dt_final_many(Launch &L, const ManyGrid &g);

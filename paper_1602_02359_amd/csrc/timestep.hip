@@ -1,14 +1,17 @@
 // Box 3 (bulk azimuthal velocity per ring, Eq. 37), box 6 (time step,
 // Eq. cfl2 items 1-3, Eq. 38) and the orbital-advection split of Eq. 29.
 //
-// One workgroup per active ring computes the ring's v0 and, for each of its
-// zones, the cell time step and the shear rate; the ring minimum/maximum goes
-// to a per-ring slot.  A single workgroup then reduces the slots (exact and
-// order independent: min/max) and forms dt.  The split of every ring's
-// displacement into (N, xi) is taken by the ring kernel of the X transport
-// (and by k_split for the stand-alone entry point).  The time step and the
-// split use floating-point contraction off and the operation order of the
-// written definition, so that the integer shift N is reproducible bit for bit.
+// A wave (or, where rings are few or long, a workgroup of four) takes a ring
+// at a time: the ring's v0 and, for each of its zones, the cell time step and
+// the shear rate; the ring's extremes go to its slot.  A single workgroup then
+// reduces the slots (exact and order independent: min/max) and forms dt.  The
+// split of every ring's displacement into (N, xi) is taken by the ring kernel
+// of the X transport (and by k_split for the stand-alone entry point).  The
+// time step and the split use floating-point contraction off and the operation
+// order of the written definition, so that the integer shift N is reproducible
+// bit for bit.
+#include <type_traits>
+
 #include "fargo_internal.h"
 
 namespace fargo {
@@ -94,31 +97,9 @@ struct Add { __device__ double operator()(double a, double b) const { return a +
 
 __global__ void k_set_dt(DevWords w, double dt) { *w.dt = dt; }
 
-// Bulk velocity of a ring (max/min exact; the mean in a fixed tree order).
-template <int M>
-__device__ inline double ring_bulk(const Mesh &m, const double (&v)[M], int tid, double *lds) {
-  const int B = blockDim.x;
-  if (m.v0_mean) {
-    double s = 0.0;
-#pragma unroll
-    for (int mm = 0; mm < M; mm++)
-      if (tid + B * mm < m.nx) s += v[mm];
-    return block_reduce(s, Add(), 0.0, lds) / m.nx;
-  }
-  double vmax = -HUGE_VAL, vmin = HUGE_VAL;
-#pragma unroll
-  for (int mm = 0; mm < M; mm++)
-    if (tid + B * mm < m.nx) {
-      vmax = v[mm] > vmax ? v[mm] : vmax;
-      vmin = v[mm] < vmin ? v[mm] : vmin;
-    }
-  block_reduce2(vmax, Max(), -HUGE_VAL, vmin, Min(), HUGE_VAL, lds);
-  return 0.5 * (vmax + vmin);
-}
-
 // Constants of Eq. cfl2 for ring (j, k): lengths and their reciprocals.
 struct CflRing {
-  double Lx, iLx, iLy, iLz, iL2, k3, dXp;
+  double Lx, iLx, iLy, iLz, iL2, k3, dXp, idXp;
 };
 __device__ inline CflRing cfl_ring(const Mesh &m, int j, int k, bool shear_on) {
 #pragma clang fp contract(off)
@@ -133,6 +114,7 @@ __device__ inline CflRing cfl_ring(const Mesh &m, int j, int k, bool shear_on) {
   C.iL2 = 1.0 / (Lmin * Lmin);
   C.k3 = 4.0 * m.cvnr * m.cvnr;
   C.dXp = shear_on ? m.DX(j + 1, k) : 1.0;
+  C.idXp = 1.0 / C.dXp;
   return C;
 }
 
@@ -142,12 +124,13 @@ __device__ inline CflRing cfl_ring(const Mesh &m, int j, int k, bool shear_on) {
 // non-finite or non-positive state in `bad`.  q: sound speed (isothermal)
 // or internal energy; vxc, vxp: full v_x on the zone's two X faces; vb: the
 // ring's bulk velocity (0 without orbital advection).
-__device__ inline double zone_rate2(const Mesh &m, const CflRing &C, double vb, double vxc, double vxp, double rho,
-                                    double q, double vyc, double vyp, double vzc, double vzp, double nu, int &bad) {
+template <bool D3, bool ADI>
+__device__ inline double zone_rate2(const CflRing &C, double vb, double vxc, double vxp, double rho, double q,
+                                    double vyc, double vyp, double vzc, double vzp, double nu, double gamma, int &bad) {
 #pragma clang fp contract(off)
   double cw2; // squared wave speed
-  if (m.eos == FARGO_ISOTHERMAL) cw2 = q * q;
-  else cw2 = m.gamma * ((m.gamma - 1.0) * q) / rho;
+  if (!ADI) cw2 = q * q;
+  else cw2 = gamma * ((gamma - 1.0) * q) / rho;
   bad |= !(rho > 0.0) || !isfinite(rho) || !isfinite(cw2) || !isfinite(vxc) || !isfinite(vyc);
   // item 1: sound waves (squared rate); item 2: fluid motion; item 3:
   // artificial viscosity on compressed directions
@@ -156,18 +139,17 @@ __device__ inline double zone_rate2(const Mesh &m, const CflRing &C, double vb, 
   const double uy = fmax(fabs(vyc), fabs(vyp));
   double r2 = fmax(ux * C.iLx, uy * C.iLy);
   const double dvx = vxp - vxc, dvy = vyp - vyc;
-  double r3 = 0.0;
-  if (dvx < 0.0) r3 = fmax(r3, C.k3 * fabs(dvx) * C.iLx);
-  if (dvy < 0.0) r3 = fmax(r3, C.k3 * fabs(dvy) * C.iLy);
-  if (m.d3) {
+  // (an expansion gives a negative number, which the zero bounds)
+  double r3 = fmax(fmax(0.0, C.k3 * -dvx * C.iLx), C.k3 * -dvy * C.iLy);
+  if (D3) {
     bad |= !isfinite(vzc);
     const double uz = fmax(fabs(vzc), fabs(vzp));
     r2 = fmax(r2, uz * C.iLz);
     const double dvz = vzp - vzc;
-    if (dvz < 0.0) r3 = fmax(r3, C.k3 * fabs(dvz) * C.iLz);
+    r3 = fmax(r3, C.k3 * -dvz * C.iLz);
   }
   double rate2 = r1s + r2 * r2 + r3 * r3;
-  if (m.visc) { // item 4: viscosity, 4 nu / Delta^2
+  if (!D3 && !ADI) { // item 4: viscosity, 4 nu / Delta^2 (nu = 0 without)
     const double r4 = 4.0 * nu * C.iL2;
     rate2 += r4 * r4;
   }
@@ -175,108 +157,237 @@ __device__ inline double zone_rate2(const Mesh &m, const CflRing &C, double vb, 
   return rate2;
 }
 
-// Rings in XCD-contiguous logical order, by tiles of 16 planes with k fastest
-// within a tile: the rings holding a ring's k + 1 and j + 1 neighbours (v_z
-// and v_y on its upper faces) were read one and 16 rings earlier, still in L2
-// except across a tile boundary.  M zones per thread.
+// x / L from L's correctly rounded reciprocal r: the quotient's remainder is
+// exact in one fused operation, and after two such corrections the result is
+// the correctly rounded quotient (Markstein 1990: the second one starts from a
+// faithful quotient), for finite x away from underflow.  Five instructions; the
+// division expands to more than twice that.
+__device__ inline double div_by(double x, double L, double r) {
+  double q = x * r;
+  q = fma(fma(-q, L, x), r, q);
+  return fma(fma(-q, L, x), r, q);
+}
+// Eq. 38 between a zone and its radial neighbour.  An infinite velocity, which
+// div_by would turn into a NaN, sets *inf (its shear rate is infinite).
+__device__ inline double shear_rate(const CflRing &C, double vxc, double vxn, int &inf) {
+#pragma clang fp contract(off)
+  inf |= __builtin_isinf(vxc) | __builtin_isinf(vxn);
+  return fabs(div_by(vxc, C.Lx, C.iLx) - div_by(vxn, C.dXp, C.idXp));
+}
+
+// Two consecutive zones of a row, at any zone.
+template <typename R>
+using Pair = R __attribute__((ext_vector_type(2), aligned(sizeof(R))));
+
+// LDS elements a ring of n zones takes: its v_x, the first zone's again after
+// the last, and what the last pair of lanes reads beyond it.
+__host__ __device__ inline int cfl_vlen(int n) { return (n + 7) & ~1; }
+
+__device__ inline double lane63(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_readlane((int)b, 63), hi = __builtin_amdgcn_readlane((int)(b >> 32), 63);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
+// The time-step pass.  A ring belongs to one wave (W = 1: no barrier, and the
+// waves of a compute unit hide each other's loads), or to a workgroup of four
+// (W = 4: rings too few to fill the chip, or too long for one wave's LDS).  A
+// lane takes two consecutive zones of every 128-zone chunk.  First the ring's
+// v_x goes to LDS, which gives v0 and later each zone's two X faces; then the
+// other fields are streamed past it, the next chunk's loads in flight while
+// one is computed.  Bound by memory: it reads 5 fields on 3D meshes, 5.8 TB/s
+// on the 2048 x 768 x 96 disk in FP64.  Against a workgroup per ring that held
+// it in registers (two divisions a zone): 1.50 to 1.05 ms there, FP32 1.31 to
+// 0.59; 1536 x 512 x 128 1.02 to 0.73; 3072 x 1024 46 to 22 us; box of 160 x 144
+// x 120 58 to 33; the FP32 batch of 256 disks 658 us in six launches to 297 in
+// one.  On a few hundred rings latency is all there is (384 x 128: 5.0 to 5.7
+// us).
+// Rings come in XCD-contiguous logical order, by tiles of 16 planes with k
+// fastest within a tile: the rings holding a ring's k + 1 and j + 1 neighbours
+// (v_z and v_y on its upper faces) were read one and 16 rings earlier, still
+// in L2 except across a tile boundary.  (Four rings in a row per wave, for a
+// quarter of the slots, measured 666 against 594 us in FP32.)
 // The state may be stored in FP32 (R = float); the time step is always formed
 // in FP64 from the stored values.
-template <int M, typename R, int NB>
-__device__ __forceinline__ void cfl_ring_body(Mesh m, StateT<R> s, int with_cfl, double *__restrict__ v0,
-                                                  double *__restrict__ ringrate, double *__restrict__ ringshear,
-                                                  int *__restrict__ err, unsigned bid_, unsigned nbk_) {
+template <int W, bool CFL, bool D3, bool ADI, typename R>
+__device__ __forceinline__ void cfl_body(Mesh m, StateT<R> s, double *__restrict__ v0,
+                                         double *__restrict__ ringrate, double *__restrict__ ringshear,
+                                         int *__restrict__ err, unsigned bid_, unsigned nbk_) {
 #pragma clang fp contract(off)
-  extern __shared__ double V[]; // the ring's v_x
-  __shared__ double red[3 * MAXW];
-  const unsigned L = xcd_remap(bid_, nbk_);
+  extern __shared__ double cfl_lds[];
+  __shared__ double red[W == 1 ? 1 : 3 * MAXW];
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = m.nx, nc = (n + 127) >> 7;
+  // (V[-1] takes the unused half of a one-zone ring's pair)
+  R *V = reinterpret_cast<R *>(cfl_lds) + (W == 1 ? wv * cfl_vlen(n) : 0) + 2;
+  const unsigned blk = xcd_remap(bid_, nbk_);
+  const int L = (int)(W == 1 ? blk * (blockDim.x >> 6) + (unsigned)wv : blk);
+  if (L >= m.nring) return;
+  const unsigned py = (unsigned)m.pitch, pz = (unsigned)m.plane();
+  const R *qf = ADI ? s.e : s.cs, *nuf = !D3 && !ADI && m.visc ? s.nu : qf;
   constexpr int KT = 16;
-  const unsigned tile = L / ((unsigned)m.ny * KT), q = L % ((unsigned)m.ny * KT);
+  // A row's pair of zones for chunk c: past the ring's end, and on the last
+  // zone of an odd ring, the ring's last two zones.  (No branch: every load of
+  // a chunk is issued before the first one is waited for.  A ring of one zone
+  // has it second in the pair, and no use for the first.)
+  auto zone = [&](int c) { return 128 * c + 2 * lane; };
+  auto at = [&](int c) { return min(zone(c), n - 2); };
+  auto ld = [&](const R *row, int c) { return *reinterpret_cast<const Pair<R> *>(row + at(c)); };
+  struct Chunk {
+    Pair<R> r, q, y0, y1, z0, z1, nu, s;
+  };
+  const bool visc = !D3 && !ADI && m.visc;
+  double rmax = 0.0, smax = 0.0;
+  int bad = 0, inf = 0;
+  const unsigned tile = (unsigned)L / ((unsigned)m.ny * KT), q = (unsigned)L % ((unsigned)m.ny * KT);
   const int kb = (int)tile * KT, kt = min(KT, m.nz - kb);
   const int kk = kb + (int)(q % (unsigned)kt), jj = (int)(q / (unsigned)kt);
   const int j = m.j0 + jj, k = m.k0 + kk;
   const int r = kk * m.ny + jj; // ring index (k - k0) * ny + (j - j0)
-  const int tid = threadIdx.x, B = blockDim.x, n = m.nx;
   const unsigned base = m.o32(0, j, k);
-  const bool shear_on = with_cfl && m.fargo && m.shear_c0 > 0.0 && j + 1 < m.jn;
-  const unsigned py = (unsigned)m.pitch, pz = (unsigned)m.plane();
-  // Every load of the ring is issued before the first use (indices clamped
-  // to the ring, so no load sits behind a branch), which keeps all of them
-  // in flight together.
-  const R *qf = m.eos == FARGO_ISOTHERMAL ? s.cs : s.e;
-  R fx[M], fr[M] = {}, fq[M] = {}, fy0[M] = {}, fy1[M] = {}, fz0[M] = {}, fz1[M] = {}, fn[M] = {}, fs[M] = {};
+  const bool shear_on = CFL && m.fargo && m.shear_c0 > 0.0 && j + 1 < m.jn;
+  const unsigned ps = shear_on ? py : 0u; // the next ring, or this one again
+  auto load = [&](int c, Chunk &z) {
+    z.r = ld(s.rho + base, c);
+    z.q = ld(qf + base, c);
+    z.y0 = ld(s.vy + base, c);
+    z.y1 = ld(s.vy + base + py, c);
+    if (D3) {
+      z.z0 = ld(s.vz + base, c);
+      z.z1 = ld(s.vz + base + pz, c);
+    }
+    if (!D3 && !ADI) z.nu = ld(nuf + base, c);
+    z.s = ld(s.vx + base + ps, c);
+  };
+  // v_x into LDS, with its extremes, four chunks at a time (chunks past the
+  // ring's end read its last zones again, which changes neither); the first
+  // chunk's other fields are on their way before a v_x is used
+  double vmax = -HUGE_VAL, vmin = HUGE_VAL;
+  Chunk z[2];
+  const int c0 = W == 1 ? 0 : wv;
+  auto vx_load = [&](int c, Pair<R> (&x)[4]) {
 #pragma unroll
-  for (int mm = 0; mm < M; mm++) {
-    const unsigned c = base + (unsigned)min(tid + B * mm, n - 1);
-    fx[mm] = s.vx[c];
-    if (with_cfl) {
-      fr[mm] = s.rho[c];
-      fq[mm] = qf[c];
-      fy0[mm] = s.vy[c];
-      fy1[mm] = s.vy[c + py];
-      if (m.d3) {
-        fz0[mm] = s.vz[c];
-        fz1[mm] = s.vz[c + pz];
-      }
-      if (m.visc) fn[mm] = s.nu[c];
-      if (shear_on) fs[mm] = s.vx[c + py];
+    for (int u = 0; u < 4; u++) x[u] = ld(s.vx + base, c + u * W);
+  };
+  auto vx_take = [&](int c, Pair<R> (&x)[4]) {
+#pragma unroll
+    for (int u = 0; u < 4; u++) {
+      if (n == 1) x[u].x = x[u].y;
+      vmax = fmax(vmax, fmax((double)x[u].x, (double)x[u].y));
+      vmin = fmin(vmin, fmin((double)x[u].x, (double)x[u].y));
+      *reinterpret_cast<Pair<R> *>(V + at(c + u * W)) = x[u];
+    }
+  };
+  {
+    Pair<R> x[4];
+    vx_load(c0, x);
+    if (CFL) load(c0, z[0]);
+    vx_take(c0, x);
+    if (c0 == 0 && lane == 0) V[n] = x[0].x;
+#pragma unroll 1
+    for (int c = c0 + 4 * W; c < nc; c += 4 * W) {
+      vx_load(c, x);
+      vx_take(c, x);
     }
   }
   // an FP32 v_x is a deviation from the ring's FP64 background: the full
-  // velocity is formed in FP64
-  double vbg = 0.0, vbg_p = 0.0;
-  if constexpr (sizeof(R) == 4) {
-    vbg = m.bg(BG_V, j, k);
-    if (shear_on) vbg_p = m.bg(BG_V, j + 1, k);
+  // velocity is formed in FP64 (adding it is monotone, so the extremes of
+  // the sums are the sums of the extremes)
+  const double vbg = sizeof(R) == 4 ? m.bg(BG_V, j, k) : 0.0;
+  const double vbg_p = sizeof(R) == 4 && shear_on ? m.bg(BG_V, j + 1, k) : 0.0;
+  if (W == 1) {
+    vmax = lane63(wave_reduce_dpp(vmax, Max(), -HUGE_VAL));
+    vmin = lane63(wave_reduce_dpp(vmin, Min(), HUGE_VAL));
+    // the wave's own LDS writes are seen by all of its lanes
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  } else {
+    block_reduce2(vmax, Max(), -HUGE_VAL, vmin, Min(), HUGE_VAL, red);
   }
-  double vx[M];
-#pragma unroll
-  for (int mm = 0; mm < M; mm++) {
-    int i = tid + B * mm;
-    vx[mm] = i < n ? (double)fx[mm] + vbg : 0.0;
-    if (i < n) V[i] = vx[mm];
+  double vb_ring = 0.5 * ((vmax + vbg) + (vmin + vbg));
+  if (m.v0_mean) { // summed by every wave in one order, whatever W
+    double a = 0.0;
+    for (int i = lane; i < n; i += 64) a += (double)V[i] + vbg;
+    for (int o = 32; o > 0; o >>= 1) a += __shfl_xor(a, o, 64);
+    vb_ring = a / n;
   }
-  // the barriers of the reduction also make V visible to the block
-  const double vb_ring = ring_bulk<M>(m, vx, tid, red);
-  if (tid == 0) v0[r] = vb_ring;
-  if (!with_cfl) return;
-  const double vb = m.fargo ? vb_ring : 0.0;
-  // the smallest step is 1 / sqrt of the largest sum of squared rates (taken
-  // in k_dt_final)
-  const CflRing C = cfl_ring(m, j, k, shear_on);
-  double rmax = 0.0, smax = 0.0;
-  int bad = 0;
-#pragma unroll
-  for (int mm = 0; mm < M; mm++) {
-    int i = tid + B * mm;
-    if (i >= n) continue;
-    const double vxc = vx[mm], vxp = V[i + 1 == n ? 0 : i + 1];
-    const double rate2 = zone_rate2(m, C, vb, vxc, vxp, (double)fr[mm], (double)fq[mm], (double)fy0[mm],
-                                    (double)fy1[mm], (double)fz0[mm], (double)fz1[mm], (double)fn[mm], bad);
-    if (rate2 >= 0.0) rmax = rate2 > rmax ? rate2 : rmax;
-    if (shear_on) {
-      double sh = fabs(vxc / C.Lx - ((double)fs[mm] + vbg_p) / C.dXp);
-      if (sh > smax) smax = sh;
+  if (tid == (W == 1 ? 64 * wv : 0)) v0[r] = vb_ring;
+  if (CFL) {
+    const double vb = m.fargo ? vb_ring : 0.0;
+    // the smallest step is 1 / sqrt of the largest sum of squared rates
+    // (taken in k_dt_final)
+    const CflRing C = cfl_ring(m, j, k, shear_on);
+    double sring = 0.0;
+    auto one = [&](double x0, double x1, R rho, R q, R y0, R y1, R z0, R z1, R nu, R xs) {
+      const double vxc = x0 + vbg, vxp = x1 + vbg;
+      const double rate2 = zone_rate2<D3, ADI>(C, vb, vxc, vxp, (double)rho, (double)q, (double)y0, (double)y1,
+                                               (double)z0, (double)z1, visc ? (double)nu : 0.0, m.gamma, bad);
+      if (rate2 >= 0.0) rmax = rate2 > rmax ? rate2 : rmax;
+      const double sh = shear_rate(C, vxc, (double)xs + vbg_p, inf);
+      sring = sh > sring ? sh : sring;
+    };
+    // (every lane takes its pair, so that no load of a chunk outlives it; a
+    // lane past the ring's end takes the last zones once more)
+    auto zones = [&](int c, const Chunk &z) {
+      const int i = at(c);
+      const Pair<R> x = *reinterpret_cast<const Pair<R> *>(V + i);
+      const double x0 = (double)x.x, x1 = (double)x.y, x2 = (double)V[i + 2];
+      one(x1, x2, z.r.y, z.q.y, z.y0.y, z.y1.y, D3 ? z.z0.y : R(0), D3 ? z.z1.y : R(0), z.nu.y, z.s.y);
+      if (n > 1) one(x0, x1, z.r.x, z.q.x, z.y0.x, z.y1.x, D3 ? z.z0.x : R(0), D3 ? z.z1.x : R(0), z.nu.x, z.s.x);
+    };
+#pragma unroll 1
+    for (int c = c0; c < nc; c += 2 * W) {
+      load(c + W, z[1]);
+      zones(c, z[0]);
+      if (c + W >= nc) break;
+      load(c + 2 * W, z[0]);
+      zones(c + W, z[1]);
+    }
+    if (shear_on) smax = inf ? HUGE_VAL : (sring > smax ? sring : smax);
+  }
+  if (!CFL) return;
+  if (W == 1) {
+    rmax = wave_reduce_dpp(rmax, Max(), 0.0);
+    smax = wave_reduce_dpp(smax, Max(), 0.0);
+    const bool anybad = __builtin_amdgcn_ballot_w64(bad != 0) != 0;
+    if (lane == 63) {
+      ringrate[L] = rmax; // the ring's largest squared rate
+      ringshear[L] = smax;
+      if (anybad) atomicOr(err, 1);
+    }
+  } else {
+    int anybad = bad;
+    block_reduce2(rmax, Max(), 0.0, smax, Max(), 0.0, red, &anybad);
+    if (tid == 0) {
+      ringrate[L] = rmax;
+      ringshear[L] = smax;
+      if (anybad) atomicOr(err, 1);
     }
   }
-  int anybad = bad;
-  block_reduce2(rmax, Max(), 0.0, smax, Max(), 0.0, red, &anybad);
-  if (tid == 0) {
-    ringrate[r] = rmax; // the ring's largest squared rate
-    ringshear[r] = smax;
-    if (anybad) atomicOr(err, 1);
-  }
 }
-template <int M, typename R, int NB>
-__global__ __launch_bounds__(NB) void k_cfl_ring(Mesh m, StateT<R> s, int with_cfl, double *__restrict__ v0,
-                                                  double *__restrict__ ringrate, double *__restrict__ ringshear,
-                                                  int *__restrict__ err) {
-  cfl_ring_body<M, R, NB>(m, s, with_cfl, v0, ringrate, ringshear, err, blockIdx.x, gridDim.x);
+constexpr int CFL_BS1 = 128; // threads of a workgroup with W = 1: two waves
+// CFL: the rates as well as v0
+template <int W, bool CFL, bool D3, bool ADI, typename R>
+__global__ __launch_bounds__(W == 1 ? CFL_BS1 : 256) void k_cfl_ring(Mesh m, StateT<R> s, double *__restrict__ v0,
+                                                                     double *__restrict__ ringrate,
+                                                                     double *__restrict__ ringshear,
+                                                                     int *__restrict__ err) {
+  cfl_body<W, CFL, D3, ADI, R>(m, s, v0, ringrate, ringshear, err, blockIdx.x, gridDim.x);
 }
+
+// One wave per ring (else four) where there are at least two rings per SIMD of
+// the chip (a few hundred rings, 633 or 768 zones each: 6.6 and 7.2 us with
+// four waves, 7.4 and 7.7 with one; 17280 rings of 160 zones 89 and 36 us, 7181
+// of 501 in FP32 48 and 22) and a ring takes at most 10 KB, so that the LDS of a
+// compute unit holds the sixteen waves its registers do (65536 rings of 1536
+// doubles: 726 us with four waves, 744 with one; 73728 of 2048: 1049 and 1090,
+// in FP32, 8 KB a ring, 702 and 594).
+inline bool cfl_wave(const Mesh &m, size_t elem) { return m.nring >= 2048 && (size_t)m.nx * elem <= 10240; }
 
 // Rings longer than one workgroup holds, in segments of CFL_SEG zones (256
 // threads, four zones each).  First each segment's largest and smallest
 // full v_x (or its sum, for the mean), then each segment combines its ring's
-// entries into v0 (min/max exactly as in ring_bulk; the mean as the sum of the
+// entries into v0 (min/max exactly; the mean as the sum of the
 // segment sums in segment order, over nx) and takes Eq. cfl2 on its zones,
 // with the v_x of the zone after its last read from memory.
 template <typename R>
@@ -317,7 +428,7 @@ __global__ __launch_bounds__(256) void k_bulk_seg(Mesh m, StateT<R> s) {
   }
 }
 
-template <typename R>
+template <bool D3, bool ADI, typename R>
 __global__ __launch_bounds__(256) void k_cfl_seg(Mesh m, StateT<R> s, int with_cfl, double *__restrict__ v0,
                                                  double *__restrict__ ringrate, double *__restrict__ ringshear,
                                                  int *__restrict__ err) {
@@ -358,24 +469,26 @@ __global__ __launch_bounds__(256) void k_cfl_seg(Mesh m, StateT<R> s, int with_c
   const double vb = m.fargo ? vb_ring : 0.0;
   const CflRing C = cfl_ring(m, j, k, shear_on);
   const unsigned py = (unsigned)m.pitch, pz = (unsigned)m.plane();
-  const R *qf = m.eos == FARGO_ISOTHERMAL ? s.cs : s.e;
+  const R *qf = ADI ? s.e : s.cs;
   double rmax = 0.0, smax = 0.0;
-  int bad = 0;
+  int bad = 0, inf = 0;
 #pragma unroll
   for (int mm = 0; mm < M; mm++) {
     const int i = i0 + tid + 256 * mm;
     if (i >= i1) continue;
     const unsigned c = base + (unsigned)i;
     const double vxc = V[i - i0], vxp = V[i - i0 + 1];
-    const double rate2 = zone_rate2(m, C, vb, vxc, vxp, (double)s.rho[c], (double)qf[c], (double)s.vy[c],
-                                    (double)s.vy[c + py], m.d3 ? (double)s.vz[c] : 0.0,
-                                    m.d3 ? (double)s.vz[c + pz] : 0.0, m.visc ? (double)s.nu[c] : 0.0, bad);
+    const double rate2 = zone_rate2<D3, ADI>(C, vb, vxc, vxp, (double)s.rho[c], (double)qf[c], (double)s.vy[c],
+                                             (double)s.vy[c + py], D3 ? (double)s.vz[c] : 0.0,
+                                             D3 ? (double)s.vz[c + pz] : 0.0,
+                                             !D3 && !ADI && m.visc ? (double)s.nu[c] : 0.0, m.gamma, bad);
     if (rate2 >= 0.0) rmax = rate2 > rmax ? rate2 : rmax;
     if (shear_on) {
-      const double sh = fabs(vxc / C.Lx - ((double)s.vx[c + py] + vbg_p) / C.dXp);
+      const double sh = shear_rate(C, vxc, (double)s.vx[c + py] + vbg_p, inf);
       if (sh > smax) smax = sh;
     }
   }
+  if (inf) smax = HUGE_VAL;
   int anybad = bad;
   block_reduce2(rmax, Max(), 0.0, smax, Max(), 0.0, red, &anybad);
   if (tid == 0) {
@@ -385,8 +498,7 @@ __global__ __launch_bounds__(256) void k_cfl_seg(Mesh m, StateT<R> s, int with_c
   }
 }
 
-// One workgroup: dt from the ring slots (or the imposed value), then the split
-// of every ring.  A non-positive or non-finite dt is flagged and replaced by 0,
+// One workgroup: dt from the ring slots.  A non-positive or non-finite dt is flagged and replaced by 0,
 // which leaves the state unchanged.
 __device__ __forceinline__ void dt_final_body(const Mesh &m, const DevWords &w, const double *__restrict__ ringrate,
                                               const double *__restrict__ ringshear) {
@@ -434,12 +546,13 @@ struct CflArgs {
   int *err;
   unsigned nb;
 };
-template <int M, typename R>
-__global__ __launch_bounds__(256) void k_cfl_ring_many(const void *args, const uint2 *tab) {
+// (a wave per ring whatever the mesh: a batch has rings enough)
+template <bool ADI, typename R>
+__global__ __launch_bounds__(CFL_BS1) void k_cfl_ring_many(const void *args, const uint2 *tab) {
   const uint2 t = many_block(tab);
   if (t.x == MANY_NONE) return;
   const CflArgs<R> a = many_args<CflArgs<R>>(args, t.x);
-  cfl_ring_body<M, R, 256>(a.m, a.s, 1, a.v0, a.ringrate, a.ringshear, a.err, t.y, a.nb);
+  cfl_body<1, true, false, ADI, R>(a.m, a.s, a.v0, a.ringrate, a.ringshear, a.err, t.y, a.nb);
 }
 struct DtArgs {
   Mesh m;
@@ -468,13 +581,6 @@ __global__ __launch_bounds__(256) void k_split(Mesh m, const double *__restrict_
   xi[r] = D - rn;
 }
 
-// NB threads per ring: 256 up to 2048 zones, 512 up to 4096
-template <int M, typename R, int NB = 256>
-void cfl_launch(Launch &L, const Mesh &m, const StateT<R> &s, int with_cfl, double *v0, double *rmin, double *rsh,
-                int *err) {
-  k_cfl_ring<M, R, NB><<<m.nring, NB, (size_t)m.nx * sizeof(double), L.s>>>(m, s, with_cfl, v0, rmin, rsh, err);
-}
-
 } // namespace
 
 void launch_set_dt(Launch &L, const DevWords &w, double dt) {
@@ -487,38 +593,31 @@ template <typename R>
 void launch_cfl(Launch &L, const Mesh &m, const StateT<R> &s, int with_cfl, double *v0, double *ringrate,
                 double *ringshear, int *err) {
   prof_begin(L, K_CFL);
-  if (m.cseg > 1) { // rings in segments
-    const unsigned nb = (unsigned)m.nring * (unsigned)m.cseg;
-    k_bulk_seg<R><<<nb, 256, 0, L.s>>>(m, s);
-    k_cfl_seg<R><<<nb, 256, 0, L.s>>>(m, s, with_cfl, v0, ringrate, ringshear, err);
-    prof_end(L, K_CFL);
-    return;
-  }
-  if (m.nx > 1792 && m.nx <= 2048) { // 512 threads of 4 zones
-    cfl_launch<4, R, 512>(L, m, s, with_cfl, v0, ringrate, ringshear, err);
-    prof_end(L, K_CFL);
-    return;
-  }
-  if (m.nx > 2048) { // nx <= 4096: 512 threads, 5 to 8 zones each
-    switch ((m.nx + 511) / 512) {
-    case 5: cfl_launch<5, R, 512>(L, m, s, with_cfl, v0, ringrate, ringshear, err); break;
-    case 6: cfl_launch<6, R, 512>(L, m, s, with_cfl, v0, ringrate, ringshear, err); break;
-    case 7: cfl_launch<7, R, 512>(L, m, s, with_cfl, v0, ringrate, ringshear, err); break;
-    default: cfl_launch<8, R, 512>(L, m, s, with_cfl, v0, ringrate, ringshear, err); break;
+  auto go = [&](auto d3, auto adi) {
+    constexpr bool D3 = decltype(d3)::value, ADI = decltype(adi)::value;
+    if (m.cseg > 1) { // rings in segments
+      const unsigned nb = (unsigned)m.nring * (unsigned)m.cseg;
+      k_bulk_seg<R><<<nb, 256, 0, L.s>>>(m, s);
+      k_cfl_seg<D3, ADI, R><<<nb, 256, 0, L.s>>>(m, s, with_cfl, v0, ringrate, ringshear, err);
+      return;
     }
-    prof_end(L, K_CFL);
-    return;
-  }
-  switch ((m.nx + 255) / 256) { // zones per thread
-  case 1: cfl_launch<1, R>(L, m, s, with_cfl, v0, ringrate, ringshear, err); break;
-  case 2: cfl_launch<2, R>(L, m, s, with_cfl, v0, ringrate, ringshear, err); break;
-  case 3: cfl_launch<3, R>(L, m, s, with_cfl, v0, ringrate, ringshear, err); break;
-  case 4: cfl_launch<4, R>(L, m, s, with_cfl, v0, ringrate, ringshear, err); break;
-  case 5: cfl_launch<5, R>(L, m, s, with_cfl, v0, ringrate, ringshear, err); break;
-  case 6: cfl_launch<6, R>(L, m, s, with_cfl, v0, ringrate, ringshear, err); break;
-  case 7: cfl_launch<7, R>(L, m, s, with_cfl, v0, ringrate, ringshear, err); break;
-  default: cfl_launch<8, R>(L, m, s, with_cfl, v0, ringrate, ringshear, err); break;
-  }
+    const bool wave = cfl_wave(m, sizeof(R));
+    const unsigned per = wave ? CFL_BS1 / 64 : 1, nb = ((unsigned)m.nring + per - 1) / per;
+    const size_t lds = (size_t)per * cfl_vlen(m.nx) * sizeof(R);
+    auto w = [&](auto wt) {
+      constexpr int W = decltype(wt)::value, BS = W == 1 ? CFL_BS1 : 256;
+      if (with_cfl) k_cfl_ring<W, true, D3, ADI, R><<<nb, BS, lds, L.s>>>(m, s, v0, ringrate, ringshear, err);
+      else k_cfl_ring<W, false, false, false, R><<<nb, BS, lds, L.s>>>(m, s, v0, ringrate, ringshear, err);
+    };
+    if (wave) w(std::integral_constant<int, 1>{});
+    else w(std::integral_constant<int, 4>{});
+  };
+  auto by_eos = [&](auto d3) {
+    if (m.eos == FARGO_ADIABATIC) go(d3, std::true_type{});
+    else go(d3, std::false_type{});
+  };
+  if (m.d3) by_eos(std::true_type{});
+  else by_eos(std::false_type{});
   prof_end(L, K_CFL);
 }
 
@@ -547,25 +646,17 @@ size_t cfl_args_bytes() { return sizeof(CflArgs<R>); }
 template <typename R>
 unsigned cfl_args(const Mesh &m, const StateT<R> &s, double *v0, double *ringrate, double *ringshear, int *err,
                   void *dst) {
-  *(CflArgs<R> *)dst = CflArgs<R>{m, s, v0, ringrate, ringshear, err, (unsigned)m.nring};
-  return (unsigned)m.nring;
+  const unsigned nb = (unsigned)((m.nring + CFL_BS1 / 64 - 1) / (CFL_BS1 / 64));
+  *(CflArgs<R> *)dst = CflArgs<R>{m, s, v0, ringrate, ringshear, err, nb};
+  return nb;
 }
 
-// rings of at most 1792 zones: 256 threads of M = ceil(nxmax / 256) zones for
-// every mesh of the launch (a shorter ring leaves some of them idle)
 template <typename R>
-void launch_cfl_many(Launch &L, const ManyGrid &g, int nxmax) {
+void launch_cfl_many(Launch &L, const Mesh &m0, const ManyGrid &g, int nxmax) {
   prof_begin(L, K_CFL);
-  const size_t sh = (size_t)nxmax * sizeof(double);
-  switch ((nxmax + 255) / 256) {
-  case 1: k_cfl_ring_many<1, R><<<g.nblk, 256, sh, L.s>>>(g.args, g.tab); break;
-  case 2: k_cfl_ring_many<2, R><<<g.nblk, 256, sh, L.s>>>(g.args, g.tab); break;
-  case 3: k_cfl_ring_many<3, R><<<g.nblk, 256, sh, L.s>>>(g.args, g.tab); break;
-  case 4: k_cfl_ring_many<4, R><<<g.nblk, 256, sh, L.s>>>(g.args, g.tab); break;
-  case 5: k_cfl_ring_many<5, R><<<g.nblk, 256, sh, L.s>>>(g.args, g.tab); break;
-  case 6: k_cfl_ring_many<6, R><<<g.nblk, 256, sh, L.s>>>(g.args, g.tab); break;
-  default: k_cfl_ring_many<7, R><<<g.nblk, 256, sh, L.s>>>(g.args, g.tab); break;
-  }
+  const size_t sh = (size_t)(CFL_BS1 / 64) * cfl_vlen(nxmax) * sizeof(R);
+  if (m0.eos == FARGO_ADIABATIC) k_cfl_ring_many<true, R><<<g.nblk, CFL_BS1, sh, L.s>>>(g.args, g.tab);
+  else k_cfl_ring_many<false, R><<<g.nblk, CFL_BS1, sh, L.s>>>(g.args, g.tab);
   prof_end(L, K_CFL);
 }
 
@@ -586,7 +677,7 @@ template unsigned cfl_args<double>(const Mesh &, const StateT<double> &, double 
 template unsigned cfl_args<float>(const Mesh &, const StateT<float> &, double *, double *, double *, int *, void *);
 template size_t cfl_args_bytes<double>();
 template size_t cfl_args_bytes<float>();
-template void launch_cfl_many<double>(Launch &, const ManyGrid &, int);
-template void launch_cfl_many<float>(Launch &, const ManyGrid &, int);
+template void launch_cfl_many<double>(Launch &, const Mesh &, const ManyGrid &, int);
+template void launch_cfl_many<float>(Launch &, const Mesh &, const ManyGrid &, int);
 
 } // namespace fargo

@@ -47,3 +47,50 @@ def test_chunked_step_fp32(geo, nx, ny, nz):
     prob = make(nx=nx, ny=ny, noise=1e-2, **({} if nz == 1 else {"nz": nz}))
     prob.params["precision"] = "fp32"
     assert _step(prob) <= 2e-6
+
+
+@pytest.mark.parametrize("nx,ny,nz,eos,v0", [(1, 2100, 1, "adi", "minmax"), (2, 700, 3, "iso", "minmax"),
+                                              (127, 2048, 1, "iso", "mean"), (129, 300, 7, "adi", "minmax"),
+                                              (641, 1100, 2 + 1, "iso", "mean"), (1281, 12, 1, "adi", "mean"),
+                                              (2561, 700, 3, "iso", "minmax"), (4095, 5, 3, "adi", "mean")])
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_time_step_pass_by_ring_count(nx, ny, nz, eos, v0, precision):
+    """dt of Eq. cfl2 (within the two codes' bound) and every ring's v0 where a wave, and where a workgroup, takes a
+    ring: few and many rings, odd lengths, rings shorter than a wave, one zone more than a chunk, the longest."""
+    import torch
+    from gpu_common import dt_close
+    print("time-step pass", nx, ny, nz, eos, v0, precision, flush=True)
+    prob = W.random_problem("cyl", nx=nx, ny=ny, nz=nz, eos=eos, seed=nx, fargo=True, bc=("fixed", "fixed", "reflect", "reflect"))
+    prob.params.update(v0_mode=v0, precision=precision)
+    s = gpu_solver(prob)
+    st = {k: None if v is None else np.ascontiguousarray(v) for k, v in s.download().items()}
+    want = O.cfl_dt(prob.params, st)
+    assert dt_close(s.fargo_cfl_dt(), want)
+    g0, gN, _ = s.fargo_ring_split(s.state["vx"], want)
+    torch.cuda.synchronize()
+    o0, oN, _ = O.ring_split(prob.params, st["vx"], want)
+    if v0 == "minmax":
+        assert np.array_equal(g0.cpu().numpy(), o0.ravel())
+    else:  # the order of the sum differs: a few units of n u
+        assert np.allclose(g0.cpu().numpy(), o0.ravel(), rtol=4096 * 2.0 ** -53, atol=4096 * 2.0 ** -53)
+    assert np.array_equal(gN.cpu().numpy(), oN.ravel())
+
+
+@pytest.mark.parametrize("field,value", [("vx", np.inf), ("vx", -np.inf), ("vx", np.nan), ("rho", 0.0), ("cs", np.inf)])
+def test_non_finite_state_is_reported(field, value):
+    """One bad zone is reported, and an infinite velocity or sound speed leaves no time step to advance by."""
+    from paper_1602_02359_amd import fargo as F
+    prob = W.disk2d_cyl(nx=130, ny=20, noise=1e-2)
+    prob.fields[field][0, 9, 129] = value
+    s = gpu_solver(prob)
+    before = s.state["rho"].clone()
+    s.fargo_step(0.0)
+    dt = s.fargo_get_dt()
+    with pytest.raises(F.FargoError) as e:
+        s.fargo_check()
+    assert e.value.code == -4  # FARGO_ENONFINITE
+    if np.isinf(value):
+        assert dt == 0.0
+        ok = np.ones(before.shape, dtype=bool)
+        ok[0, 8:11] = False
+        assert np.array_equal(s.state["rho"].cpu().numpy()[ok], before.cpu().numpy()[ok])
