@@ -56,7 +56,6 @@ def words_per_unit(p):
         # name: (words per zone, zones per launch)
         "cfl": (2 + nvel, act),                              # rho, cs|e, velocities
         "source": ((2 + pw + nvel) + (nvel + adi), act),     # rho, cs|e, pot, v -> v'', e''
-        "source_ghosts": (2 * (nvel + adi), whole - act),    # v, e -> v'', e'' in ghost zones
         "sweep_y": ((1 + nvel + adi) + nT, y_rows),          # rho, v'', e'' -> T (momenta formed on the fly)
         "sweep_z": ((2 * nT + 1) if d3 else 0, act),         # T, v_z -> T
         "ring_x": ((nT + 1) + (2 + adi + 2 + (2 if d3 else 0)), act),  # T, v_x -> rho, v_x, e, Pi_y, Pi_z
@@ -68,9 +67,8 @@ def words_per_unit(p):
 # the source file of each kernel: a measured traffic figure is used only while
 # the file (and the shared internal header) is unchanged since the counters
 # were taken
-KERNEL_SOURCES = {"cfl": "timestep.hip", "source": "source.hip", "source_ghosts": "source.hip",
-                  "sweep_y": "transport.hip", "sweep_z": "transport.hip", "ring_x": "transport.hip",
-                  "zx_ring": "transport.hip",
+KERNEL_SOURCES = {"cfl": "timestep.hip", "source": "source.hip", "sweep_y": "transport.hip",
+                  "sweep_z": "transport.hip", "ring_x": "transport.hip", "zx_ring": "transport.hip",
                   "vel_yz": "transport.hip"}
 
 

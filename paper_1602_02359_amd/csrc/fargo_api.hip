@@ -17,8 +17,8 @@ using namespace fargo;
 
 namespace fargo {
 
-const char *kernel_names[K_COUNT] = {"set_dt", "bc_faces", "bc_ghosts", "cfl",    "dt_final", "split",
-                                     "source", "source_ghosts", "visc", "sweep_y", "sweep_z",  "ring_x",
+const char *kernel_names[K_COUNT] = {"set_dt", "bc", "cfl",    "dt_final", "split",
+                                     "source", "visc", "sweep_y", "sweep_z",  "ring_x",
                                      "vel_yz", "shift",    "sums",      "sums_final", "zx_ring",
                                      "lfc_features", "lfc_fwd_l1", "lfc_fwd_l2", "lfc_fwd_l3", "lfc_drho",
                                      "lfc_wgrad_l3", "lfc_adj_l3", "lfc_wgrad_l2", "lfc_adj_l2",
@@ -377,14 +377,17 @@ int upload_background(fargo_ctx *ctx, const double *vb) {
   return hip_ok(hipMemcpy((void *)m.bgt, tab.data(), tab.size() * 8, hipMemcpyHostToDevice));
 }
 
-// boxes 2, 3, 4, 6 and the split of Eq. 29 (dt > 0: imposed)
+// boxes 2, 3, 4 and 6 (dt > 0: imposed); returns what the source step forms its
+// dt from, nothing where dt is in the device word (always with in_word)
 template <typename F>
-void timestep_phase(fargo_ctx *c, Launch &L, const StateT<F> &S, double dt) {
+DtIn timestep_phase(fargo_ctx *c, Launch &L, const StateT<F> &S, double dt, bool in_word) {
   const Mesh &m = c->m;
   if (dt > 0.0) launch_set_dt(L, c->w, dt);
-  launch_bc(L, m, S.rho, S.e, S.vx, S.vy, S.vz);
+  launch_bc(L, m, S.rho, S.e, S.vx, S.vy, S.vz, false);
   launch_cfl(L, m, S, 1, c->v0, c->ringrate, c->ringshear, c->w.err);
-  launch_dt_final(L, m, c->w, c->ringrate, c->ringshear, dt > 0.0);
+  if (dt > 0.0) return DtIn{nullptr, nullptr, 0};
+  // (the sums' partials hold nothing during a step)
+  return launch_dt(L, m, c->w, c->ringrate, c->ringshear, c->partial, in_word);
 }
 
 } // namespace
@@ -601,8 +604,8 @@ int fargo_cfl_dt(fargo_ctx *ctx, fargo_state *state, double *dt_host, void *stre
   if (rc) return rc;
   hipStream_t s = (hipStream_t)stream;
   Launch L{s, &ctx->prof};
-  if (fp32(ctx)) timestep_phase(ctx, L, state_of<float>(ctx, state), 0.0);
-  else timestep_phase(ctx, L, state_of<double>(ctx, state), 0.0);
+  if (fp32(ctx)) timestep_phase(ctx, L, state_of<float>(ctx, state), 0.0, true);
+  else timestep_phase(ctx, L, state_of<double>(ctx, state), 0.0, true);
   if (hipGetLastError() != hipSuccess) return FARGO_EHIP;
   if (!dt_host) return FARGO_OK;
   double dt = 0.0;
@@ -625,10 +628,10 @@ template <typename F>
 void step_impl(fargo_ctx *ctx, const fargo_state *state, double dt, Launch &L) {
   const Mesh &m = ctx->m;
   StateT<F> S = state_of<F>(ctx, state);
-  timestep_phase(ctx, L, S, dt > 0.0 ? dt : 0.0);                                  // boxes 2, 3, 4, 6
+  const DtIn in = timestep_phase(ctx, L, S, dt > 0.0 ? dt : 0.0, false);           // boxes 2, 3, 4, 6
   const double *dtp = ctx->w.dt;
   F *v2[4] = {(F *)ctx->v2[0], (F *)ctx->v2[1], (F *)ctx->v2[2], (F *)ctx->v2[3]};
-  launch_source(L, m, S, dtp, v2[0], v2[1], v2[2], v2[3]);                        // boxes 7a-7c
+  launch_source(L, m, S, in, ctx->w, v2[0], v2[1], v2[2], v2[3]);                 // boxes 6, 7a-7c
   StateT<F> P = S; // post-source fields: density of the state, v'' and e''
   P.vx = v2[0];
   P.vy = v2[1];
@@ -641,7 +644,7 @@ void step_impl(fargo_ctx *ctx, const fargo_state *state, double dt, Launch &L) {
   }
   P.vz = v2[2];
   P.e = v2[3];
-  launch_bc(L, m, P.rho, P.e, P.vx, P.vy, P.vz);                                   // box 9
+  launch_bc(L, m, P.rho, P.e, P.vx, P.vy, P.vz, true);                             // box 9
   const TSetT<F> TA = tset<F>(ctx, ctx->TA), TB = tset<F>(ctx, ctx->TB);
   launch_sweep_y(L, m, P, TB, dtp);                                                // boxes 12a-c, Y
   const TSetT<F> *cur = &TB, *other = &TA;
@@ -994,7 +997,7 @@ int fused_build(fargo_batch *b) {
     F *v2[4] = {(F *)c->v2[0], (F *)c->v2[1], (F *)c->v2[2], (F *)c->v2[3]};
     H[FU_CFL].blocks(d, cfl_args<F>(m, S, c->v0, c->ringrate, c->ringshear, c->w.err, H[FU_CFL].slot(d)));
     H[FU_DT].blocks(d, dt_final_args(m, c->w, c->ringrate, c->ringshear, H[FU_DT].slot(d)));
-    H[FU_SRC].blocks(d, source_args<F>(m, S, dtp, v2[0], v2[1], v2[2], v2[3], H[FU_SRC].slot(d)));
+    H[FU_SRC].blocks(d, source_args<F>(m, S, c->w, v2[0], v2[1], v2[2], v2[3], H[FU_SRC].slot(d)));
     H[FU_SRCG].blocks(d, source_ghosts_args<F>(m, S, v2[0], v2[1], v2[2], v2[3], H[FU_SRCG].slot(d)));
     StateT<F> P = S; // post-source fields, as in the step
     P.vx = v2[0];

@@ -254,6 +254,101 @@ inline int fill_chunks(int n, int most, int least, long each, long slots, int ov
 }
 constexpr int CHIP_CUS = 256; // compute units of the chip
 
+constexpr int MAXW = 16; // waves per block, at most
+
+// A lane move of a double by DPP (two 32-bit moves); lanes with no source
+// lane, and the rows the row mask leaves out, take id.
+template <int CTRL, int RM = 0xf>
+__device__ inline double dpp_or(double x, double id) {
+  const long long xv = __double_as_longlong(x), iv = __double_as_longlong(id);
+  const int lo = __builtin_amdgcn_update_dpp((int)iv, (int)xv, CTRL, RM, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp((int)(iv >> 32), (int)(xv >> 32), CTRL, RM, 0xf, false);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+// The maximum or minimum of a wave's 64 values, in lane 63, by VALU lane
+// moves alone: shifts by 1, 2, 4 and 8 within each row of 16 lanes (lane 15
+// of a row then holds the row's result), then the broadcasts of lane 15 into
+// rows 1 and 3 and of lane 31 into rows 2 and 3.  Exact in any order, so it
+// serves min and max only.
+template <typename Op>
+__device__ inline double wave_reduce_dpp(double v, Op op, double id) {
+  constexpr int ROW_SHR = 0x110, ROW_BCAST15 = 0x142, ROW_BCAST31 = 0x143;
+  v = op(v, dpp_or<ROW_SHR + 1>(v, id));
+  v = op(v, dpp_or<ROW_SHR + 2>(v, id));
+  v = op(v, dpp_or<ROW_SHR + 4>(v, id));
+  v = op(v, dpp_or<ROW_SHR + 8>(v, id));
+  v = op(v, dpp_or<ROW_BCAST15, 0xa>(v, id));
+  v = op(v, dpp_or<ROW_BCAST31, 0xc>(v, id));
+  return v;
+}
+
+// Two reductions of a block at once (min or max: exact in any order), with
+// two barriers for both: each wave reduces by DPP lane moves, its lane 63
+// puts the result in LDS, and every lane then reads the waves' results and
+// reduces them itself; lds holds 2 * MAXW values.  With `flag`, the OR of
+// every thread's *flag rides along (a wave ballot, then MAXW more values of
+// lds) and is left in *flag of every thread.
+template <typename OpA, typename OpB>
+__device__ inline void block_reduce2(double &a, OpA opa, double ida, double &b, OpB opb, double idb, double *lds,
+                                     int *flag = nullptr) {
+  a = wave_reduce_dpp(a, opa, ida);
+  b = wave_reduce_dpp(b, opb, idb);
+  const bool fw = flag && __builtin_amdgcn_ballot_w64(*flag != 0) != 0;
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  __syncthreads();
+  if (lane == 63) {
+    lds[wid] = a;
+    lds[MAXW + wid] = b;
+    if (flag) lds[2 * MAXW + wid] = fw ? 1.0 : 0.0;
+  }
+  __syncthreads();
+  const int nw = (blockDim.x + 63) >> 6;
+  a = ida;
+  b = idb;
+  int f = 0;
+  for (int w = 0; w < nw; w++) {
+    a = opa(a, lds[w]);
+    b = opb(b, lds[MAXW + w]);
+    if (flag) f |= lds[2 * MAXW + w] != 0.0;
+  }
+  if (flag) *flag = f;
+}
+
+struct Max { __device__ double operator()(double a, double b) const { return a > b ? a : b; } };
+struct Min { __device__ double operator()(double a, double b) const { return a < b ? a : b; } };
+
+__device__ inline double lane63(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_readlane((int)b, 63), hi = __builtin_amdgcn_readlane((int)(b >> 32), 63);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
+// dt from the slots of the time-step pass.  Their extremes are exact in any
+// order; a non-positive or non-finite dt is replaced by 0, which leaves the
+// state unchanged, and sets *bad.
+struct DtSlots {
+  const double *rate, *shear;
+  int nslot;
+  double courant, shear_c0; // shear_c0 <= 0: no shear limit
+};
+// thread t of n's share
+__device__ inline void slot_extremes(const DtSlots &in, int t, int n, double &rmax, double &smax) {
+  rmax = smax = 0.0;
+#pragma unroll 4
+  for (int r = t; r < in.nslot; r += n) {
+    const double a = in.rate[r], b = in.shear[r];
+    rmax = a > rmax ? a : rmax;
+    smax = b > smax ? b : smax;
+  }
+}
+__device__ inline double dt_of_extremes(const DtSlots &in, double rmax, double smax, bool *bad) {
+#pragma clang fp contract(off)
+  double dt = in.courant * (1.0 / sqrt(rmax));
+  if (in.shear_c0 > 0.0 && smax > 0.0) dt = fmin(dt, in.shear_c0 / smax);
+  *bad = !(dt > 0.0) || !isfinite(dt);
+  return *bad ? 0.0 : dt;
+}
+
 // Order-preserving integer image of a non-negative double (for atomic min/max).
 __device__ inline unsigned long long dbits(double x) { return (unsigned long long)__double_as_longlong(x); }
 
@@ -271,7 +366,7 @@ void prof_begin(Launch &L, int kid);
 void prof_end(Launch &L, int kid);
 
 enum KernelId {
-  K_SET_DT = 0, K_BC_FACES, K_BC_GHOSTS, K_CFL, K_DT_FINAL, K_SPLIT, K_SRC, K_SRC_GHOSTS, K_VISC, K_SWEEP_Y,
+  K_SET_DT = 0, K_BC, K_CFL, K_DT_FINAL, K_SPLIT, K_SRC, K_VISC, K_SWEEP_Y,
   K_SWEEP_Z, K_RING_X, K_VEL, K_SHIFT, K_SUMS, K_SUMS_FINAL, K_ZX,
   // learned flux correction
   K_LFC_FEATURES, K_LFC_FWD1, K_LFC_FWD2, K_LFC_FWD3, K_LFC_DRHO, K_LFC_W3, K_LFC_ADJ3, K_LFC_W2, K_LFC_ADJ2,
@@ -333,9 +428,9 @@ __device__ inline uint2 many_block(const uint2 *tab) {
 }
 
 // Each launcher is defined once for R = double and R = float.
-// boundaries (boxes 2 and 9)
+// boundaries (boxes 2 and, post, 9)
 template <typename R>
-void launch_bc(Launch &L, const Mesh &m, R *rho, R *e, R *vx, R *vy, R *vz);
+void launch_bc(Launch &L, const Mesh &m, R *rho, R *e, R *vx, R *vy, R *vz, bool post);
 // boxes 3, 6 and the split of Eq. 29 (always FP64)
 void launch_set_dt(Launch &L, const DevWords &w, double dt);
 // per ring: v0 and (with_cfl) the largest squared rate 1/dt^2 of Eq. cfl2 and the maximum shear rate
@@ -345,14 +440,30 @@ constexpr int CFL_SEG = 1024;      // zones of a segment of a longer ring
 template <typename R>
 void launch_cfl(Launch &L, const Mesh &m, const StateT<R> &s, int with_cfl, double *v0, double *ringrate,
                 double *ringshear, int *err);
-// dt from the ring slots (unless imposed; the ring kernel splits each ring's
-// displacement itself)
-void launch_dt_final(Launch &L, const Mesh &m, const DevWords &w, const double *ringrate, const double *ringshear,
-                     int use_given);
+// What the source step forms dt from: the rates and shears of launch_cfl, in
+// nslot slots (0: dt is in the device word already).
+struct DtIn {
+  const double *rate, *shear;
+  int nslot;
+};
+// The ring slots of a 2D mesh where they are at most DT_SLOTS, else none, with dt in the
+// device word (`scratch`: 2 * DT_GROUPS doubles).  384 x 128 zones: the source
+// step takes 5.7 us with the 128 slots and 6.2 after a kernel of 3.8 for them;
+// 3072 x 1024: 68 us with the 1024 slots, whose loads wait among those of all
+// the tiles, and 45 after 5.
+constexpr int DT_SLOTS = 256, DT_GROUPS = 64;
+DtIn launch_dt(Launch &L, const Mesh &m, const DevWords &w, const double *ringrate, const double *ringshear,
+               double *scratch, bool in_word);
+__host__ __device__ inline DtSlots dt_slots(const Mesh &m, const DtIn &in) {
+  return DtSlots{in.rate, in.shear, in.nslot, m.courant, m.fargo ? m.shear_c0 : 0.0};
+}
 void launch_split(Launch &L, const Mesh &m, const double *v0, double dt, int32_t *N, double *xi);
-// box 7: post-source velocities and energy into vx2, vy2, vz2, e2
+// box 7: post-source velocities and energy into vx2, vy2, vz2, e2 (with the
+// ghosts that box 9 does not fill), at the dt formed from `in`, which it leaves
+// in the device word
 template <typename R>
-void launch_source(Launch &L, const Mesh &m, const StateT<R> &s, const double *dt, R *vx2, R *vy2, R *vz2, R *e2);
+void launch_source(Launch &L, const Mesh &m, const StateT<R> &s, const DtIn &in, const DevWords &w, R *vx2, R *vy2,
+                   R *vz2, R *e2);
 // box 7d: viscous stress (cylindrical 2D) from vx2, vy2 into vx3, vy3
 template <typename R>
 void launch_visc(Launch &L, const Mesh &m, const StateT<R> &s, const R *vx2, const R *vy2, R *vx3, R *vy3,
@@ -411,7 +522,7 @@ void launch_dt_final_many(Launch &L, const ManyGrid &g);
 template <typename F>
 size_t source_args_bytes();
 template <typename F>
-unsigned source_args(const Mesh &m, const StateT<F> &s, const double *dt, F *vx2, F *vy2, F *vz2, F *e2, void *dst);
+unsigned source_args(const Mesh &m, const StateT<F> &s, const DevWords &w, F *vx2, F *vy2, F *vz2, F *e2, void *dst);
 template <typename F>
 unsigned source_ghosts_args(const Mesh &m, const StateT<F> &s, F *vx2, F *vy2, F *vz2, F *e2, void *dst);
 template <typename F>

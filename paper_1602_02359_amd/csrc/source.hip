@@ -118,6 +118,44 @@ struct Zv {
   F vz, vx, vxp; // vxp: v_x on the next X face
 };
 
+// Ghost rows that carry v^n and e into v'' and e'': those of FIXED sides (box
+// 9 fills the others), and next to the Y sides those that box 7d reads first.
+// Y ghost rows of planes [ka, kb) (extended over FIXED Z sides), then the Z
+// ghost planes of rows [jt, jt + h); y0, y1: whether the Y sides belong to it.
+struct GhostRows {
+  int jn, kn, nyl, nyr, nzl, nzr, kl, nk;
+  __host__ __device__ GhostRows(const Mesh &m, bool y0, bool y1, int ka, int kb) : jn(m.jn), kn(m.kn) {
+    nyl = y0 && (m.visc || m.bc[0] == FARGO_BC_FIXED) ? NGH : 0;
+    nyr = nyl + (y1 && (m.visc || m.bc[1] == FARGO_BC_FIXED) ? NGH : 0);
+    nzl = m.d3 && ka == m.k0 && m.bc[2] == FARGO_BC_FIXED ? NGH : 0;
+    nzr = nzl + (m.d3 && kb == m.kn && m.bc[3] == FARGO_BC_FIXED ? NGH : 0);
+    kl = ka - nzl;
+    nk = kb + (nzr - nzl) - kl;
+  }
+  __host__ __device__ int rows(int jt, int h) const { return nyr * nk + nzr * h; }
+  __device__ void row(int t, int jt, int h, int &j, int &k) const {
+    if (t < nyr * nk) {
+      const int q = t % nyr;
+      j = q < nyl ? q : jn + q - nyl;
+      k = kl + t / nyr;
+    } else {
+      t -= nyr * nk;
+      const int q = t % nzr;
+      j = jt + t / nzr;
+      k = q < nzl ? q : kn + q - nzl;
+    }
+  }
+};
+template <typename F, bool D3, bool ADI>
+__device__ inline void carry_ghost(const StateT<F> &s, unsigned o, F *__restrict__ vx2, F *__restrict__ vy2,
+                                   F *__restrict__ vz2, F *__restrict__ e2) {
+  const F a = s.vx[o], b = s.vy[o], d = D3 ? s.vz[o] : F(0), e = ADI ? s.e[o] : F(0);
+  vx2[o] = a;
+  vy2[o] = b;
+  if (D3) vz2[o] = d;
+  if (ADI) e2[o] = e;
+}
+
 // A plane goes through three phases: staging into LDS (S), v' of its faces
 // (F), and the zones (Z).  The march is software-pipelined over planes: one
 // barrier interval runs Z(k), F(k+1) and S(k+2) on separate buffers, so each
@@ -125,10 +163,10 @@ struct Zv {
 // The geometry and the equation of state are template parameters: fewer
 // run-time conditions leave more scalar registers for the march.
 template <typename F, bool D3, int GEO, bool ADI>
-__device__ __forceinline__ void source_body(Mesh m, StateT<F> s, const double *__restrict__ dtp,
+__device__ __forceinline__ void source_body(Mesh m, StateT<F> s, DtIn in, DevWords dw,
                                                   F *__restrict__ vx2, F *__restrict__ vy2, F *__restrict__ vz2,
-                                                  F *__restrict__ e2, int nbx, int nby, int zlen, unsigned bid_,
-                                                  unsigned nbk_) {
+                                                  F *__restrict__ e2, int nbx, int nby, int zlen, int ghosts,
+                                                  unsigned bid_, unsigned nbk_) {
   constexpr int TY = tile_rows<F, D3, GEO, ADI>(), NB = D3 ? 2 : 1;
   constexpr bool KI = keep_inv<F, TY, NB, GEO == FARGO_SPHERICAL>();
   __shared__ Lds<F, TY, NB, GEO == FARGO_SPHERICAL, KI> L;
@@ -151,12 +189,41 @@ __device__ __forceinline__ void source_body(Mesh m, StateT<F> s, const double *_
   const unsigned grp = Lb / gsz, idx = Lb % gsz, gy = (unsigned)min(G, nby - (int)grp * G);
   const int ty = (int)(grp * (unsigned)G + idx % gy), tx = (int)(idx / gy);
   const int i0 = tx * TX, jt0 = m.j0 + ty * TY;
+  // the workgroup's active planes
+  const int k0_ = D3 ? m.k0 + (int)zc * zlen : 0, kn_ = D3 ? min(k0_ + zlen, m.kn) : 1;
   const int w = min(TX, m.nx - i0), h = min(TY, m.jn - jt0);
   const bool act = r < h && c < w;
   const int i = i0 + c, j = jt0 + r;
   constexpr bool adi = ADI;
   constexpr bool sph = GEO == FARGO_SPHERICAL, cyl = GEO == FARGO_CYLINDRICAL;
-  const F dt = vreg((F)*dtp), c2 = vreg((F)(m.cvnr * m.cvnr)), om = vreg((F)m.omega), gm1 = vreg((F)(m.gamma - 1.0));
+  // dt: the device word, or, on 2D meshes of few rings, formed here from the
+  // time-step pass's slots by the first wave of every workgroup, which saves a
+  // launch of one workgroup (DT_SLOTS); the first workgroup leaves it in the
+  // word for the kernels that follow
+  __shared__ double dt_sh;
+  const bool slots = !D3 && in.nslot > 0;
+  F dt = slots ? F(0) : vreg((F)*dw.dt);
+  auto form_dt = [&]() {
+    if (!slots || r != 0) return;
+    const DtSlots sl = dt_slots(m, in);
+    double rmax, smax;
+    slot_extremes(sl, c, WAVE, rmax, smax);
+    rmax = lane63(wave_reduce_dpp(rmax, Max(), 0.0));
+    smax = lane63(wave_reduce_dpp(smax, Max(), 0.0));
+    bool bad;
+    const double d = dt_of_extremes(sl, rmax, smax, &bad);
+    if (c == 0) {
+      dt_sh = d;
+      if (bid_ == 0) {
+        if (bad) atomicOr(dw.err, 2);
+        *dw.dt = d;
+      }
+    }
+  };
+  auto take_dt = [&]() { // after a barrier
+    if (slots) dt = vreg((F)dt_sh);
+  };
+  const F c2 = vreg((F)(m.cvnr * m.cvnr)), om = vreg((F)m.omega), gm1 = vreg((F)(m.gamma - 1.0));
   const unsigned plane = (unsigned)m.plane();
   // geometric factors of the thread's row (the products with the plane
   // factors are those of Mesh::Sx, Sy, Sz and Vinv); rows past the tile
@@ -433,6 +500,7 @@ __device__ __forceinline__ void source_body(Mesh m, StateT<F> s, const double *_
 
   if constexpr (!D3) {
     // a single plane: S, F, Z in turn
+    form_dt();
     Zv<F> z0{};
     Halo hv{};
     F e_old = F(0);
@@ -443,12 +511,13 @@ __device__ __forceinline__ void source_body(Mesh m, StateT<F> s, const double *_
     load_halo(0, hv);
     stage(0, 0, 0, z0, F(0), hv);
     __syncthreads();
+    take_dt();
     faces(0, 0, 0);
     __syncthreads();
     if (act) zones(0, 0, 0, ZPart{}, e_old);
   } else {
   // ---- 3D march over the workgroup's active planes k0 .. kn-1
-  const int k0 = m.k0 + (int)zc * zlen, kn = min(k0 + zlen, m.kn);
+  const int k0 = k0_, kn = kn_;
   // Z window of the thread's column at the top of interval kk:
   //   Z1, Z2 = records of planes kk+1, kk+2; vzk = v_z of plane kk;
   //   A[0..2] = v'_z of faces kk .. kk+2, IZ likewise; Q[0..2] = q_z of
@@ -548,47 +617,36 @@ __device__ __forceinline__ void source_body(Mesh m, StateT<F> s, const double *_
     rb = rb1;
   }
   }
+  if (!ghosts) return;
+  // the ghost rows next to the tile's, a row of its columns per wave
+  const GhostRows G_(m, ty == 0, ty == nby - 1, k0_, kn_);
+  for (int t = r; t < G_.rows(jt0, h); t += TY) {
+    int jg_, kg_;
+    G_.row(t, jt0, h, jg_, kg_);
+    if (c < w) carry_ghost<F, D3, ADI>(s, m.o32(i, jg_, kg_), vx2, vy2, vz2, e2);
+  }
 }
 template <typename F, bool D3, int GEO, bool ADI>
 __global__ __launch_bounds__((src_threads<F, D3, GEO, ADI>()), (src_waves<F, D3, GEO, ADI>())) void k_source(
-    Mesh m, StateT<F> s, const double *__restrict__ dtp, F *__restrict__ vx2, F *__restrict__ vy2,
-    F *__restrict__ vz2, F *__restrict__ e2, int nbx, int nby, int zlen) {
-  source_body<F, D3, GEO, ADI>(m, s, dtp, vx2, vy2, vz2, e2, nbx, nby, zlen, blockIdx.x, gridDim.x);
+    Mesh m, StateT<F> s, DtIn in, DevWords dw, F *__restrict__ vx2, F *__restrict__ vy2, F *__restrict__ vz2,
+    F *__restrict__ e2, int nbx, int nby, int zlen, int ghosts) {
+  source_body<F, D3, GEO, ADI>(m, s, in, dw, vx2, vy2, vz2, e2, nbx, nby, zlen, ghosts, blockIdx.x, gridDim.x);
 }
 
-// Ghost zones (Y ghost rows of every plane, and Z ghost planes of the active
-// rows) carry v^n and e into v'' and e''; one block per row.
-template <typename F>
-__device__ __forceinline__ void source_ghosts_body(Mesh m, StateT<F> s, F *__restrict__ vx2,
-                                                       F *__restrict__ vy2, F *__restrict__ vz2,
-                                                       F *__restrict__ e2, unsigned bid_, unsigned nbk_) {
-  const int b = bid_, ngy = m.nyg - m.ny;
+// The ghost rows alone, one block per row.
+template <typename F, bool D3, bool ADI>
+__device__ __forceinline__ void source_ghosts_body(const Mesh &m, const StateT<F> &s, F *__restrict__ vx2,
+                                                   F *__restrict__ vy2, F *__restrict__ vz2, F *__restrict__ e2,
+                                                   unsigned bid_) {
+  const GhostRows G(m, true, true, m.k0, m.kn);
   int j, k;
-  if (b < m.nzg * ngy) {
-    k = b / ngy;
-    const int g = b % ngy;
-    j = g < m.j0 ? g : m.jn + (g - m.j0);
-  } else {
-    const int q = b - m.nzg * ngy, ngz = m.nzg - m.nz;
-    j = m.j0 + q % m.ny;
-    const int g = q / m.ny;
-    k = g < m.k0 ? g : m.kn + (g - m.k0);
-    (void)ngz;
-  }
-  const unsigned row = m.o32(0, j, k);
-  for (int i = threadIdx.x; i < m.nx; i += blockDim.x) {
-    const unsigned o = row + (unsigned)i;
-    vx2[o] = s.vx[o];
-    vy2[o] = s.vy[o];
-    if (m.d3) vz2[o] = s.vz[o];
-    if (m.eos == FARGO_ADIABATIC) e2[o] = s.e[o];
-  }
+  G.row((int)bid_, m.j0, m.ny, j, k);
+  for (int i = threadIdx.x; i < m.nx; i += blockDim.x) carry_ghost<F, D3, ADI>(s, m.o32(i, j, k), vx2, vy2, vz2, e2);
 }
-template <typename F>
-__global__ __launch_bounds__(256) void k_source_ghosts(Mesh m, StateT<F> s, F *__restrict__ vx2,
-                                                       F *__restrict__ vy2, F *__restrict__ vz2,
-                                                       F *__restrict__ e2) {
-  source_ghosts_body<F>(m, s, vx2, vy2, vz2, e2, blockIdx.x, gridDim.x);
+template <typename F, bool D3, bool ADI>
+__global__ __launch_bounds__(256) void k_source_ghosts(Mesh m, StateT<F> s, F *__restrict__ vx2, F *__restrict__ vy2,
+                                                       F *__restrict__ vz2, F *__restrict__ e2) {
+  source_ghosts_body<F, D3, ADI>(m, s, vx2, vy2, vz2, e2, blockIdx.x);
 }
 
 // multi-mesh forms (ManyGrid)
@@ -596,7 +654,7 @@ template <typename F>
 struct SourceArgs {
   Mesh m;
   StateT<F> s;
-  const double *dt;
+  DevWords dw;
   F *vx2, *vy2, *vz2, *e2;
   int nbx, nby;
   unsigned nb;
@@ -607,16 +665,15 @@ __global__ __launch_bounds__((src_threads<F, D3, GEO, ADI>()), (src_waves<F, D3,
   const uint2 t = many_block(tab);
   if (t.x == MANY_NONE) return;
   const SourceArgs<F> a = many_args<SourceArgs<F>>(args, t.x);
-  source_body<F, D3, GEO, ADI>(a.m, a.s, a.dt, a.vx2, a.vy2, a.vz2, a.e2, a.nbx, a.nby, 1, t.y, a.nb);
+  source_body<F, D3, GEO, ADI>(a.m, a.s, DtIn{}, a.dw, a.vx2, a.vy2, a.vz2, a.e2, a.nbx, a.nby, 1, 0, t.y, a.nb);
 }
-template <typename F>
+template <typename F, bool ADI>
 __global__ __launch_bounds__(256) void k_source_ghosts_many(const void *args, const uint2 *tab) {
   const uint2 t = many_block(tab);
   if (t.x == MANY_NONE) return;
   const SourceArgs<F> a = many_args<SourceArgs<F>>(args, t.x);
-  source_ghosts_body<F>(a.m, a.s, a.vx2, a.vy2, a.vz2, a.e2, t.y, a.nb);
+  source_ghosts_body<F, false, ADI>(a.m, a.s, a.vx2, a.vy2, a.vz2, a.e2, t.y);
 }
-
 // tile rows of the source step's launch on mesh m
 template <typename F>
 int src_rows(const Mesh &m) {
@@ -638,15 +695,16 @@ long src_slots() {
 } // namespace
 
 template <typename F>
-void launch_source(Launch &L, const Mesh &m, const StateT<F> &s, const double *dt, F *vx2, F *vy2, F *vz2, F *e2) {
+void launch_source(Launch &L, const Mesh &m, const StateT<F> &s, const DtIn &in, const DevWords &w, F *vx2, F *vy2,
+                   F *vz2, F *e2) {
   const int nbx = (m.nx + TX - 1) / TX, nby = (m.ny + src_rows<F>(m) - 1) / src_rows<F>(m);
-  const unsigned ng = (unsigned)(m.nzg * (m.nyg - m.ny) + (m.d3 ? (m.nzg - m.nz) * m.ny : 0));
   prof_begin(L, K_SRC);
   auto go = [&](auto d3, auto geo, auto adi) {
     constexpr bool D3 = decltype(d3)::value, ADI = decltype(adi)::value;
     constexpr int GEO = decltype(geo)::value;
     int zlen = 1;
     unsigned nb = (unsigned)nbx * (unsigned)nby;
+    const int ng = GhostRows(m, true, true, m.k0, m.kn).rows(m.j0, m.ny);
     if constexpr (D3) {
       // the march in chunks of planes where the tiles alone leave compute units
       // idle, or a last round of workgroups nearly empty (a chunk reads five
@@ -659,7 +717,14 @@ void launch_source(Launch &L, const Mesh &m, const StateT<F> &s, const double *d
       zlen = (m.nz + nzc - 1) / nzc;
       nb *= (unsigned)((m.nz + zlen - 1) / zlen);
     }
-    k_source<F, D3, GEO, ADI><<<nb, src_threads<F, D3, GEO, ADI>(), 0, L.s>>>(m, s, dt, vx2, vy2, vz2, e2, nbx, nby, zlen);
+    // The tiles at a side take its ghost rows along where a launch costs more
+    // than the tail they add (633 x 211, 270 tiles: 1 against 4 us alone; the
+    // batch of 256 disks 40 against 9; 2048 x 768 x 96, 1536 tiles, 69 against
+    // 14 us)
+    const bool here = nb <= 2 * CHIP_CUS;
+    k_source<F, D3, GEO, ADI><<<nb, src_threads<F, D3, GEO, ADI>(), 0, L.s>>>(m, s, in, w, vx2, vy2, vz2, e2, nbx, nby,
+                                                                              zlen, here ? 1 : 0);
+    if (!here && ng > 0) k_source_ghosts<F, D3, ADI><<<(unsigned)ng, 256, 0, L.s>>>(m, s, vx2, vy2, vz2, e2);
   };
   auto by_eos = [&](auto d3, auto geo) {
     if (m.eos == FARGO_ADIABATIC) go(d3, geo, std::true_type{});
@@ -673,31 +738,28 @@ void launch_source(Launch &L, const Mesh &m, const StateT<F> &s, const double *d
   if (m.d3) by_geo(std::true_type{});
   else by_geo(std::false_type{});
   prof_end(L, K_SRC);
-  prof_begin(L, K_SRC_GHOSTS);
-  k_source_ghosts<F><<<ng, 256, 0, L.s>>>(m, s, vx2, vy2, vz2, e2);
-  prof_end(L, K_SRC_GHOSTS);
 }
 
-template void launch_source<double>(Launch &, const Mesh &, const StateT<double> &, const double *, double *, double *,
-                                    double *, double *);
-template void launch_source<float>(Launch &, const Mesh &, const StateT<float> &, const double *, float *, float *,
-                                   float *, float *);
+template void launch_source<double>(Launch &, const Mesh &, const StateT<double> &, const DtIn &, const DevWords &,
+                                    double *, double *, double *, double *);
+template void launch_source<float>(Launch &, const Mesh &, const StateT<float> &, const DtIn &, const DevWords &,
+                                   float *, float *, float *, float *);
 
 template <typename F>
 size_t source_args_bytes() { return sizeof(SourceArgs<F>); }
 
 template <typename F>
-unsigned source_args(const Mesh &m, const StateT<F> &s, const double *dt, F *vx2, F *vy2, F *vz2, F *e2, void *dst) {
+unsigned source_args(const Mesh &m, const StateT<F> &s, const DevWords &w, F *vx2, F *vy2, F *vz2, F *e2, void *dst) {
   const int nbx = (m.nx + TX - 1) / TX, nby = (m.ny + src_rows<F>(m) - 1) / src_rows<F>(m);
   const unsigned nb = (unsigned)nbx * (unsigned)nby;
-  *(SourceArgs<F> *)dst = SourceArgs<F>{m, s, dt, vx2, vy2, vz2, e2, nbx, nby, nb};
+  *(SourceArgs<F> *)dst = SourceArgs<F>{m, s, w, vx2, vy2, vz2, e2, nbx, nby, nb};
   return nb;
 }
 
 template <typename F>
 unsigned source_ghosts_args(const Mesh &m, const StateT<F> &s, F *vx2, F *vy2, F *vz2, F *e2, void *dst) {
-  const unsigned ng = (unsigned)(m.nzg * (m.nyg - m.ny) + (m.d3 ? (m.nzg - m.nz) * m.ny : 0));
-  *(SourceArgs<F> *)dst = SourceArgs<F>{m, s, nullptr, vx2, vy2, vz2, e2, 0, 0, ng};
+  const unsigned ng = (unsigned)GhostRows(m, true, true, m.k0, m.kn).rows(m.j0, m.ny);
+  *(SourceArgs<F> *)dst = SourceArgs<F>{m, s, DevWords{}, vx2, vy2, vz2, e2, 0, 0, ng};
   return ng;
 }
 
@@ -715,15 +777,14 @@ void launch_source_many(Launch &L, const Mesh &m0, const ManyGrid &g, const Many
   if (m0.geo == FARGO_SPHERICAL) by_eos(std::integral_constant<int, FARGO_SPHERICAL>{});
   else if (m0.geo == FARGO_CYLINDRICAL) by_eos(std::integral_constant<int, FARGO_CYLINDRICAL>{});
   else by_eos(std::integral_constant<int, FARGO_CARTESIAN>{});
+  if (m0.eos == FARGO_ADIABATIC) k_source_ghosts_many<F, true><<<ghosts.nblk, 256, 0, L.s>>>(ghosts.args, ghosts.tab);
+  else k_source_ghosts_many<F, false><<<ghosts.nblk, 256, 0, L.s>>>(ghosts.args, ghosts.tab);
   prof_end(L, K_SRC);
-  prof_begin(L, K_SRC_GHOSTS);
-  k_source_ghosts_many<F><<<ghosts.nblk, 256, 0, L.s>>>(ghosts.args, ghosts.tab);
-  prof_end(L, K_SRC_GHOSTS);
 }
 
 #define FARGO_SOURCE_MANY(F)                                                                                        \
   template size_t source_args_bytes<F>();                                                                          \
-  template unsigned source_args<F>(const Mesh &, const StateT<F> &, const double *, F *, F *, F *, F *, void *);   \
+  template unsigned source_args<F>(const Mesh &, const StateT<F> &, const DevWords &, F *, F *, F *, F *, void *); \
   template unsigned source_ghosts_args<F>(const Mesh &, const StateT<F> &, F *, F *, F *, F *, void *);            \
   template void launch_source_many<F>(Launch &, const Mesh &, const ManyGrid &, const ManyGrid &);
 FARGO_SOURCE_MANY(double)

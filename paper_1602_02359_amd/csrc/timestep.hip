@@ -3,9 +3,9 @@
 //
 // A wave (or, where rings are few or long, a workgroup of four) takes a ring
 // at a time: the ring's v0 and, for each of its zones, the cell time step and
-// the shear rate; the ring's extremes go to its slot.  A single workgroup then
-// reduces the slots (exact and order independent: min/max) and forms dt.  The
-// split of every ring's displacement into (N, xi) is taken by the ring kernel
+// the shear rate; the ring's extremes go to its slot.  A workgroup then reduces
+// the slots (exact and order independent: min/max) and forms dt; where they are
+// few the source step does so itself.  The split of every ring's displacement into (N, xi) is taken by the ring kernel
 // of the X transport (and by k_split for the stand-alone entry point).  The
 // time step and the split use floating-point contraction off and the operation
 // order of the written definition, so that the integer shift N is reproducible
@@ -17,8 +17,6 @@
 namespace fargo {
 
 namespace {
-
-constexpr int MAXW = 16; // waves per block, at most
 
 template <typename Op>
 __device__ inline double block_reduce(double v, Op op, double id, double *lds) {
@@ -33,66 +31,6 @@ __device__ inline double block_reduce(double v, Op op, double id, double *lds) {
   return v; // valid in every lane
 }
 
-// A lane move of a double by DPP (two 32-bit moves); lanes with no source
-// lane, and the rows the row mask leaves out, take id.
-template <int CTRL, int RM = 0xf>
-__device__ inline double dpp_or(double x, double id) {
-  const long long xv = __double_as_longlong(x), iv = __double_as_longlong(id);
-  const int lo = __builtin_amdgcn_update_dpp((int)iv, (int)xv, CTRL, RM, 0xf, false);
-  const int hi = __builtin_amdgcn_update_dpp((int)(iv >> 32), (int)(xv >> 32), CTRL, RM, 0xf, false);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
-}
-// The maximum or minimum of a wave's 64 values, in lane 63, by VALU lane
-// moves alone: shifts by 1, 2, 4 and 8 within each row of 16 lanes (lane 15
-// of a row then holds the row's result), then the broadcasts of lane 15 into
-// rows 1 and 3 and of lane 31 into rows 2 and 3.  Exact in any order, so it
-// serves min and max only.
-template <typename Op>
-__device__ inline double wave_reduce_dpp(double v, Op op, double id) {
-  constexpr int ROW_SHR = 0x110, ROW_BCAST15 = 0x142, ROW_BCAST31 = 0x143;
-  v = op(v, dpp_or<ROW_SHR + 1>(v, id));
-  v = op(v, dpp_or<ROW_SHR + 2>(v, id));
-  v = op(v, dpp_or<ROW_SHR + 4>(v, id));
-  v = op(v, dpp_or<ROW_SHR + 8>(v, id));
-  v = op(v, dpp_or<ROW_BCAST15, 0xa>(v, id));
-  v = op(v, dpp_or<ROW_BCAST31, 0xc>(v, id));
-  return v;
-}
-
-// Two reductions of a block at once (min or max: exact in any order), with
-// two barriers for both: each wave reduces by DPP lane moves, its lane 63
-// puts the result in LDS, and every lane then reads the waves' results and
-// reduces them itself; lds holds 2 * MAXW values.  With `flag`, the OR of
-// every thread's *flag rides along (a wave ballot, then MAXW more values of
-// lds) and is left in *flag of every thread.
-template <typename OpA, typename OpB>
-__device__ inline void block_reduce2(double &a, OpA opa, double ida, double &b, OpB opb, double idb, double *lds,
-                                     int *flag = nullptr) {
-  a = wave_reduce_dpp(a, opa, ida);
-  b = wave_reduce_dpp(b, opb, idb);
-  const bool fw = flag && __builtin_amdgcn_ballot_w64(*flag != 0) != 0;
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  __syncthreads();
-  if (lane == 63) {
-    lds[wid] = a;
-    lds[MAXW + wid] = b;
-    if (flag) lds[2 * MAXW + wid] = fw ? 1.0 : 0.0;
-  }
-  __syncthreads();
-  const int nw = (blockDim.x + 63) >> 6;
-  a = ida;
-  b = idb;
-  int f = 0;
-  for (int w = 0; w < nw; w++) {
-    a = opa(a, lds[w]);
-    b = opb(b, lds[MAXW + w]);
-    if (flag) f |= lds[2 * MAXW + w] != 0.0;
-  }
-  if (flag) *flag = f;
-}
-
-struct Max { __device__ double operator()(double a, double b) const { return a > b ? a : b; } };
-struct Min { __device__ double operator()(double a, double b) const { return a < b ? a : b; } };
 struct Add { __device__ double operator()(double a, double b) const { return a + b; } };
 
 __global__ void k_set_dt(DevWords w, double dt) { *w.dt = dt; }
@@ -182,12 +120,6 @@ using Pair = R __attribute__((ext_vector_type(2), aligned(sizeof(R))));
 // LDS elements a ring of n zones takes: its v_x, the first zone's again after
 // the last, and what the last pair of lanes reads beyond it.
 __host__ __device__ inline int cfl_vlen(int n) { return (n + 7) & ~1; }
-
-__device__ inline double lane63(double v) {
-  const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_readlane((int)b, 63), hi = __builtin_amdgcn_readlane((int)(b >> 32), 63);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
-}
 
 // The time-step pass.  A ring belongs to one wave (W = 1: no barrier, and the
 // waves of a compute unit hide each other's loads), or to a workgroup of four
@@ -315,7 +247,7 @@ __device__ __forceinline__ void cfl_body(Mesh m, StateT<R> s, double *__restrict
   if (CFL) {
     const double vb = m.fargo ? vb_ring : 0.0;
     // the smallest step is 1 / sqrt of the largest sum of squared rates
-    // (taken in k_dt_final)
+    // (taken in dt_of_slots)
     const CflRing C = cfl_ring(m, j, k, shear_on);
     double sring = 0.0;
     auto one = [&](double x0, double x1, R rho, R q, R y0, R y1, R z0, R z1, R nu, R xs) {
@@ -498,43 +430,40 @@ __global__ __launch_bounds__(256) void k_cfl_seg(Mesh m, StateT<R> s, int with_c
   }
 }
 
-// One workgroup: dt from the ring slots.  A non-positive or non-finite dt is flagged and replaced by 0,
-// which leaves the state unchanged.
-__device__ __forceinline__ void dt_final_body(const Mesh &m, const DevWords &w, const double *__restrict__ ringrate,
-                                              const double *__restrict__ ringshear) {
-#pragma clang fp contract(off)
+// dt from the slots into the device word: one workgroup, every wave a share of
+// the slots.
+__device__ __forceinline__ void dt_final_body(const DtSlots &in, const DevWords &w) {
   __shared__ double red[2 * MAXW];
-  constexpr int U = 8; // loads in flight per thread
-  double rmax = 0.0, smax = 0.0;
-  const int nslot = m.nring * m.cseg;
-  for (int r0 = threadIdx.x; r0 < nslot; r0 += U * blockDim.x) {
-    double a[U], b[U];
-#pragma unroll
-    for (int u = 0; u < U; u++) {
-      const int r = r0 + u * (int)blockDim.x;
-      a[u] = r < nslot ? ringrate[r] : 0.0;
-      b[u] = r < nslot ? ringshear[r] : 0.0;
-    }
-#pragma unroll
-    for (int u = 0; u < U; u++) {
-      rmax = a[u] > rmax ? a[u] : rmax;
-      smax = b[u] > smax ? b[u] : smax;
-    }
-  }
+  double rmax, smax;
+  slot_extremes(in, threadIdx.x, blockDim.x, rmax, smax);
   block_reduce2(rmax, Max(), 0.0, smax, Max(), 0.0, red);
+  bool bad;
+  const double dt = dt_of_extremes(in, rmax, smax, &bad);
   if (threadIdx.x == 0) {
-    double dt = m.courant * (1.0 / sqrt(rmax));
-    if (m.fargo && m.shear_c0 > 0.0 && smax > 0.0) dt = fmin(dt, m.shear_c0 / smax);
-    if (!(dt > 0.0) || !isfinite(dt)) {
-      atomicOr(w.err, 2);
-      dt = 0.0;
-    }
+    if (bad) atomicOr(w.err, 2);
     *w.dt = dt;
   }
 }
-__global__ __launch_bounds__(1024) void k_dt_final(Mesh m, DevWords w, const double *__restrict__ ringrate,
-                                                   const double *__restrict__ ringshear) {
-  dt_final_body(m, w, ringrate, ringshear);
+__global__ __launch_bounds__(1024) void k_dt_final(DtSlots in, DevWords w) { dt_final_body(in, w); }
+
+// The slots' extremes by groups of consecutive slots, one block per group (a
+// workgroup alone reads at the rate of its compute unit, 40 GB/s).
+__global__ __launch_bounds__(256) void k_dt_groups(const double *__restrict__ rate, const double *__restrict__ shear,
+                                                   int nslot, int per, double *__restrict__ out) {
+  __shared__ double red[2 * MAXW];
+  double rmax = 0.0, smax = 0.0;
+  const int r1 = min(nslot, ((int)blockIdx.x + 1) * per);
+#pragma unroll 4
+  for (int r = blockIdx.x * per + threadIdx.x; r < r1; r += 256) {
+    const double a = rate[r], b = shear[r];
+    rmax = a > rmax ? a : rmax;
+    smax = b > smax ? b : smax;
+  }
+  block_reduce2(rmax, Max(), 0.0, smax, Max(), 0.0, red);
+  if (threadIdx.x == 0) {
+    out[blockIdx.x] = rmax;
+    out[DT_GROUPS + blockIdx.x] = smax;
+  }
 }
 
 // multi-mesh forms (ManyGrid)
@@ -555,15 +484,14 @@ __global__ __launch_bounds__(CFL_BS1) void k_cfl_ring_many(const void *args, con
   cfl_body<1, true, false, ADI, R>(a.m, a.s, a.v0, a.ringrate, a.ringshear, a.err, t.y, a.nb);
 }
 struct DtArgs {
-  Mesh m;
+  DtSlots in;
   DevWords w;
-  const double *ringrate, *ringshear;
 };
-__global__ __launch_bounds__(1024) void k_dt_final_many(const void *args, const uint2 *tab) {
+__global__ __launch_bounds__(256) void k_dt_final_many(const void *args, const uint2 *tab) {
   const uint2 t = many_block(tab);
   if (t.x == MANY_NONE) return;
   const DtArgs a = many_args<DtArgs>(args, t.x);
-  dt_final_body(a.m, a.w, a.ringrate, a.ringshear);
+  dt_final_body(a.in, a.w);
 }
 
 // The split of Eq. 29, one thread per ring, with dt given by value or, if
@@ -626,12 +554,21 @@ template void launch_cfl<double>(Launch &, const Mesh &, const StateT<double> &,
 template void launch_cfl<float>(Launch &, const Mesh &, const StateT<float> &, int, double *, double *, double *,
                                 int *);
 
-void launch_dt_final(Launch &L, const Mesh &m, const DevWords &w, const double *ringrate, const double *ringshear,
-                     int use_given) {
-  if (use_given) return;
+DtIn launch_dt(Launch &L, const Mesh &m, const DevWords &w, const double *ringrate, const double *ringshear,
+               double *scratch, bool in_word) {
+  DtIn in{ringrate, ringshear, m.nring * m.cseg};
+  if (in.nslot <= DT_SLOTS && !m.d3 && !in_word) return in;
   prof_begin(L, K_DT_FINAL);
-  k_dt_final<<<1, 1024, 0, L.s>>>(m, w, ringrate, ringshear);
+  // by groups first where one workgroup would read for longer than a second
+  // launch takes (17280 slots: 8.7 us alone, 9.4 by groups; 73728: 30 and 9.4)
+  if (in.nslot > 20000) {
+    const int per = (in.nslot + DT_GROUPS - 1) / DT_GROUPS;
+    k_dt_groups<<<DT_GROUPS, 256, 0, L.s>>>(ringrate, ringshear, in.nslot, per, scratch);
+    in = DtIn{scratch, scratch + DT_GROUPS, DT_GROUPS};
+  }
+  k_dt_final<<<1, in.nslot > 64 ? 1024 : 64, 0, L.s>>>(dt_slots(m, in), w);
   prof_end(L, K_DT_FINAL);
+  return DtIn{nullptr, nullptr, 0};
 }
 
 void launch_split(Launch &L, const Mesh &m, const double *v0, double dt, int32_t *N, double *xi) {
@@ -663,13 +600,13 @@ void launch_cfl_many(Launch &L, const Mesh &m0, const ManyGrid &g, int nxmax) {
 size_t dt_final_args_bytes() { return sizeof(DtArgs); }
 
 unsigned dt_final_args(const Mesh &m, const DevWords &w, const double *ringrate, const double *ringshear, void *dst) {
-  *(DtArgs *)dst = DtArgs{m, w, ringrate, ringshear};
+  *(DtArgs *)dst = DtArgs{dt_slots(m, DtIn{ringrate, ringshear, m.nring}), w};
   return 1;
 }
 
 void launch_dt_final_many(Launch &L, const ManyGrid &g) {
   prof_begin(L, K_DT_FINAL);
-  k_dt_final_many<<<g.nblk, 1024, 0, L.s>>>(g.args, g.tab);
+  k_dt_final_many<<<g.nblk, 256, 0, L.s>>>(g.args, g.tab);
   prof_end(L, K_DT_FINAL);
 }
 

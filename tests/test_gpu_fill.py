@@ -12,12 +12,19 @@ from gpu_common import errors, gpu_solver
 
 pytestmark = pytest.mark.gpu
 
-SIDES = {"periodic": ("periodic",) * 4, "reflect": ("reflect",) * 4}
+SIDES = {"periodic": ("periodic",) * 4, "reflect": ("reflect",) * 4, "fixed": ("fixed",) * 4,
+         "mixed": ("reflect", "outflow", "outflow", "reflect"), "outflow": ("outflow",) * 4,
+         "half": ("fixed", "outflow", "reflect", "fixed")}
 MESHES = [("cart", 64, 3, 3, "adi", "periodic"), ("cart", 65, 16, 4, "iso", "periodic"),
           ("cart", 40, 13, 17, "adi", "reflect"), ("cyl", 130, 12, 9, "iso", "reflect"),
           ("cyl", 193, 33, 33, "iso", "reflect"), ("sph", 70, 24, 13, "adi", "reflect"),
           ("cyl", 300, 129, 1, "iso", "reflect"), ("cyl", 64, 1000, 1, "adi", "reflect"),
-          ("cyl", 20, 400, 5, "adi", "reflect")]
+          ("cyl", 20, 400, 5, "adi", "reflect"),
+          # three zones between the sides: every ghost mirrors a zone next to the other side
+          ("cyl", 33, 3, 3, "adi", "mixed"), ("cart", 64, 3, 3, "adi", "outflow"), ("sph", 40, 3, 3, "iso", "reflect"),
+          # caller-fixed sides in both directions, tiles that hold one side, both, or none
+          ("cart", 70, 5, 4, "iso", "fixed"), ("cyl", 130, 40, 9, "adi", "half"), ("cart", 70, 33, 1, "adi", "half"),
+          ("cyl", 64, 200, 1, "iso", "fixed")]
 DISKS = [("sph", 70, 24, 13), ("sph", 136, 9, 4), ("sph", 260, 40, 37), ("cyl", 150, 23, 17), ("cyl", 64, 5, 3),
          ("2d", 300, 129, 1), ("2d", 64, 1000, 1)]
 
