@@ -212,6 +212,29 @@ struct TSetT {
   int nq;
 };
 
+// Neighbour lanes through DPP whole-wave shifts by one lane (wave_shr:1,
+// wave_shl:1): a VALU move, with no trip through the LDS crossbar.  The lane
+// at the end of the wave, which has no source lane, reads zero (bound_ctrl);
+// it is a halo lane, whose outputs are never stored.  Taking no old value
+// lets the move write its destination directly, without a copy first.
+template <int CTRL>
+__device__ inline int dpp_lane(int x) { return __builtin_amdgcn_mov_dpp(x, CTRL, 0xf, 0xf, true); }
+template <int CTRL, typename F>
+__device__ inline F dpp_move(F x) {
+  if constexpr (sizeof(F) == 8) {
+    const long long v = __double_as_longlong(x);
+    const int lo = dpp_lane<CTRL>((int)v), hi = dpp_lane<CTRL>((int)(v >> 32));
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+  } else {
+    return __int_as_float(dpp_lane<CTRL>(__float_as_int(x)));
+  }
+}
+constexpr int DPP_WAVE_SHL1 = 0x130, DPP_WAVE_SHR1 = 0x138;
+template <typename F>
+__device__ inline F from_prev_lane(F x) { return dpp_move<DPP_WAVE_SHR1>(x); }
+template <typename F>
+__device__ inline F from_next_lane(F x) { return dpp_move<DPP_WAVE_SHL1>(x); }
+
 // Workgroups are dispatched round-robin over the 8 XCDs of the chip, each with
 // its own L2.  This maps the hardware block id to a logical one so that every
 // XCD works on a contiguous range of logical blocks (a bijection of [0, G)).
@@ -253,6 +276,13 @@ inline int fill_chunks(int n, int most, int least, long each, long slots, int ov
   return best;
 }
 constexpr int CHIP_CUS = 256; // compute units of the chip
+// Workgroups of bs threads of a kernel that the chip holds at once.
+template <typename K>
+long block_slots(K kernel, int bs) {
+  int per_cu = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, bs, 0) != hipSuccess || per_cu < 1) per_cu = 2;
+  return (long)per_cu * CHIP_CUS;
+}
 
 constexpr int MAXW = 16; // waves per block, at most
 
@@ -467,7 +497,7 @@ void launch_source(Launch &L, const Mesh &m, const StateT<R> &s, const DtIn &in,
 // box 7d: viscous stress (cylindrical 2D) from vx2, vy2 into vx3, vy3
 template <typename R>
 void launch_visc(Launch &L, const Mesh &m, const StateT<R> &s, const R *vx2, const R *vy2, R *vx3, R *vy3,
-                 const double *dt, R *const tau[3]);
+                 const double *dt);
 // box 12
 template <typename R>
 void launch_sweep_y(Launch &L, const Mesh &m, const StateT<R> &s, const TSetT<R> &out, const double *dt);
@@ -531,9 +561,9 @@ template <typename F>
 size_t visc_args_bytes();
 template <typename F>
 unsigned visc_args(const Mesh &m, const StateT<F> &s, const F *vx2, const F *vy2, F *vx3, F *vy3, const double *dt,
-                   F *const tau[3], void *dst, unsigned *nb1);
+                   void *dst);
 template <typename F>
-void launch_visc_many(Launch &L, const ManyGrid &g1, const ManyGrid &g);
+void launch_visc_many(Launch &L, const ManyGrid &g);
 template <typename F>
 size_t sweep_y_args_bytes();
 template <typename F>

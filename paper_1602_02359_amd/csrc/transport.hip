@@ -374,29 +374,6 @@ struct RingShape {
   static constexpr int M = 2, HLL = 3, HRL = 3; // halo lanes on each side
 };
 
-// Neighbour lanes through DPP whole-wave shifts by one lane (wave_shr:1,
-// wave_shl:1): a VALU move, with no trip through the LDS crossbar.  The lane
-// at the end of the wave, which has no source lane, reads zero (bound_ctrl);
-// it is a halo lane, whose outputs are never stored.  Taking no old value
-// lets the move write its destination directly, without a copy first.
-template <int CTRL>
-__device__ inline int dpp_lane(int x) { return __builtin_amdgcn_mov_dpp(x, CTRL, 0xf, 0xf, true); }
-template <int CTRL, typename F>
-__device__ inline F dpp_move(F x) {
-  if constexpr (sizeof(F) == 8) {
-    const long long v = __double_as_longlong(x);
-    const int lo = dpp_lane<CTRL>((int)v), hi = dpp_lane<CTRL>((int)(v >> 32));
-    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
-  } else {
-    return __int_as_float(dpp_lane<CTRL>(__float_as_int(x)));
-  }
-}
-constexpr int DPP_WAVE_SHL1 = 0x130, DPP_WAVE_SHR1 = 0x138;
-template <typename F>
-__device__ inline F from_prev_lane(F x) { return dpp_move<DPP_WAVE_SHR1>(x); }
-template <typename F>
-__device__ inline F from_next_lane(F x) { return dpp_move<DPP_WAVE_SHL1>(x); }
-
 // a[] of the lane's M zones and its two neighbours on each side
 template <typename F, int M>
 struct Span {
@@ -1013,14 +990,6 @@ constexpr int SWEEP_OVER = 2; // zones a chunk costs beside its own (1, 2 and 4 
 inline Mesh filled(const Mesh &m, int n, long each, long slots, int &nchunk) {
   nchunk = fill_chunks(n, m.chunk, 1, each, slots, SWEEP_OVER);
   return chunked(m, n, nchunk);
-}
-
-// Workgroups of bs threads of a kernel that the chip holds at once.
-template <typename K>
-long block_slots(K kernel, int bs) {
-  int per_cu = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, bs, 0) != hipSuccess || per_cu < 1) per_cu = 2;
-  return (long)per_cu * CHIP_CUS;
 }
 
 template <typename F, int NQ, bool D3, bool ADI>

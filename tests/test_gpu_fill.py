@@ -56,6 +56,20 @@ def test_chunked_step_fp32(geo, nx, ny, nz):
     assert _step(prob) <= 2e-6
 
 
+@pytest.mark.parametrize("nx,ny", [(2, 9), (61, 33), (62, 64), (63, 31), (125, 5), (187, 100), (640, 40)])
+@pytest.mark.parametrize("side", ["fixed", "reflect", "outflow"])
+def test_viscous_pass_at_segment_edges(nx, ny, side):
+    """Box 7d where a ring is shorter than a wave's 62 columns, fills them exactly and spills over by one, with chunks of
+    one row and of many, against the oracle."""
+    print("viscous pass", nx, ny, side, flush=True)
+    prob = W.disk2d_visc(nx=nx, ny=ny, alpha=0.05, noise=0.2, seed=nx + ny)
+    prob.params["bc"] = SIDES[side]
+    rng = np.random.default_rng(nx)
+    for k in ("vx", "vy"):
+        prob.fields[k] += 0.02 * rng.standard_normal(prob.shape)
+    assert _step(prob) <= 1e-12
+
+
 @pytest.mark.parametrize("nx,ny,nz,eos,v0", [(1, 2100, 1, "adi", "minmax"), (2, 700, 3, "iso", "minmax"),
                                               (127, 2048, 1, "iso", "mean"), (129, 300, 7, "adi", "minmax"),
                                               (641, 1100, 2 + 1, "iso", "mean"), (1281, 12, 1, "adi", "mean"),
