@@ -158,7 +158,7 @@ size_t elem_bytes(const fargo_params *p) { return p->precision == FARGO_FP32_BUL
 // host tables, in the order of GeoTables
 struct HostGeo {
   std::vector<double> ymin, ymed, zmin, zmed, sinz, Ly, hy, sxj, syj, szj, invVj, sxk, syk, szk, dxlen;
-  std::vector<double> inv_dxlen, inv_hy, inv_Ly, inv_ymin, inv_ymed, cotz, inv_dzmed, inv_dz;
+  std::vector<double> inv_dxlen, inv_hy, inv_Ly, inv_ymin, inv_ymed, cotz, inv_dzmed, inv_dz, inv_syk;
 };
 
 #pragma clang fp contract(off)
@@ -242,6 +242,7 @@ void make_geo(const fargo_params *p, HostGeo &G) {
   G.inv_ymin.resize(nyg + 1);
   for (int j = 0; j <= nyg; j++) G.inv_ymin[j] = G.ymin[j] != 0.0 ? 1.0 / G.ymin[j] : 0.0;
   G.inv_ymed = inv(G.ymed);
+  G.inv_syk = inv(G.syk);
   G.cotz.resize(nzg + 1);
   for (int k = 0; k <= nzg; k++)
     G.cotz[k] = p->geometry == FARGO_SPHERICAL ? std::cos(G.zmin[k]) / std::sin(G.zmin[k]) : 0.0;
@@ -477,7 +478,7 @@ int fargo_init(const fargo_params *params, void *workspace, size_t ws_bytes, far
   const std::vector<double> *rows[GJ_N] = {&G.ymin, &G.ymed,  &G.Ly,     &G.hy,     &G.sxj,      &G.syj,
                                           &G.szj,  &G.invVj, &G.inv_hy, &G.inv_Ly, &G.inv_ymin, &G.inv_ymed};
   const std::vector<double> *planes[GK_N] = {&G.zmin, &G.zmed, &G.sinz, &G.sxk,      &G.syk,
-                                            &G.szk,  &G.cotz, &G.inv_dzmed, &G.inv_dz};
+                                            &G.szk,  &G.cotz, &G.inv_dzmed, &G.inv_dz, &G.inv_syk};
   for (const std::vector<double> *v : rows) {
     buf.insert(buf.end(), v->begin(), v->end());
     buf.resize(buf.size() + (nyg + 1) - v->size(), 0.0);

@@ -55,6 +55,7 @@ enum GeoPlane {
   GK_COTZ,      // cot(zmin) in spherical geometry (nzg + 1 entries)
   GK_INV_DZMED, // 1 / (zmed[k] - zmed[k-1])
   GK_INV_DZ,    // 1 / (zmin[k+1] - zmin[k])
+  GK_INV_SYK,   // 1 / GK_SYK
   GK_N
 };
 struct GeoTables {
@@ -87,6 +88,7 @@ struct GeoTables {
   __device__ inline double cotz(int k) const { return tk(GK_COTZ, k); }
   __device__ inline double inv_dzmed(int k) const { return tk(GK_INV_DZMED, k); }
   __device__ inline double inv_dz(int k) const { return tk(GK_INV_DZ, k); }
+  __device__ inline double inv_syk(int k) const { return tk(GK_INV_SYK, k); }
   // azimuthal zone length and its reciprocal at index k * nyg + j
   __device__ inline double dxlen(size_t i) const { return t2(0, i); }
   __device__ inline double inv_dxlen(size_t i) const { return t2(1, i); }
@@ -155,7 +157,7 @@ struct Mesh {
   __device__ inline double Sx(int j, int k) const { return g.sxj(j) * g.sxk(k); }
   __device__ inline double Sy(int j, int k) const { return g.syj(j) * g.syk(k); }
   __device__ inline double Sz(int j, int k) const { return g.szj(j) * g.szk(k); }
-  __device__ inline double Vinv(int j, int k) const { return g.invVj(j) / g.syk(k); }
+  __device__ inline double Vinv(int j, int k) const { return g.invVj(j) * g.inv_syk(k); }
   __device__ inline double Vol(int j, int k) const { return g.syk(k) / g.invVj(j); }
   __device__ inline double DX(int j, int k) const { return g.dxlen((size_t)k * nyg + j); }
   __device__ inline double Lz(int j, int k) const {

@@ -36,20 +36,22 @@ namespace fargo {
 namespace {
 
 // Reciprocal and quotient for the ring kernel, which is bound by its vector
-// instruction count: the hardware reciprocal estimate refined by
-// Newton-Raphson steps r <- r + r (1 - d r), two in FP64 and one in FP32,
-// which leaves r within about one unit in the last place of 1/d (the correctly
-// rounded division costs about twice the instructions).  The rounding of such
-// a quotient varies from zone to zone like that of a division.  d must be a
-// normal number; a zero or denormal d, which the kernel only meets in
-// discarded selects and halo lanes, gives an infinite or meaningless value and
-// no trap.
+// instruction count: the hardware reciprocal estimate r refined by the series
+// of 1 / (d r) = 1 + e + e^2 + ..., e = 1 - d r.  In FP64 (e some 2^-23) two
+// terms, three fused operations; in FP32 one, two operations.  That leaves the
+// result within about one unit in the last place (the correctly rounded
+// division costs more than twice the instructions), rounded differently from
+// zone to zone like a division.  d must be a normal number; a zero or denormal
+// d, which the kernel only meets in discarded selects and halo lanes, gives an
+// infinite or meaningless value and no trap.
 __device__ inline double ring_rcp(double d) {
-  double r = __builtin_amdgcn_rcp(d);
-  r = fma(r, fma(-d, r, 1.0), r);
-  return fma(r, fma(-d, r, 1.0), r);
+  const double r = __builtin_amdgcn_rcp(d), e = fma(-d, r, 1.0);
+  return fma(r, fma(e, e, e), r);
 }
-__device__ inline double ring_div(double n, double d) { return n * ring_rcp(d); }
+__device__ inline double ring_div(double n, double d) {
+  const double r = __builtin_amdgcn_rcp(d), e = fma(-d, r, 1.0), q = n * r;
+  return fma(q, fma(e, e, e), q);
+}
 __device__ inline float ring_rcp(float d) {
   const float r = __builtin_amdgcn_rcpf(d);
   return fmaf(r, fmaf(-d, r, 1.0f), r);
@@ -343,18 +345,6 @@ __global__ __launch_bounds__(256) void k_sweep_z(Mesh m, const F *__restrict__ v
   column_sweep<F, NQ, true, sizeof(F) == 4, Raw>(a0, a1, dt, raw, derive, Tof, geo, st, dl);
 }
 
-// Monotonised central slope of the PPA edge values (Eq. 34): zero at an
-// extremum, else the central difference limited by twice each one-sided one.
-// min(2 a, 2 b, |d| / 2) is formed as 2 min(a, b, |d| / 4) (exact: scaling by
-// powers of two) and takes the sign of d (d = 0 only at an extremum).
-template <typename F>
-__device__ inline F mc_slope(F qm, F q0, F qp) {
-  const F d = qp - qm;
-  if ((qp - q0) * (q0 - qm) <= F(0)) return F(0);
-  const F mag = F(2) * fmin(fmin(fabs(q0 - qm), fabs(qp - q0)), F(0.25) * fabs(d));
-  return copysign(mag, d);
-}
-
 // ------------------------------------------------------------------------
 // X: every wave owns a segment of one ring.  Lane l holds the M consecutive
 // zones z0 + M l .. z0 + M l + M - 1 of a window of 64 M zones that starts
@@ -366,27 +356,25 @@ __device__ inline F mc_slope(F qm, F q0, F qp) {
 // Outputs are written out of place (shifted by N on store), so that the
 // segments of a ring can run in any order.
 // ------------------------------------------------------------------------
-// Two zones per lane in both precisions (in FP32 four zones per lane, with
-// fewer halo lanes, measured no faster: the larger register window lowers the
-// number of waves that hide the loads).
+// The ring kernel takes two zones per lane in FP64 and four in FP32, where they
+// fit in registers (five waves per SIMD) and save half the lane moves a zone and
+// a third of the halo: the batch of 256 disks 834 to 760 us.  The fused Z/X pass
+// takes two.
 template <typename F>
-struct RingShape {
-  static constexpr int M = 2, HLL = 3, HRL = 3; // halo lanes on each side
-};
+constexpr int ring_m() { return sizeof(F) == 8 ? 2 : 4; }
+constexpr int halo_lanes(int M) { return (6 + M - 1) / M; } // on each side
 
-// a[] of the lane's M zones and its two neighbours on each side
+// The differences of neighbouring zones: d[x] between zones x - 1 and x of the
+// lane, x = 0 .. M, and the value below the first zone.
 template <typename F, int M>
-struct Span {
-  F a[M];
-  F p2, p1, n1, n2;
-  __device__ inline void edges() {
-    p2 = from_prev_lane(a[M - 2]);
-    p1 = from_prev_lane(a[M - 1]);
-    n1 = from_next_lane(a[0]);
-    n2 = from_next_lane(a[1]);
-  }
-  __device__ inline F operator()(int x) const { // x in [-2, M + 1], static after unrolling
-    return x == -2 ? p2 : x == -1 ? p1 : x == M ? n1 : x == M + 1 ? n2 : a[x];
+struct Diffs {
+  F below, d[M + 1];
+  __device__ inline explicit Diffs(const F (&a)[M]) {
+    below = from_prev_lane(a[M - 1]);
+    d[0] = a[0] - below;
+#pragma unroll
+    for (int x = 1; x < M; x++) d[x] = a[x] - a[x - 1];
+    d[M] = from_next_lane(a[0]) - a[M - 1];
   }
 };
 
@@ -403,42 +391,15 @@ __device__ inline void prev_of(const F (&a)[M], F (&out)[M]) { // value of zone 
   for (int m = 0; m < M; m++) out[m] = m > 0 ? a[m - 1] : p1;
 }
 
-// PPA on one zone (Eqs. 34-36): limit the parabola through the edge values
-// l, r (flat at an extremum, steepened away from an overshoot), then the
-// interface value supplied by the zone, the mean of the parabola over the
-// fraction |xi| next to its right edge (xi >= 0) or left edge (xi < 0).
-// The fraction enters through the ring constants X: x = |xi|, x (1 - x) and
-// the sign of xi, which are the same for every zone of the ring.
-template <typename F>
-struct PpaX {
-  F x, x1x;
-  bool right; // xi >= 0
-};
-// (At an extremum both edges are q0 and the mean is q0 exactly; that case is
-// taken at the end, so the steepening selects do not test it.)
-template <typename F>
-__device__ inline F ppa_eval(F qm, F q0, F qp, F l, F r, const PpaX<F> &X) {
-  const F sixth = F(1) / F(6);
-  const F D = r - l, C = q0 - F(0.5) * (l + r);
-  const F DC = D * C, DD6 = D * D * sixth;
-  const bool flat = (qp - q0) * (q0 - qm) <= F(0);
-  const bool stl = DC > DD6, str = !stl && -DD6 > DC;
-  const F ln = stl ? F(3) * q0 - F(2) * r : l;
-  const F rn = str ? F(3) * q0 - F(2) * l : r;
-  const F ed = X.right ? rn : ln;
-  const F v = ed + X.x * (q0 - ed) + X.x1x * (F(2) * q0 - rn - ln);
-  return flat ? q0 : v;
-}
-
 // Interface values on the lane's zones; each zone's slope and each face's
 // edge value is computed once and handed to the neighbouring zone (in a
 // register, or by a DPP lane move).
 //   vlx_faces: van Leer on a uniform zone width, slopes in units of the zone
 //   (harmonic mean of the two one-sided differences, zero unless they have
 //   the same sign), and the half-step value at each zone's lower face
-//   upwinded on w, with cw = w dt / dX (Eq. 15).
-//   The upwind factors depend on the face velocity only and are formed once
-//   for all quantities: (1 - cw)/2 and (1 + cw)/2 (the halving is exact).
+//   upwinded on w, with cw = w dt / dX (Eq. 15).  The factors 2 of the
+//   harmonic mean and 1/2 of the half step cancel (both exact): a holds half a
+//   slope, and 1 - cw and 1 + cw, formed once for all quantities, multiply it.
 template <typename F, int M>
 struct Upwind {
   bool pos[M]; // w >= 0
@@ -448,37 +409,70 @@ struct Upwind {
     for (int q = 0; q < M; q++) {
       const F cw = w[q] * cdt;
       pos[q] = w[q] >= F(0);
-      cl[q] = (F(1) - cw) * F(0.5);
-      cr[q] = (F(1) + cw) * F(0.5);
+      cl[q] = F(1) - cw;
+      cr[q] = F(1) + cw;
     }
   }
 };
 template <typename F, int M>
-__device__ inline void vlx_faces(const Span<F, M> &Q, const Upwind<F, M> &U, F (&out)[M]) {
+__device__ inline void vlx_faces(const F (&Q)[M], const Upwind<F, M> &U, F (&out)[M]) {
+  const Diffs<F, M> D(Q);
   F a[M], ap[M];
 #pragma unroll
   for (int q = 0; q < M; q++) {
-    const F dm = Q(q) - Q(q - 1), dp = Q(q + 1) - Q(q), pr = dm * dp;
-    a[q] = pr > F(0) ? ring_div(F(2) * pr, dm + dp) : F(0);
+    const F pr = D.d[q] * D.d[q + 1];
+    a[q] = pr > F(0) ? ring_div(pr, D.d[q] + D.d[q + 1]) : F(0);
   }
   prev_of(a, ap);
 #pragma unroll
-  for (int q = 0; q < M; q++) out[q] = U.pos[q] ? Q(q - 1) + ap[q] * U.cl[q] : Q(q) - a[q] * U.cr[q];
+  for (int q = 0; q < M; q++)
+    out[q] = U.pos[q] ? (q > 0 ? Q[q > 0 ? q - 1 : 0] : D.below) + ap[q] * U.cl[q] : Q[q] - a[q] * U.cr[q];
 }
-//   ppa_values: monotonised central slopes, the edge value of each face
-//   (Eq. 34) and the interface value supplied by each zone.
-template <typename F, int M>
-__device__ inline void ppa_values(const Span<F, M> &Q, const PpaX<F> &X, F (&out)[M]) {
-  const F sixth = F(1) / F(6);
-  F d[M], dp[M], l[M], r[M];
+//   ppa_values (Eqs. 34-36): the interface value that each zone supplies, the
+//   mean of its limited parabola over the fraction x = |xi| next to its right
+//   edge (RIGHT: xi >= 0) or left edge.  The parabola is held as its edges'
+//   distances from the mean, a = q^R - q and b = q - q^L.  With the monotonised
+//   slope limited by twice each one-sided difference an edge value lies between
+//   its two zones, so away from an extremum a and b have the sign of the slope,
+//   and the tests of Eq. 36 (D C > D^2 / 6, -D^2 / 6 > D C with D = a + b, C =
+//   (b - a) / 2) read |b| > 2 |a|, |a| > 2 |b|; the steepened edges are b = 2 a
+//   and a = 2 b.  The mean over the fraction is then q + (1 - x)(a + x (b - a))
+//   on the right, q - (1 - x)(b + x (a - b)) on the left, and q at an extremum.
+//   (d is half the slope; scalings by powers of two are exact.)  About two
+//   thirds of the operations of the edge values written out.
+template <typename F>
+struct PpaX {
+  F x, omx; // |xi| and 1 - |xi|
+  bool right; // xi >= 0
+};
+template <bool RIGHT, typename F, int M>
+__device__ inline void ppa_values(const F (&Q)[M], const PpaX<F> &X, F (&out)[M]) {
+  const F third = F(1) / F(3);
+  const Diffs<F, M> D(Q);
+  F d[M], dp[M], a[M], b[M], low[M];
+  bool flat[M];
 #pragma unroll
-  for (int q = 0; q < M; q++) d[q] = mc_slope(Q(q - 1), Q(q), Q(q + 1));
+  for (int q = 0; q < M; q++) {
+    const F l = D.d[q], r = D.d[q + 1];
+    flat[q] = l * r <= F(0);
+    const F mag = fmin(fmin(fabs(l), fabs(r)), F(0.25) * fabs(l + r));
+    d[q] = flat[q] ? F(0) : copysign(mag, r);
+  }
   prev_of(d, dp);
 #pragma unroll
-  for (int q = 0; q < M; q++) l[q] = Q(q - 1) + F(0.5) * (Q(q) - Q(q - 1)) - (d[q] - dp[q]) * sixth;
-  next_of(l, r);
+  for (int q = 0; q < M; q++) { // the zone's lower face: q - q^L, and q^R - q of the zone below
+    const F t = d[q] - dp[q], h = F(0.5) * D.d[q];
+    b[q] = h + third * t;
+    low[q] = h - third * t;
+  }
+  next_of(low, a);
 #pragma unroll
-  for (int q = 0; q < M; q++) out[q] = ppa_eval(Q(q - 1), Q(q), Q(q + 1), l[q], r[q], X);
+  for (int q = 0; q < M; q++) {
+    const F a2 = a[q] + a[q], b2 = b[q] + b[q];
+    const F bl = fabs(b[q]) > fabs(a2) ? a2 : b[q], al = fabs(a[q]) > fabs(b2) ? b2 : a[q];
+    const F v = RIGHT ? Q[q] + X.omx * (al + X.x * (bl - al)) : Q[q] - X.omx * (bl + X.x * (al - bl));
+    out[q] = flat[q] ? Q[q] : v;
+  }
 }
 
 // Element i of the row that starts at p, for 0 <= i < 2^31 / sizeof(T): a
@@ -495,9 +489,9 @@ __device__ inline T *at(T *p, unsigned i) {
 // ring) coordinate zl, iz[] are their ring indices (wrapped into [0, n)), and
 // contig tells whether they are consecutive in memory.  Only the lanes outside
 // the halo store, and only zones before the end of the segment.
-template <typename F>
+template <typename F, int M_>
 struct RingLane {
-  static constexpr int M = RingShape<F>::M, HLL = RingShape<F>::HLL, HRL = RingShape<F>::HRL;
+  static constexpr int M = M_, HLL = halo_lanes(M), HRL = halo_lanes(M);
   static constexpr int U = (WAVE - HLL - HRL) * M; // output zones per wave
   int n, lane, zl, aend, iz[M];
   bool contig;
@@ -508,11 +502,32 @@ struct RingLane {
     contig = zl >= 0 && zl + M <= n;
 #pragma unroll
     for (int q = 0; q < M; q++) {
-      const int z = (zl + q) % n;
-      iz[q] = z < 0 ? z + n : z;
+      const int z = zl + q;
+      if (n >= WAVE * M) { // the window is no longer than the ring: one wrap at most
+        iz[q] = z < 0 ? z + n : (z >= n ? z - n : z);
+      } else {
+        const int y = z % n;
+        iz[q] = y < 0 ? y + n : y;
+      }
     }
   }
   __device__ inline bool useful(int q) const { return lane >= HLL && lane < WAVE - HRL && zl + q < aend; }
+  // the lane's zones into the row that starts at p, shifted by Nm zones: pairs
+  // (at any alignment) where both zones are wanted and consecutive
+  __device__ inline void store(F *p, int Nm, const F (&v)[M]) const {
+    using V2 = F __attribute__((ext_vector_type(2), aligned(sizeof(F))));
+#pragma unroll
+    for (int q = 0; q < M; q += 2) {
+      int o = iz[q] + Nm;
+      o = o >= n ? o - n : o;
+      if (useful(q + 1) && o + 1 < n) {
+        *reinterpret_cast<V2 *>(at(p, (unsigned)o)) = V2{v[q], v[q + 1]};
+      } else if (useful(q)) {
+        *at(p, (unsigned)o) = v[q];
+        if (useful(q + 1)) *at(p, 0u) = v[q + 1];
+      }
+    }
+  }
   // the lane's zones of the row that starts at p, one load per zone and no
   // branch on contig (for loads inside a loop)
   __device__ inline void load_each(const F *p, F (&out)[M]) const {
@@ -546,7 +561,7 @@ struct RingLane {
 // Omega = 0 on a Cartesian mesh).
 template <typename F>
 struct RingConst {
-  F dt, S, vinv, vb, cdt, pfac, R, iR, Rw;
+  F Sdt, vinv, vb, cdt, pfac, R, iR, Rw; // Sdt: face area times dt
   PpaX<F> X;
   bool fg;
   int Nm;
@@ -569,8 +584,7 @@ __device__ inline RingConst<F> ring_const(const Mesh &m, int j, int k, int r, do
   RingConst<F> C;
   const int n = m.nx;
   const double dXd = m.DX(j, k), Sd = m.Sx(j, k);
-  C.dt = (F)dtd;
-  C.S = (F)Sd;
+  C.Sdt = (F)(Sd * dtd);
   C.vinv = (F)m.Vinv(j, k);
   C.fg = m.fargo != 0;
   const double v0d = C.fg ? v0[r] : 0.0;
@@ -581,17 +595,21 @@ __device__ inline RingConst<F> ring_const(const Mesh &m, int j, int k, int r, do
   int N = 0;
   double xid = 0.0;
   if (C.fg) ring_split_at(v0d, dtd, dXd, N, xid);
-  C.Nm = ((N % n) + n) % n; // shift on store: zone i goes to (i + Nm) mod n
+  // shift on store: zone i goes to (i + Nm) mod n
+  N = __builtin_amdgcn_readfirstlane(N);
+  if (N < -n || N >= n) N %= n;
+  C.Nm = N < 0 ? N + n : N;
   const F xi = (F)xid;
-  C.X = PpaX<F>{fabs(xi), fabs(xi) * (F(1) - fabs(xi)), xi >= F(0)};
-  C.cdt = (F)(dtd / dXd);
+  C.X = PpaX<F>{fabs(xi), F(1) - fabs(xi), xi >= F(0)};
+  const double idX = m.g.inv_dxlen((size_t)k * m.nyg + j);
+  C.cdt = (F)(dtd * idX);
   C.pfac = (F)(xid * dXd * Sd);
   if (m.geo == FARGO_CARTESIAN) {
     C.R = C.iR = F(1);
     C.Rw = F(0);
   } else {
     C.R = (F)m.Rcyl(j, k);
-    C.iR = (F)(1.0 / m.Rcyl(j, k));
+    C.iR = (F)(m.geo == FARGO_SPHERICAL ? m.dx * idX : m.g.inv_ymed(j));
     // FP32: the X momenta are deviations R (v_x - vb) from the ring's
     // background, and so is the v_x formed from them (no frame term)
     C.Rw = sizeof(F) == 4 ? F(0) : C.R * (F)m.omega;
@@ -609,62 +627,52 @@ __device__ constexpr int ring_qorder(int t) { return t + 2 < NQ ? t + 2 : t + 2 
 // van Leer residual sweep with w - v0, PPA residual, 12d along X; every
 // output is stored shifted by N zones, out of place (Pi+-_y and Pi+-_z into
 // Tout, e and the density and v_x into the state).
-template <typename F, int NQ>
-__device__ inline void ring_update(const RingLane<F> &L, const RingConst<F> &C, unsigned base,
-                                   const F (&Ra)[RingShape<F>::M], F (&w)[RingShape<F>::M],
-                                   const F (&Qall)[NQ][RingShape<F>::M], const TSetT<F> &Tout, bool has_e,
-                                   const StateT<F> &s) {
-  constexpr int M = RingShape<F>::M;
-  const int n = L.n;
-  auto out_at = [&](int q) { // index in the ring of the lane's zone q after the shift
-    const int o = L.iz[q] + C.Nm;
-    return (unsigned)(o >= n ? o - n : o);
-  };
-  const F dt = C.dt, S = C.S, vinv = C.vinv;
-  F ri0[M], Fl[M], ri1[M], El[M], rf[M];
-  Span<F, M> R;
-#pragma unroll
-  for (int q = 0; q < M; q++) R.a[q] = Ra[q];
+// RIGHT: xi >= 0.
+// Bound by its vector instructions until they went from some 1250 to 950 a wave
+// (one sign of xi per compiled form, the parabola's edges as distances, the
+// reciprocal's series, one wrap instead of a modulo, stores in pairs): the
+// 2048 x 768 x 96 disk 3.62 to 3.17 ms, where its 14 words a zone move at 5.3
+// TB/s; 1536 x 512 x 128 2.78 to 2.43; FP32 Z/X pass 3.26 to 2.88; the FP32
+// batch of 256 disks 962 to 834 us (then four zones a lane).
+template <bool RIGHT, typename F, int NQ, int M>
+__device__ inline void ring_update_dir(const RingLane<F, M> &L, const RingConst<F> &C, unsigned base,
+                                       const F (&Ra)[M], F (&w)[M],
+                                       const F (&Qall)[NQ][M], const TSetT<F> &Tout, bool has_e,
+                                       const StateT<F> &s) {
+  const F vinv = C.vinv;
+  F ri0[M], Fl[M], ri1[M], El[M], Eh[M], rf[M];
   // ---- density: van Leer residual sweep, then the PPA residual
   Upwind<F, M> Uw;
   {
 #pragma unroll
     for (int q = 0; q < M; q++) {
       w[q] -= C.vb;
-      ri0[q] = ring_rcp(R.a[q]);
+      ri0[q] = ring_rcp(Ra[q]);
     }
-    R.edges();
     F st[M];
     Uw.set(w, C.cdt);
-    vlx_faces(R, Uw, st);
+    vlx_faces(Ra, Uw, st);
 #pragma unroll
-    for (int q = 0; q < M; q++) Fl[q] = w[q] * st[q] * S * dt;
-    F Fh[M];
+    for (int q = 0; q < M; q++) Fl[q] = w[q] * st[q] * C.Sdt;
+    F Fh[M], R1[M];
     next_of(Fl, Fh);
-    Span<F, M> R1;
 #pragma unroll
     for (int q = 0; q < M; q++) {
-      R1.a[q] = R.a[q] - vinv * (Fh[q] - Fl[q]);
-      ri1[q] = ring_rcp(R1.a[q]);
-      rf[q] = R1.a[q];
+      R1[q] = Ra[q] - vinv * (Fh[q] - Fl[q]);
+      ri1[q] = ring_rcp(R1[q]);
+      rf[q] = R1[q];
     }
     if (C.fg) {
-      R1.edges();
+      // El, Eh: PPA mass flux through the zone's lower and upper face, each
+      // supplied by the zone upstream of it
       F val[M];
-      ppa_values(R1, C.X, val);
+      ppa_values<RIGHT>(R1, C.X, val);
 #pragma unroll
-      for (int q = 0; q < M; q++) val[q] = C.pfac * val[q];
-      // El: PPA mass flux through the zone's lower face (supplied by the
-      // upstream zone of that face)
-      if (C.X.right) prev_of(val, El);
-      else {
+      for (int q = 0; q < M; q++) (RIGHT ? Eh[q] : El[q]) = C.pfac * val[q];
+      if (RIGHT) prev_of(Eh, El);
+      else next_of(El, Eh);
 #pragma unroll
-        for (int q = 0; q < M; q++) El[q] = val[q];
-      }
-      F Eh[M];
-      next_of(El, Eh);
-#pragma unroll
-      for (int q = 0; q < M; q++) rf[q] = R1.a[q] - vinv * (Eh[q] - El[q]);
+      for (int q = 0; q < M; q++) rf[q] = R1[q] - vinv * (Eh[q] - El[q]);
     }
   }
   // ---- the other quantities
@@ -672,35 +680,24 @@ __device__ inline void ring_update(const RingLane<F> &L, const RingConst<F> &C, 
 #pragma unroll
   for (int t = 0; t < NQ; t++) {
     const int qi = ring_qorder<NQ>(t);
-    Span<F, M> Qs;
-    F Qv[M];
+    F Qv[M], Qs[M], G[M], Gh[M];
 #pragma unroll
-    for (int q = 0; q < M; q++) Qv[q] = Qall[t][q];
-#pragma unroll
-    for (int q = 0; q < M; q++) Qs.a[q] = Qv[q] * ri0[q];
-    Qs.edges();
-    F G[M], Gh[M];
+    for (int q = 0; q < M; q++) Qs[q] = Qall[t][q] * ri0[q];
     vlx_faces(Qs, Uw, G);
 #pragma unroll
     for (int q = 0; q < M; q++) G[q] = G[q] * Fl[q];
     next_of(G, Gh);
 #pragma unroll
-    for (int q = 0; q < M; q++) Qv[q] = Qv[q] - vinv * (Gh[q] - G[q]);
+    for (int q = 0; q < M; q++) Qv[q] = Qall[t][q] - vinv * (Gh[q] - G[q]);
     if (C.fg) {
 #pragma unroll
-      for (int q = 0; q < M; q++) Qs.a[q] = Qv[q] * ri1[q];
-      Qs.edges();
+      for (int q = 0; q < M; q++) Qs[q] = Qv[q] * ri1[q];
       F st[M], Hl[M], Hh[M];
-      ppa_values(Qs, C.X, st);
-      if (C.X.right) {
-        prev_of(st, Hl);
+      ppa_values<RIGHT>(Qs, C.X, st);
 #pragma unroll
-        for (int q = 0; q < M; q++) Hl[q] *= El[q];
-      } else {
-#pragma unroll
-        for (int q = 0; q < M; q++) Hl[q] = st[q] * El[q];
-      }
-      next_of(Hl, Hh);
+      for (int q = 0; q < M; q++) (RIGHT ? Hh[q] : Hl[q]) = st[q] * (RIGHT ? Eh[q] : El[q]);
+      if (RIGHT) prev_of(Hh, Hl);
+      else next_of(Hl, Hh);
 #pragma unroll
       for (int q = 0; q < M; q++) Qv[q] = Qv[q] - vinv * (Hh[q] - Hl[q]);
     }
@@ -711,27 +708,32 @@ __device__ inline void ring_update(const RingLane<F> &L, const RingConst<F> &C, 
 #pragma unroll
       for (int q = 0; q < M; q++) pxp[q] = Qv[q];
     } else {
-      F *dst = ((has_e && qi == NQ - 1) ? s.e : Tout.q[qi]) + base;
-#pragma unroll
-      for (int q = 0; q < M; q++)
-        if (L.useful(q)) *at(dst, out_at(q)) = Qv[q];
+      L.store(((has_e && qi == NQ - 1) ? s.e : Tout.q[qi]) + base, C.Nm, Qv);
     }
   }
   // ---- box 12d along X (Eq. 18) on the shifted ring: face i + N takes zones i - 1, i
-  F pp[M], rp[M];
+  F pp[M], rp[M], vx[M];
   prev_of(pxp, pp);
   prev_of(rf, rp);
 #pragma unroll
   for (int q = 0; q < M; q++) {
-    if (!L.useful(q)) continue;
     const F mom = ring_div(pp[q] + pxm[q], rp[q] + rf[q]);
-    const unsigned o = out_at(q);
     // FP64: the product with the ring's 1/R; FP32 divides, since there a
     // rounded 1/R would bias v_x the same way at every step
-    if constexpr (sizeof(F) == 8) *at(s.vx + base, o) = mom * C.iR - C.Rw;
-    else *at(s.vx + base, o) = mom / C.R - C.Rw;
-    *at(s.rho + base, o) = rf[q];
+    if constexpr (sizeof(F) == 8) vx[q] = mom * C.iR - C.Rw;
+    else vx[q] = mom / C.R - C.Rw;
   }
+  L.store(s.vx + base, C.Nm, vx);
+  L.store(s.rho + base, C.Nm, rf);
+}
+// xi has one sign on a ring: a wave takes one of the two forms.
+template <typename F, int NQ, int M>
+__device__ inline void ring_update(const RingLane<F, M> &L, const RingConst<F> &C, unsigned base,
+                                   const F (&Ra)[M], F (&w)[M],
+                                   const F (&Qall)[NQ][M], const TSetT<F> &Tout, bool has_e,
+                                   const StateT<F> &s) {
+  if (C.X.right) ring_update_dir<true, F, NQ, M>(L, C, base, Ra, w, Qall, Tout, has_e, s);
+  else ring_update_dir<false, F, NQ, M>(L, C, base, Ra, w, Qall, Tout, has_e, s);
 }
 
 // X transport of every active ring (2D meshes, where there is no Z sweep).
@@ -739,7 +741,7 @@ template <typename F, int NQ>
 __device__ __forceinline__ void ring_x_body(Mesh m, const F *__restrict__ vx2, TSetT<F> T, TSetT<F> Tout,
                                                 StateT<F> s, const double *__restrict__ v0,
                                                 const double *__restrict__ dtp, int nseg, unsigned bid_, unsigned nbk_) {
-  constexpr int M = RingShape<F>::M;
+  constexpr int M = ring_m<F>();
   const unsigned blk = xcd_remap(bid_, nbk_);
   const int lane = threadIdx.x & (WAVE - 1);
   // wave-uniform (readfirstlane), so that the ring's constants come through
@@ -749,7 +751,7 @@ __device__ __forceinline__ void ring_x_body(Mesh m, const F *__restrict__ vx2, T
   const int r = (int)(gw / nseg), seg = (int)(gw % nseg);
   const int j = m.j0 + r % m.ny, k = m.k0 + r / m.ny;
   const unsigned base = m.o32(0, j, k);
-  const RingLane<F> L(m.nx, seg, lane);
+  const RingLane<F, M> L(m.nx, seg, lane);
   const RingConst<F> C = ring_const<F>(m, j, k, r, *dtp, v0);
   // every load of the window is issued before the first use
   F w[M], Ra[M], Qall[NQ][M];
@@ -757,7 +759,7 @@ __device__ __forceinline__ void ring_x_body(Mesh m, const F *__restrict__ vx2, T
   L.load(vx2 + base, w);
 #pragma unroll
   for (int t = 0; t < NQ; t++) L.load(T.q[ring_qorder<NQ>(t)] + base, Qall[t]);
-  ring_update<F, NQ>(L, C, base, Ra, w, Qall, Tout, T.a[T_E] != nullptr, s);
+  ring_update<F, NQ, M>(L, C, base, Ra, w, Qall, Tout, T.a[T_E] != nullptr, s);
 }
 template <typename F, int NQ>
 __global__ __launch_bounds__(256, 3) void k_ring_x(Mesh m, const F *__restrict__ vx2, TSetT<F> T, TSetT<F> Tout,
@@ -783,7 +785,7 @@ template <typename F, int NQ>
 __global__ __launch_bounds__(256, 3) void k_zx(Mesh m, const F *__restrict__ vx2, const F *__restrict__ vz,
                                             TSetT<F> T, TSetT<F> Tout, StateT<F> s, const double *__restrict__ v0,
                                             const double *__restrict__ dtp, int nseg, int nkc) {
-  constexpr int M = RingShape<F>::M;
+  constexpr int M = 2;
   const unsigned blk = xcd_remap(blockIdx.x, gridDim.x);
   const int lane = threadIdx.x & (WAVE - 1);
   const long gw = (long)blk * (blockDim.x / WAVE) + __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
@@ -792,7 +794,7 @@ __global__ __launch_bounds__(256, 3) void k_zx(Mesh m, const F *__restrict__ vx2
   const long rest = gw / nseg;
   const int j = m.j0 + (int)(rest % m.ny), kc = (int)(rest / m.ny);
   const int a0 = m.k0 + kc * m.chunk, a1 = min(a0 + m.chunk, m.kn);
-  const RingLane<F> L(m.nx, seg, lane);
+  const RingLane<F, M> L(m.nx, seg, lane);
   const double dtd = *dtp;
   const F dt = (F)dtd;
   const bool has_e = T.a[T_E] != nullptr;
@@ -911,7 +913,7 @@ __global__ __launch_bounds__(256, 3) void k_zx(Mesh m, const F *__restrict__ vx2
       }
       const int r = (k - m.k0) * m.ny + (j - m.j0);
       const RingConst<F> C = ring_const<F>(m, j, k, r, dtd, v0);
-      ring_update<F, NQ>(L, C, m.o32(0, j, k), Ra, w, Qall, Tout, has_e, s);
+      ring_update<F, NQ, M>(L, C, m.o32(0, j, k), Ra, w, Qall, Tout, has_e, s);
     }
 #pragma unroll
     for (int c = 0; c < M; c++) {
@@ -1046,7 +1048,7 @@ void launch_sweep_z(Launch &L, const Mesh &m, const F *vz, const TSetT<F> &in, c
 template <typename F>
 void launch_ring_x(Launch &L, const Mesh &m, const F *vx2, const TSetT<F> &T, const TSetT<F> &Tout,
                    const StateT<F> &s, const double *v0, const double *dt) {
-  constexpr int U = (WAVE - RingShape<F>::HLL - RingShape<F>::HRL) * RingShape<F>::M;
+  constexpr int U = RingLane<F, ring_m<F>()>::U;
   const int nseg = (m.nx + U - 1) / U;
   const long waves = (long)m.nring * nseg;
   const unsigned nb = (unsigned)((waves + 3) / 4);
@@ -1064,7 +1066,7 @@ void launch_ring_x(Launch &L, const Mesh &m, const F *vx2, const TSetT<F> &T, co
 template <typename F>
 void launch_zx(Launch &L, const Mesh &m0, const F *vx2, const F *vz, const TSetT<F> &T, const TSetT<F> &Tout,
                const StateT<F> &s, const double *v0, const double *dt) {
-  constexpr int U = RingLane<F>::U;
+  constexpr int U = RingLane<F, 2>::U;
   static const long slots[2] = {4 * block_slots(k_zx<F, 6>, 256), 4 * block_slots(k_zx<F, 7>, 256)};
   int nkc;
   const int nseg = (m0.nx + U - 1) / U;
@@ -1218,7 +1220,7 @@ size_t ring_x_args_bytes() { return sizeof(RingArgs<F>); }
 template <typename F>
 unsigned ring_x_args(const Mesh &m, const F *vx2, const TSetT<F> &T, const TSetT<F> &Tout, const StateT<F> &s,
                      const double *v0, const double *dt, void *dst) {
-  constexpr int U = (WAVE - RingShape<F>::HLL - RingShape<F>::HRL) * RingShape<F>::M;
+  constexpr int U = RingLane<F, ring_m<F>()>::U;
   const int nseg = (m.nx + U - 1) / U;
   const unsigned nb = (unsigned)(((long)m.nring * nseg + 3) / 4);
   *(RingArgs<F> *)dst = RingArgs<F>{m, vx2, T, Tout, s, v0, dt, nseg, nb};

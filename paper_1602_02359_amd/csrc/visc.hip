@@ -48,7 +48,7 @@ __device__ __forceinline__ void visc_body(const Visc<F> &V, unsigned bid_, unsig
   const int i = z < 0 ? z + n : (z >= n ? z % n : z);
   const bool useful = lane >= 1 && lane <= VISC_U && z < n;
   const F dt = (F)*V.dt;
-  const double idphi = 1.0 / m.dx, isyk = 1.0 / m.g.syk(0), syk = m.g.syk(0), sxk = m.g.sxk(0);
+  const double idphi = 1.0 / m.dx, isyk = m.g.inv_syk(0), syk = m.g.syk(0), sxk = m.g.sxk(0);
   struct Row {
     F rho, nu, vx, vy;
   };

@@ -70,6 +70,23 @@ def test_viscous_pass_at_segment_edges(nx, ny, side):
     assert _step(prob) <= 1e-12
 
 
+@pytest.mark.parametrize("nx,turn", [(115, 0.0), (116, -3.0), (117, 3.0), (127, 0.4), (128, -0.4), (129, 50.0),
+                                     (239, -1.0), (240, 2.0), (241, -2.0), (255, 70.0), (256, -70.0), (257, 1.0),
+                                     (480, 7.0), (481, -0.01)])
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+def test_ring_segments_and_windows(nx, turn, precision):
+    """Rings one zone around a wave's segment (116 zones in FP64, 240 in FP32) and around its window (128 and 256), the
+    frame turned so that the circular shift goes either way, far and not at all, against the oracle."""
+    print("ring segments", nx, turn, precision, flush=True)
+    if precision == "fp64":
+        prob = W.random_problem("cyl", nx=nx, ny=6, nz=1, eos="adi", seed=nx, fargo=True, bc=SIDES["reflect"])
+        prob.fields["vx"] += turn
+    else:
+        prob = W.disk2d_cyl(nx=nx, ny=12, noise=1e-2)
+        prob.params["precision"] = "fp32"
+    assert _step(prob) <= (1e-12 if precision == "fp64" else 2e-6)
+
+
 @pytest.mark.parametrize("nx,ny,nz,eos,v0", [(1, 2100, 1, "adi", "minmax"), (2, 700, 3, "iso", "minmax"),
                                               (127, 2048, 1, "iso", "mean"), (129, 300, 7, "adi", "minmax"),
                                               (641, 1100, 2 + 1, "iso", "mean"), (1281, 12, 1, "adi", "mean"),
