@@ -57,7 +57,6 @@ def words_per_unit(p):
         "cfl": (2 + nvel, act),                              # rho, cs|e, velocities
         "source": ((2 + pw + nvel) + (nvel + adi), act),     # rho, cs|e, pot, v -> v'', e''
         "sweep_y": ((1 + nvel + adi) + nT, y_rows),          # rho, v'', e'' -> T (momenta formed on the fly)
-        "sweep_z": ((2 * nT + 1) if d3 else 0, act),         # T, v_z -> T
         "ring_x": ((nT + 1) + (2 + adi + 2 + (2 if d3 else 0)), act),  # T, v_x -> rho, v_x, e, Pi_y, Pi_z
         "zx_ring": ((nT + 2 + 2 + adi + 4) if d3 else 0, act),   # Y-swept T, v_z, v_x -> rho, v_x, e, Pi_y, Pi_z
         "vel_yz": ((1 + 2 + (2 if d3 else 0)) + (nvel - 1), act),      # rho, Pi_y, Pi_z -> v_y, v_z
@@ -68,8 +67,7 @@ def words_per_unit(p):
 # the file (and the shared internal header) is unchanged since the counters
 # were taken
 KERNEL_SOURCES = {"cfl": "timestep.hip", "source": "source.hip", "sweep_y": "transport.hip",
-                  "sweep_z": "transport.hip", "ring_x": "transport.hip", "zx_ring": "transport.hip",
-                  "vel_yz": "transport.hip"}
+                  "ring_x": "transport.hip", "zx_ring": "transport.hip", "vel_yz": "transport.hip"}
 
 
 def source_hash(kernel):
@@ -728,18 +726,14 @@ def main():
                 "effective_GBs": head["value"] * compulsory_bytes(p) / 1e9})
     roof = head["roofline"]
     roof["frac_of_copy_ceiling"] = round(roof["achieved"] / ceiling, 4)
-    if args.precision == "fp64" and "sweep_z" in head["kernels"] and "ring_x" in head["kernels"]:
-        # the ceilings of the two largest kernels' own access patterns: the Z
-        # sweep reads density, v_z and NQ conserved fields and writes density
-        # and the NQ fields (2 NQ + 3 words a zone), one column per thread;
-        # the X transport reads density, v_x and NQ fields and writes NQ (the
-        # Y/Z momenta, e, density and v_x: 2 NQ + 2 words), consecutive zones
-        # per wave
-        kz, kx = head["kernels"]["sweep_z"], head["kernels"]["ring_x"]
-        nqz = (round(kz["alg_bytes"] / (cells * 8)) - 3) // 2
-        nqx = (round(kx["alg_bytes"] / (cells * 8)) - 2) // 2
-        pats = {"sweep_z": dict(pattern_bandwidth(p["nx"], p["ny"], p["nz"], nqz + 2, nqz + 1), walk="column"),
-                "ring_x": dict(pattern_bandwidth(p["nx"], p["ny"], p["nz"], nqx + 2, nqx), walk="flat")}
+    if args.precision == "fp64" and "zx_ring" in head["kernels"]:
+        # the ceiling of the largest kernel's own access pattern: the fused Z
+        # sweep and X transport reads density, v_z, v_x and NQ conserved fields
+        # and writes NQ (the Y/Z momenta, e, density and v_x: 2 NQ + 3 words a
+        # zone), walking up the planes
+        kz = head["kernels"]["zx_ring"]
+        nq = (round(kz["alg_bytes"] / (cells * 8)) - 3) // 2
+        pats = {"zx_ring": dict(pattern_bandwidth(p["nx"], p["ny"], p["nz"], nq + 3, nq), walk="column")}
         for name, pat in pats.items():
             ceil_k = pat["column_march_GBs"] if pat["walk"] == "column" else pat["flat_GBs"]
             pat["kernel_GBs"] = head["kernels"][name]["GBs"]

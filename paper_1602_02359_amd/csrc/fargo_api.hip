@@ -18,7 +18,7 @@ using namespace fargo;
 namespace fargo {
 
 const char *kernel_names[K_COUNT] = {"set_dt", "bc", "cfl",    "dt_final", "split",
-                                     "source", "visc", "sweep_y", "sweep_z",  "ring_x",
+                                     "source", "visc", "sweep_y", "ring_x",
                                      "vel_yz", "shift",    "sums",      "sums_final", "zx_ring",
                                      "lfc_features", "lfc_fwd_l1", "lfc_fwd_l2", "lfc_fwd_l3", "lfc_drho",
                                      "lfc_wgrad_l3", "lfc_adj_l3", "lfc_wgrad_l2", "lfc_adj_l2",
@@ -646,21 +646,9 @@ void step_impl(fargo_ctx *ctx, const fargo_state *state, double dt, Launch &L) {
   launch_bc(L, m, P.rho, P.e, P.vx, P.vy, P.vz, true);                             // box 9
   const TSetT<F> TA = tset<F>(ctx, ctx->TA), TB = tset<F>(ctx, ctx->TB);
   launch_sweep_y(L, m, P, TB, dtp);                                                // boxes 12a-c, Y
-  const TSetT<F> *cur = &TB, *other = &TA;
-  if constexpr (std::is_same<F, float>::value) {
-    if (m.d3) { // FP32: Z, X, split, FARGO and 12d (v_x) in one pass
-      launch_zx(L, m, (const F *)P.vx, (const F *)P.vz, TB, TA, S, ctx->v0, dtp);
-      launch_vel(L, m, S, TA);                                                     // 12d (v_y, v_z)
-      return;
-    }
-  }
-  if (m.d3) {
-    launch_sweep_z(L, m, (const F *)P.vz, TB, TA, dtp);                            // Z
-    cur = &TA;
-    other = &TB;
-  }
-  launch_ring_x(L, m, (const F *)P.vx, *cur, *other, S, ctx->v0, dtp);           // X, split, FARGO, 12d (v_x)
-  launch_vel(L, m, S, *other);                                                     // 12d (v_y, v_z)
+  if (m.d3) launch_zx(L, m, (const F *)P.vx, (const F *)P.vz, TB, TA, S, ctx->v0, dtp); // Z, X, split, FARGO, 12d (v_x)
+  else launch_ring_x(L, m, (const F *)P.vx, TB, TA, S, ctx->v0, dtp);              // X, split, FARGO, 12d (v_x)
+  launch_vel(L, m, S, TA);                                                         // 12d (v_y, v_z)
 }
 
 } // namespace

@@ -399,7 +399,7 @@ void prof_end(Launch &L, int kid);
 
 enum KernelId {
   K_SET_DT = 0, K_BC, K_CFL, K_DT_FINAL, K_SPLIT, K_SRC, K_VISC, K_SWEEP_Y,
-  K_SWEEP_Z, K_RING_X, K_VEL, K_SHIFT, K_SUMS, K_SUMS_FINAL, K_ZX,
+  K_RING_X, K_VEL, K_SHIFT, K_SUMS, K_SUMS_FINAL, K_ZX,
   // learned flux correction
   K_LFC_FEATURES, K_LFC_FWD1, K_LFC_FWD2, K_LFC_FWD3, K_LFC_DRHO, K_LFC_W3, K_LFC_ADJ3, K_LFC_W2, K_LFC_ADJ2,
   K_LFC_W1, K_LFC_REDUCE, K_LFC_ADAM, K_LFC_APPLY,
@@ -503,15 +503,13 @@ void launch_visc(Launch &L, const Mesh &m, const StateT<R> &s, const R *vx2, con
 // box 12
 template <typename R>
 void launch_sweep_y(Launch &L, const Mesh &m, const StateT<R> &s, const TSetT<R> &out, const double *dt);
-template <typename R>
-void launch_sweep_z(Launch &L, const Mesh &m, const R *vz, const TSetT<R> &in, const TSetT<R> &out, const double *dt);
 // X sweep, split of Eq. 29, FARGO and 12d along X: reads T, writes rho, v_x, e
 // of the state and the Y/Z momenta into Tout (out of place, shifted)
 template <typename R>
 void launch_ring_x(Launch &L, const Mesh &m, const R *vx2, const TSetT<R> &T, const TSetT<R> &Tout,
                    const StateT<R> &s, const double *v0, const double *dt);
 // 3D: the Z sweep of the Y-swept set T fused with the X transport of
-// launch_ring_x (used for the FP32-bulk state)
+// launch_ring_x
 template <typename R>
 void launch_zx(Launch &L, const Mesh &m, const R *vx2, const R *vz, const TSetT<R> &T, const TSetT<R> &Tout,
                const StateT<R> &s, const double *v0, const double *dt);

@@ -16,9 +16,10 @@
 //   12d  velocities from the transported momenta (Eq. 18): v_x by the ring
 //        kernel, v_y and v_z by a final pass.
 //
-// Y and Z sweeps are column sweeps: a thread walks a chunk of one column with
-// a sliding window of three zones in registers, so that every value is loaded
-// once and every face flux and slope is computed once.
+// The Y sweep and, in the pass that it shares with the X transport, the Z sweep
+// are column sweeps: a thread walks a chunk of one column with a sliding window
+// of three zones in registers, so that every value is loaded once and every face
+// flux and slope is computed once.
 //
 // The field type F is double, or float for the FP32-bulk state; the arithmetic
 // of a kernel is carried out in F (per-ring constants such as dt/dX and the
@@ -57,59 +58,73 @@ __device__ inline float ring_rcp(float d) {
   return fmaf(r, fmaf(-d, r, 1.0f), r);
 }
 __device__ inline float ring_div(float n, float d) { return n * ring_rcp(d); }
-// The quotient of a column sweep's van Leer slope: correctly rounded in FP64
-// (the sweeps there are bound by memory), the refined reciprocal in FP32,
-// where the Y sweep is bound by its vector instructions (as in the ring
-// kernel and the Z part of k_zx)
+// The quotient of the Y sweep's van Leer slope: correctly rounded in FP64
+// (the sweep is bound by memory there), the refined reciprocal in FP32, where
+// it is bound by its vector instructions (as the ring kernel and k_zx are)
 __device__ inline double sweep_div(double n, double d) { return n / d; }
 __device__ inline float sweep_div(float n, float d) { return ring_div(n, d); }
 
-// van Leer slope per unit length from the one-sided differences and the
-// centre distances below (hm) and above (hp): 2 dl dr/(dl + dr) with
-// dl = dm/hm, dr = dp/hp, zero unless dl dr > 0.
-// Contraction is off in the slopes: a sweep forms the first slope of a chunk
-// of zones before its loop and the others inside it, and the same rounding
-// in both places keeps the result independent of the chunk size.
-template <typename F>
+// Half the van Leer slope per unit length from the one-sided differences and
+// the centre distances below (hm) and above (hp): dl dr/(dl + dr) with
+// dl = dm/hm, dr = dp/hp, zero unless dl dr > 0.  b adds, for a quantity stored
+// as a deviation from a background that changes from zone to zone, the
+// background's increments across the lower and upper face (bm, bp), so that the
+// differences are those of the full values.
+// Contraction is off in the slopes and their one fused operation is written
+// out: a sweep forms the first slope of a chunk of zones before its loop and
+// the others inside it, and the same rounding in both places keeps the result
+// independent of the chunk size.  DIV: the quotient.
+template <class DIV, typename F>
+__device__ inline F vl_half(F dm, F dp, F hm, F hp) {
+#pragma clang fp contract(off)
+  const F pr = dm * dp;
+  return pr > F(0) ? DIV::of(pr, fma(dm, hp, dp * hm)) : F(0);
+}
+template <class DIV, typename F>
 __device__ inline F vl_slope(F qm, F q0, F qp, F hm, F hp) {
 #pragma clang fp contract(off)
-  F dm = q0 - qm, dp = qp - q0;
-  F pr = dm * dp;
-  return pr > F(0) ? sweep_div(F(2) * pr, dm * hp + dp * hm) : F(0);
+  return vl_half<DIV>(q0 - qm, qp - q0, hm, hp);
 }
-
-// The same slope for a quantity stored as a deviation from a background that
-// changes from zone to zone: bm and bp are the background's increments across
-// the lower and upper face, so the differences are those of the full values.
-template <typename F>
+template <class DIV, typename F>
 __device__ inline F vl_slope_b(F qm, F q0, F qp, F hm, F hp, F bm, F bp) {
 #pragma clang fp contract(off)
-  F dm = (q0 - qm) + bm, dp = (qp - q0) + bp;
-  F pr = dm * dp;
-  return pr > F(0) ? sweep_div(F(2) * pr, dm * hp + dp * hm) : F(0);
+  return vl_half<DIV>((q0 - qm) + bm, (qp - q0) + bp, hm, hp);
 }
+struct SweepDiv {
+  template <typename F>
+  __device__ static inline F of(F n, F d) { return sweep_div(n, d); }
+};
+struct RingDiv {
+  template <typename F>
+  __device__ static inline F of(F n, F d) { return ring_div(n, d); }
+};
 
-// half-step interface value at a face, upwinded on w (Eq. 15)
+// Upwinding at a face with velocity w (Eq. 15): the half-step interface value is
+// q + s (L - w dt) from the zone below (width Ll), q - s (L + w dt) from the one
+// above (width Lr), with s half the slope; the factors serve every quantity.
 template <typename F>
-__device__ inline F vl_star(F w, F dt, F ql, F al, F Ll, F qr, F ar, F Lr) {
-  return w >= F(0) ? ql + al * (Ll - w * dt) * F(0.5) : qr - ar * (Lr + w * dt) * F(0.5);
-}
+struct Upface {
+  bool pos;
+  F cl, cr;
+  __device__ inline Upface(F w, F dt, F Ll, F Lr) : pos(w >= F(0)), cl(Ll - w * dt), cr(Lr + w * dt) {}
+  __device__ inline F star(F ql, F sl, F qr, F sr) const { return pos ? ql + sl * cl : qr - sr * cr; }
+};
 
-template <typename F, int NQ, bool CT>
+template <typename F, int NQ>
 struct Zone {
   F rho, q[NQ]; // density, Q/rho
   F w;          // velocity on the zone's lower face in the sweep direction
-  F T[CT ? NQ : 1]; // conserved Q, when carried in the window (CT)
+  F e;          // the energy, as loaded
 };
 
 // Column sweep over zones [a0, a1) of one column.  `raw(a, RW&)` issues the
 // loads of zone a, `derive(a, const RW&, Zone&)` forms its density, Q/rho and
 // lower-face velocity, `Tof(a, const Zone&, q)` gives the conserved Q of zone
-// a (carried in the window when CT, else formed again); `geo` gives L(a) (zone width), h(f)
-// (centre distance at face f), S(f), Vi(a); `st(a, rho, T[])` stores the
-// updated zone.  The loads of zone f + 1 + PD are issued while zone f is
-// being computed (PD = 1 or 2 zones of loads in flight; with two, the two
-// load buffers take turns, so that no copy waits for a load).
+// a; `geo` gives L(a) (zone width), h(f) (centre distance at face f), S(f),
+// Vi(a); `st(a, rho, T[])` stores the updated zone.  The loads of zone f + 3
+// are issued while zone f is being computed (two zones of loads in flight,
+// measured faster than one on 3D meshes and on the fused batch of 2D disks; the
+// two load buffers take turns, so that no copy waits for a load).
 // With DEV, quantities 0 and 1 (the X momenta) are deviations from a
 // background ell that is constant on a ring (the FP32-bulk state): `dl(f)`
 // gives ell(f) - ell(f - 1) at face f.  Slopes take the full differences,
@@ -117,12 +132,10 @@ struct Zone {
 // lower zone, and the update of a zone adds the background carried in
 // through its lower face, so that in exact arithmetic the result is the
 // full update minus ell times the updated density.
-template <typename F, int NQ, bool CT, bool DEV, class RW, int PD = 1, class RAW, class DER, class TOF, class GEO,
-          class ST, class DLF>
+template <typename F, int NQ, bool DEV, class RW, class RAW, class DER, class TOF, class GEO, class ST, class DLF>
 __device__ inline void column_sweep(int a0, int a1, F dt, const RAW &raw, const DER &derive, const TOF &Tof,
                                     const GEO &geo, const ST &st, const DLF &dl) {
-  static_assert(PD == 1 || PD == 2, "one or two zones of loads in flight");
-  Zone<F, NQ, CT> zm, z0, zp;
+  Zone<F, NQ> zm, z0, zp;
   RW rn, rn2;
   raw(a0 - 2, rn);
   derive(a0 - 2, rn, zp); // used only for the first slope
@@ -131,40 +144,41 @@ __device__ inline void column_sweep(int a0, int a1, F dt, const RAW &raw, const 
   raw(a0, rn);
   derive(a0, rn, z0);
   raw(a0 + 1, rn);
-  if (PD == 2 && a0 + 2 <= a1 + 1) raw(a0 + 2, rn2);
+  if (a0 + 2 <= a1 + 1) raw(a0 + 2, rn2);
   F sm[NQ + 1], s0[NQ + 1];
   F dlf = DEV ? dl(a0) : F(0); // background increment at face f
   {
     F hm = geo.h(a0 - 1), hp = geo.h(a0);
-    sm[NQ] = vl_slope(zp.rho, zm.rho, z0.rho, hm, hp);
+    sm[NQ] = vl_slope<SweepDiv>(zp.rho, zm.rho, z0.rho, hm, hp);
 #pragma unroll
     for (int q = 0; q < NQ; q++)
-      sm[q] = (DEV && q < 2) ? vl_slope_b(zp.q[q], zm.q[q], z0.q[q], hm, hp, dl(a0 - 1), dlf)
-                             : vl_slope(zp.q[q], zm.q[q], z0.q[q], hm, hp);
+      sm[q] = (DEV && q < 2) ? vl_slope_b<SweepDiv>(zp.q[q], zm.q[q], z0.q[q], hm, hp, dl(a0 - 1), dlf)
+                             : vl_slope<SweepDiv>(zp.q[q], zm.q[q], z0.q[q], hm, hp);
   }
   F Fp = F(0), FQp[NQ];
 #pragma unroll
   for (int q = 0; q < NQ; q++) FQp[q] = F(0);
   F Lm = geo.L(a0 - 1);
   // face f: zone f + 1 from buffer cur, whose loads are then refilled with
-  // those of zone f + 1 + PD
+  // those of zone f + 3
   auto face = [&](int f, RW &cur) {
     derive(f + 1, cur, zp);
-    if (f + 1 + PD <= a1 + 1) raw(f + 1 + PD, cur);
+    if (f + 3 <= a1 + 1) raw(f + 3, cur);
     const F dlf1 = DEV ? dl(f + 1) : F(0);
     F hm = geo.h(f), hp = geo.h(f + 1);
-    s0[NQ] = vl_slope(zm.rho, z0.rho, zp.rho, hm, hp);
+    s0[NQ] = vl_slope<SweepDiv>(zm.rho, z0.rho, zp.rho, hm, hp);
 #pragma unroll
     for (int q = 0; q < NQ; q++)
-      s0[q] = (DEV && q < 2) ? vl_slope_b(zm.q[q], z0.q[q], zp.q[q], hm, hp, dlf, dlf1)
-                             : vl_slope(zm.q[q], z0.q[q], zp.q[q], hm, hp);
+      s0[q] = (DEV && q < 2) ? vl_slope_b<SweepDiv>(zm.q[q], z0.q[q], zp.q[q], hm, hp, dlf, dlf1)
+                             : vl_slope<SweepDiv>(zm.q[q], z0.q[q], zp.q[q], hm, hp);
     F L0 = geo.L(f);
     F w = z0.w;
-    F Fr = w * vl_star(w, dt, zm.rho, sm[NQ], Lm, z0.rho, s0[NQ], L0) * geo.S(f) * dt;
+    const Upface<F> U(w, dt, Lm, L0);
+    F Fr = w * U.star(zm.rho, sm[NQ], z0.rho, s0[NQ]) * geo.S(f) * dt;
     F FQ[NQ];
 #pragma unroll
     for (int q = 0; q < NQ; q++)
-      FQ[q] = vl_star(w, dt, zm.q[q], sm[q], Lm, (DEV && q < 2) ? z0.q[q] + dlf : z0.q[q], s0[q], L0) * Fr;
+      FQ[q] = U.star(zm.q[q], sm[q], (DEV && q < 2) ? z0.q[q] + dlf : z0.q[q], s0[q]) * Fr;
     if (f > a0) {
       F vi = geo.Vi(f - 1);
       F Tn[NQ];
@@ -185,15 +199,10 @@ __device__ inline void column_sweep(int a0, int a1, F dt, const RAW &raw, const 
     Lm = L0;
     dlf = dlf1;
   };
-  if constexpr (PD == 1) {
 #pragma unroll 1
-    for (int f = a0; f <= a1; f++) face(f, rn);
-  } else {
-#pragma unroll 1
-    for (int f = a0; f <= a1; f += 2) {
-      face(f, rn);
-      if (f + 1 <= a1) face(f + 1, rn2);
-    }
+  for (int f = a0; f <= a1; f += 2) {
+    face(f, rn);
+    if (f + 1 <= a1) face(f + 1, rn2);
   }
 }
 
@@ -235,7 +244,7 @@ __device__ __forceinline__ void sweep_y_body(Mesh m, const F *__restrict__ rho, 
     }
     if (ADI) z.e = e[c];
   };
-  auto derive = [&](int a, const Raw &w, Zone<F, NQ, false> &z) {
+  auto derive = [&](int a, const Raw &w, Zone<F, NQ> &z) {
     const F r = w.rho;
     z.rho = r;
     z.w = w.vy0;
@@ -254,13 +263,13 @@ __device__ __forceinline__ void sweep_y_body(Mesh m, const F *__restrict__ rho, 
     }
     if (ADI) {
       z.q[NQ - 1] = w.e / r;
-      z.T[0] = w.e; // the window carries no other conserved value (CT is false)
+      z.e = w.e;
     }
   };
   // the momenta are rho m(v) exactly as formed; e as loaded, carried in the
   // window (read again three rows later, it would come from memory again)
-  auto Tof = [&](int, const Zone<F, NQ, false> &z, int q) {
-    if (ADI && q == NQ - 1) return z.T[0];
+  auto Tof = [&](int, const Zone<F, NQ> &z, int q) {
+    if (ADI && q == NQ - 1) return z.e;
     return z.rho * z.q[q];
   };
   struct Geo {
@@ -278,10 +287,7 @@ __device__ __forceinline__ void sweep_y_body(Mesh m, const F *__restrict__ rho, 
     for (int q = 0; q < NQ; q++) out.q[q][c] = T[q];
   };
   auto dl = [&](int f) { return (F)m.bg(BG_DLY, f, k); };
-  // two zones of loads in flight (measured faster on 3D meshes and on the
-  // fused batch of 2D disks; the Z sweep, whose window holds the conserved
-  // values too, gains nothing from it)
-  column_sweep<F, NQ, false, DEV, Raw, 2>(a0, a1, dt, raw, derive, Tof, geo, st, dl);
+  column_sweep<F, NQ, DEV, Raw>(a0, a1, dt, raw, derive, Tof, geo, st, dl);
 }
 template <typename F, int NQ, bool D3, bool ADI>
 __global__ __launch_bounds__(256) void k_sweep_y(Mesh m, const F *__restrict__ rho, const F *__restrict__ vx,
@@ -289,60 +295,6 @@ __global__ __launch_bounds__(256) void k_sweep_y(Mesh m, const F *__restrict__ r
                                                  const F *__restrict__ e, TSetT<F> out,
                                                  const double *__restrict__ dtp, int nchunk) {
   sweep_y_body<F, NQ, D3, ADI>(m, rho, vx, vy, vz, e, out, dtp, nchunk, blockIdx.x, gridDim.x);
-}
-
-// ------------------------------------------------------------------------
-// Z sweep on the Y-swept quantities.
-// ------------------------------------------------------------------------
-template <typename F, int NQ>
-__global__ __launch_bounds__(256) void k_sweep_z(Mesh m, const F *__restrict__ vz, TSetT<F> in, TSetT<F> out,
-                                                 const double *__restrict__ dtp, int nchunk) {
-  unsigned Lb = xcd_remap(blockIdx.x, gridDim.x);
-  int jr = (int)(Lb % (unsigned)m.ny);
-  unsigned rest = Lb / (unsigned)m.ny;
-  int ch = (int)(rest % (unsigned)nchunk), ib = (int)(rest / (unsigned)nchunk);
-  int i = ib * (int)blockDim.x + (int)threadIdx.x;
-  if (i >= m.nx) return;
-  const int j = m.j0 + jr;
-  const int a0 = m.k0 + ch * m.chunk, a1 = min(a0 + m.chunk, m.kn);
-  const F dt = (F)*dtp;
-  struct Raw {
-    F rho, w, T[NQ];
-  };
-  auto raw = [&](int a, Raw &z) {
-    const unsigned c = m.o32(i, j, a);
-    z.rho = in.a[T_RHO][c];
-    z.w = vz[c];
-#pragma unroll
-    for (int q = 0; q < NQ; q++) z.T[q] = in.q[q][c];
-  };
-  auto derive = [&](int, const Raw &w, Zone<F, NQ, true> &z) {
-    const F ri = F(1) / w.rho;
-    z.rho = w.rho;
-    z.w = w.w;
-#pragma unroll
-    for (int q = 0; q < NQ; q++) {
-      z.T[q] = w.T[q];
-      z.q[q] = w.T[q] * ri;
-    }
-  };
-  auto Tof = [&](int, const Zone<F, NQ, true> &z, int q) { return z.T[q]; };
-  struct Geo {
-    const Mesh &m;
-    int j;
-    __device__ F L(int a) const { return (F)m.Lz(j, a); }
-    __device__ F h(int f) const { return (F)m.hz(j, f); }
-    __device__ F S(int f) const { return (F)m.Sz(j, f); }
-    __device__ F Vi(int a) const { return (F)m.Vinv(j, a); }
-  } geo{m, j};
-  auto st = [&](int a, F r, const F (&T)[NQ]) {
-    unsigned c = m.o32(i, j, a);
-    out.a[T_RHO][c] = r;
-#pragma unroll
-    for (int q = 0; q < NQ; q++) out.q[q][c] = T[q];
-  };
-  auto dl = [&](int f) { return (F)m.bg(BG_DLZ, j, f); };
-  column_sweep<F, NQ, true, sizeof(F) == 4, Raw>(a0, a1, dt, raw, derive, Tof, geo, st, dl);
 }
 
 // ------------------------------------------------------------------------
@@ -356,13 +308,18 @@ __global__ __launch_bounds__(256) void k_sweep_z(Mesh m, const F *__restrict__ v
 // Outputs are written out of place (shifted by N on store), so that the
 // segments of a ring can run in any order.
 // ------------------------------------------------------------------------
-// The ring kernel takes two zones per lane in FP64 and four in FP32, where they
-// fit in registers (five waves per SIMD) and save half the lane moves a zone and
-// a third of the halo: the batch of 256 disks 834 to 760 us.  The fused Z/X pass
-// takes two.
+// Zones per lane.  The ring kernel takes two in FP64 and four in FP32, where
+// they fit in registers (five waves per SIMD) and save half the lane moves a
+// zone and a third of the halo: the batch of 256 disks 834 to 760 us.  The fused
+// Z/X pass, which also holds the window of the Z sweep, takes one in FP64 (162
+// registers, three waves per SIMD; two needed 310, one wave) and two in FP32.
 template <typename F>
 constexpr int ring_m() { return sizeof(F) == 8 ? 2 : 4; }
-constexpr int halo_lanes(int M) { return (6 + M - 1) / M; } // on each side
+template <typename F>
+constexpr int zx_m() { return sizeof(F) == 8 ? 1 : 2; }
+// halo lanes below and above: a zone's result depends on zones z - 6 .. z + 5
+constexpr int halo_below(int M) { return (6 + M - 1) / M; } // halo lanes
+constexpr int halo_above(int M) { return (5 + M - 1) / M; }
 
 // The differences of neighbouring zones: d[x] between zones x - 1 and x of the
 // lane, x = 0 .. M, and the value below the first zone.
@@ -491,7 +448,7 @@ __device__ inline T *at(T *p, unsigned i) {
 // the halo store, and only zones before the end of the segment.
 template <typename F, int M_>
 struct RingLane {
-  static constexpr int M = M_, HLL = halo_lanes(M), HRL = halo_lanes(M);
+  static constexpr int M = M_, HLL = halo_below(M), HRL = halo_above(M);
   static constexpr int U = (WAVE - HLL - HRL) * M; // output zones per wave
   int n, lane, zl, aend, iz[M];
   bool contig;
@@ -512,22 +469,6 @@ struct RingLane {
     }
   }
   __device__ inline bool useful(int q) const { return lane >= HLL && lane < WAVE - HRL && zl + q < aend; }
-  // the lane's zones into the row that starts at p, shifted by Nm zones: pairs
-  // (at any alignment) where both zones are wanted and consecutive
-  __device__ inline void store(F *p, int Nm, const F (&v)[M]) const {
-    using V2 = F __attribute__((ext_vector_type(2), aligned(sizeof(F))));
-#pragma unroll
-    for (int q = 0; q < M; q += 2) {
-      int o = iz[q] + Nm;
-      o = o >= n ? o - n : o;
-      if (useful(q + 1) && o + 1 < n) {
-        *reinterpret_cast<V2 *>(at(p, (unsigned)o)) = V2{v[q], v[q + 1]};
-      } else if (useful(q)) {
-        *at(p, (unsigned)o) = v[q];
-        if (useful(q + 1)) *at(p, 0u) = v[q + 1];
-      }
-    }
-  }
   // the lane's zones of the row that starts at p, one load per zone and no
   // branch on contig (for loads inside a loop)
   __device__ inline void load_each(const F *p, F (&out)[M]) const {
@@ -550,6 +491,43 @@ struct RingLane {
     } else {
 #pragma unroll
       for (int q = 0; q < M; q++) out[q] = *at(p, (unsigned)iz[q]);
+    }
+  }
+};
+
+// Where the lane's zones go when the ring is stored shifted by Nm zones: pairs
+// (at any alignment) where both zones are wanted and consecutive.  Formed once
+// for the quantities of a ring.
+template <typename F, int M>
+struct RingOut {
+  static constexpr int P = M == 1 ? 1 : 2, H = M / P; // zones per store, stores
+  unsigned o[H];
+  bool one[H], two[H], wrap[H]; // the first zone alone, both at o, the second at the ring's start
+  __device__ inline RingOut(const RingLane<F, M> &L, int Nm) {
+#pragma unroll
+    for (int h = 0; h < H; h++) {
+      const int q = P * h;
+      int z = L.iz[q] + Nm;
+      z = z >= L.n ? z - L.n : z;
+      o[h] = (unsigned)z;
+      const bool second = P == 2 && L.useful(q + P - 1);
+      two[h] = second && z + 1 < L.n;
+      wrap[h] = second && !two[h];
+      one[h] = L.useful(q) && !two[h];
+    }
+  }
+  __device__ inline void operator()(F *p, const F (&v)[M]) const {
+    using V2 = F __attribute__((ext_vector_type(2), aligned(sizeof(F))));
+#pragma unroll
+    for (int h = 0; h < H; h++) {
+      if constexpr (P == 1) {
+        if (one[h]) *at(p, o[h]) = v[h];
+      } else if (two[h]) {
+        *reinterpret_cast<V2 *>(at(p, o[h])) = V2{v[2 * h], v[2 * h + 1]};
+      } else if (one[h]) {
+        *at(p, o[h]) = v[2 * h];
+        if (wrap[h]) *at(p, 0u) = v[2 * h + 1];
+      }
     }
   }
 };
@@ -640,6 +618,7 @@ __device__ inline void ring_update_dir(const RingLane<F, M> &L, const RingConst<
                                        const F (&Qall)[NQ][M], const TSetT<F> &Tout, bool has_e,
                                        const StateT<F> &s) {
   const F vinv = C.vinv;
+  const RingOut<F, M> put(L, C.Nm);
   F ri0[M], Fl[M], ri1[M], El[M], Eh[M], rf[M];
   // ---- density: van Leer residual sweep, then the PPA residual
   Upwind<F, M> Uw;
@@ -708,7 +687,7 @@ __device__ inline void ring_update_dir(const RingLane<F, M> &L, const RingConst<
 #pragma unroll
       for (int q = 0; q < M; q++) pxp[q] = Qv[q];
     } else {
-      L.store(((has_e && qi == NQ - 1) ? s.e : Tout.q[qi]) + base, C.Nm, Qv);
+      put(((has_e && qi == NQ - 1) ? s.e : Tout.q[qi]) + base, Qv);
     }
   }
   // ---- box 12d along X (Eq. 18) on the shifted ring: face i + N takes zones i - 1, i
@@ -723,8 +702,8 @@ __device__ inline void ring_update_dir(const RingLane<F, M> &L, const RingConst<
     if constexpr (sizeof(F) == 8) vx[q] = mom * C.iR - C.Rw;
     else vx[q] = mom / C.R - C.Rw;
   }
-  L.store(s.vx + base, C.Nm, vx);
-  L.store(s.rho + base, C.Nm, rf);
+  put(s.vx + base, vx);
+  put(s.rho + base, rf);
 }
 // xi has one sign on a ring: a wave takes one of the two forms.
 template <typename F, int NQ, int M>
@@ -777,15 +756,22 @@ __global__ __launch_bounds__(256, 3) void k_ring_x(Mesh m, const F *__restrict__
 // quantities never go through memory.  The halo zones of the segment are
 // swept along Z as well, so segments stay independent.  The conserved
 // quantities handed on are formed again as rho (Q/rho).
-// Used for the FP32-bulk state, where the window and the X transport fit in
-// about 160 VGPRs (three waves per SIMD); in FP64 the kernel needs about 310
-// (one wave per SIMD) and the separate Z sweep and ring kernel are faster.
 // Its quotients, in the Z part as in the X part, are those of ring_div.
+// Bound by its vector instructions (some 850 a wave and plane in FP64, 4 cycles
+// each), and yet faster than a Z sweep and a ring kernel apart, whose 29 words a
+// zone between them become 16: 2048 x 768 x 96 in FP64 3.78 + 3.19 ms apart, 5.42
+// fused, 5.14 with the stores' places formed once per ring, the half step's
+// factors once per face and the halo a lane shorter; 1536 x 512 x 128 adiabatic
+// 2.85 + 2.45, 4.61, 4.17 (at two waves per SIMD, where the three that the
+// launch bound would allow spill: 4.74); 160 x 144 x 120: 96 + 83, 143, 132 us.
+// In FP32 2.90 to 2.87 ms.  Selects in place of the branches around quotients
+// cost registers and gained nothing, nor did two or three planes per turn of the
+// loop, which save the window's moves but spill.
 template <typename F, int NQ>
-__global__ __launch_bounds__(256, 3) void k_zx(Mesh m, const F *__restrict__ vx2, const F *__restrict__ vz,
+__global__ __launch_bounds__(256, (sizeof(F) == 8 && NQ == 7 ? 2 : 3)) void k_zx(Mesh m, const F *__restrict__ vx2, const F *__restrict__ vz,
                                             TSetT<F> T, TSetT<F> Tout, StateT<F> s, const double *__restrict__ v0,
                                             const double *__restrict__ dtp, int nseg, int nkc) {
-  constexpr int M = 2;
+  constexpr int M = zx_m<F>();
   const unsigned blk = xcd_remap(blockIdx.x, gridDim.x);
   const int lane = threadIdx.x & (WAVE - 1);
   const long gw = (long)blk * (blockDim.x / WAVE) + __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
@@ -826,18 +812,6 @@ __global__ __launch_bounds__(256, 3) void k_zx(Mesh m, const F *__restrict__ vx2
     }
   };
   auto Lz = [&](int a) { return (F)m.Lz(j, a); };
-  // the van Leer slopes of vl_slope and vl_slope_b with the quotient of
-  // ring_div
-  auto vl_slope_q = [](F qm, F q0, F qp, F hm, F hp) {
-#pragma clang fp contract(off)
-    const F dm = q0 - qm, dp = qp - q0, pr = dm * dp;
-    return pr > F(0) ? ring_div(F(2) * pr, dm * hp + dp * hm) : F(0);
-  };
-  auto vl_slope_qb = [](F qm, F q0, F qp, F hm, F hp, F bm, F bp) {
-#pragma clang fp contract(off)
-    const F dm = (q0 - qm) + bm, dp = (qp - q0) + bp, pr = dm * dp;
-    return pr > F(0) ? ring_div(F(2) * pr, dm * hp + dp * hm) : F(0);
-  };
   // FP32: the X momenta (quantities 0 and 1) are deviations from a background
   // constant on each ring, as in column_sweep; dl(f) is its increment across
   // Z face f
@@ -859,11 +833,11 @@ __global__ __launch_bounds__(256, 3) void k_zx(Mesh m, const F *__restrict__ vx2
     const F hm = hz(a0 - 1), hp = hz(a0), dlm = dl(a0 - 1);
 #pragma unroll
     for (int c = 0; c < M; c++) {
-      sm[NQ][c] = vl_slope_q(zp.rho[c], zm.rho[c], z0.rho[c], hm, hp);
+      sm[NQ][c] = vl_slope<RingDiv>(zp.rho[c], zm.rho[c], z0.rho[c], hm, hp);
 #pragma unroll
       for (int q = 0; q < NQ; q++)
-        sm[q][c] = (DEV && q < 2) ? vl_slope_qb(zp.q[q][c], zm.q[q][c], z0.q[q][c], hm, hp, dlm, dlf)
-                                  : vl_slope_q(zp.q[q][c], zm.q[q][c], z0.q[q][c], hm, hp);
+        sm[q][c] = (DEV && q < 2) ? vl_slope_b<RingDiv>(zp.q[q][c], zm.q[q][c], z0.q[q][c], hm, hp, dlm, dlf)
+                                  : vl_slope<RingDiv>(zp.q[q][c], zm.q[q][c], z0.q[q][c], hm, hp);
     }
   }
   F Fp[M], FQp[NQ][M];
@@ -882,18 +856,19 @@ __global__ __launch_bounds__(256, 3) void k_zx(Mesh m, const F *__restrict__ vx2
     F Fr[M], FQ[NQ][M];
 #pragma unroll
     for (int c = 0; c < M; c++) {
-      s0[NQ][c] = vl_slope_q(zm.rho[c], z0.rho[c], zp.rho[c], hm, hp);
+      s0[NQ][c] = vl_slope<RingDiv>(zm.rho[c], z0.rho[c], zp.rho[c], hm, hp);
 #pragma unroll
       for (int q = 0; q < NQ; q++)
-        s0[q][c] = (DEV && q < 2) ? vl_slope_qb(zm.q[q][c], z0.q[q][c], zp.q[q][c], hm, hp, dlf, dlf1)
-                                  : vl_slope_q(zm.q[q][c], z0.q[q][c], zp.q[q][c], hm, hp);
+        s0[q][c] = (DEV && q < 2) ? vl_slope_b<RingDiv>(zm.q[q][c], z0.q[q][c], zp.q[q][c], hm, hp, dlf, dlf1)
+                                  : vl_slope<RingDiv>(zm.q[q][c], z0.q[q][c], zp.q[q][c], hm, hp);
       const F w = z0.w[c];
-      Fr[c] = w * vl_star(w, dt, zm.rho[c], sm[NQ][c], Lm, z0.rho[c], s0[NQ][c], L0) * Sf * dt;
+      const Upface<F> U(w, dt, Lm, L0);
+      Fr[c] = w * U.star(zm.rho[c], sm[NQ][c], z0.rho[c], s0[NQ][c]) * Sf * dt;
 #pragma unroll
       for (int q = 0; q < NQ; q++) {
         // relative to the background of the face's lower zone
         const F qr = (DEV && q < 2) ? z0.q[q][c] + dlf : z0.q[q][c];
-        FQ[q][c] = vl_star(w, dt, zm.q[q][c], sm[q][c], Lm, qr, s0[q][c], L0) * Fr[c];
+        FQ[q][c] = U.star(zm.q[q][c], sm[q][c], qr, s0[q][c]) * Fr[c];
       }
     }
     if (f > a0) {
@@ -1007,18 +982,6 @@ void sweep_y_launch(Launch &L, const Mesh &m0, const StateT<F> &s, const TSetT<F
   k_sweep_y<F, NQ, D3, ADI><<<nb, bs, 0, L.s>>>(m, s.rho, s.vx, s.vy, s.vz, s.e, out, dt, nchunk);
 }
 
-template <typename F, int NQ>
-void sweep_z_launch(Launch &L, const Mesh &m0, const F *vz, const TSetT<F> &in, const TSetT<F> &out, const double *dt) {
-  constexpr auto kern = k_sweep_z<F, NQ>;
-  static const long slots[4] = {block_slots(kern, 64), block_slots(kern, 128), block_slots(kern, 192),
-                                block_slots(kern, 256)};
-  int nib, bs, nchunk;
-  row_blocks(m0.nx, nib, bs);
-  const Mesh m = filled(m0, m0.nz, (long)nib * m0.ny, slots[bs / WAVE - 1], nchunk);
-  unsigned nb = (unsigned)nib * (unsigned)nchunk * (unsigned)m.ny;
-  k_sweep_z<F, NQ><<<nb, bs, 0, L.s>>>(m, vz, in, out, dt, nchunk);
-}
-
 } // namespace
 
 // s: rho of the state, post-source velocities and energy (box 9 filled)
@@ -1036,14 +999,6 @@ void launch_sweep_y(Launch &L, const Mesh &m, const StateT<F> &s, const TSetT<F>
   prof_end(L, K_SWEEP_Y);
 }
 
-template <typename F>
-void launch_sweep_z(Launch &L, const Mesh &m, const F *vz, const TSetT<F> &in, const TSetT<F> &out, const double *dt) {
-  prof_begin(L, K_SWEEP_Z);
-  if (in.nq == 7) sweep_z_launch<F, 7>(L, m, vz, in, out, dt);
-  else sweep_z_launch<F, 6>(L, m, vz, in, out, dt);
-  prof_end(L, K_SWEEP_Z);
-}
-
 // Waves of 64 lanes, four per block; ceil(nx / U) waves per ring.
 template <typename F>
 void launch_ring_x(Launch &L, const Mesh &m, const F *vx2, const TSetT<F> &T, const TSetT<F> &Tout,
@@ -1053,12 +1008,8 @@ void launch_ring_x(Launch &L, const Mesh &m, const F *vx2, const TSetT<F> &T, co
   const long waves = (long)m.nring * nseg;
   const unsigned nb = (unsigned)((waves + 3) / 4);
   prof_begin(L, K_RING_X);
-  switch (T.nq) { // Pi-+_x, Pi-+_y [, Pi-+_z] [, e]
-  case 4: k_ring_x<F, 4><<<nb, 256, 0, L.s>>>(m, vx2, T, Tout, s, v0, dt, nseg); break;
-  case 5: k_ring_x<F, 5><<<nb, 256, 0, L.s>>>(m, vx2, T, Tout, s, v0, dt, nseg); break;
-  case 6: k_ring_x<F, 6><<<nb, 256, 0, L.s>>>(m, vx2, T, Tout, s, v0, dt, nseg); break;
-  default: k_ring_x<F, 7><<<nb, 256, 0, L.s>>>(m, vx2, T, Tout, s, v0, dt, nseg); break;
-  }
+  if (T.nq == 5) k_ring_x<F, 5><<<nb, 256, 0, L.s>>>(m, vx2, T, Tout, s, v0, dt, nseg); // Pi-+_x, Pi-+_y, e
+  else k_ring_x<F, 4><<<nb, 256, 0, L.s>>>(m, vx2, T, Tout, s, v0, dt, nseg);
   prof_end(L, K_RING_X);
 }
 
@@ -1066,7 +1017,7 @@ void launch_ring_x(Launch &L, const Mesh &m, const F *vx2, const TSetT<F> &T, co
 template <typename F>
 void launch_zx(Launch &L, const Mesh &m0, const F *vx2, const F *vz, const TSetT<F> &T, const TSetT<F> &Tout,
                const StateT<F> &s, const double *v0, const double *dt) {
-  constexpr int U = RingLane<F, 2>::U;
+  constexpr int U = RingLane<F, zx_m<F>()>::U;
   static const long slots[2] = {4 * block_slots(k_zx<F, 6>, 256), 4 * block_slots(k_zx<F, 7>, 256)};
   int nkc;
   const int nseg = (m0.nx + U - 1) / U;
@@ -1271,15 +1222,13 @@ FARGO_TRANSPORT_MANY(float)
 
 #define FARGO_TRANSPORT_INST(F)                                                                                    \
   template void launch_sweep_y<F>(Launch &, const Mesh &, const StateT<F> &, const TSetT<F> &, const double *);   \
-  template void launch_sweep_z<F>(Launch &, const Mesh &, const F *, const TSetT<F> &, const TSetT<F> &,         \
-                                  const double *);                                                               \
   template void launch_ring_x<F>(Launch &, const Mesh &, const F *, const TSetT<F> &, const TSetT<F> &,         \
                                  const StateT<F> &, const double *, const double *);                             \
+  template void launch_zx<F>(Launch &, const Mesh &, const F *, const F *, const TSetT<F> &, const TSetT<F> &,    \
+                             const StateT<F> &, const double *, const double *);                                  \
   template void launch_vel<F>(Launch &, const Mesh &, const StateT<F> &, const TSetT<F> &);
 FARGO_TRANSPORT_INST(double)
 FARGO_TRANSPORT_INST(float)
 #undef FARGO_TRANSPORT_INST
-template void launch_zx<float>(Launch &, const Mesh &, const float *, const float *, const TSetT<float> &,
-                               const TSetT<float> &, const StateT<float> &, const double *, const double *);
 
 } // namespace fargo

@@ -87,6 +87,19 @@ def test_ring_segments_and_windows(nx, turn, precision):
     assert _step(prob) <= (1e-12 if precision == "fp64" else 2e-6)
 
 
+@pytest.mark.parametrize("geo,eos", [("cyl", "iso"), ("sph", "adi"), ("cart", "adi")])
+@pytest.mark.parametrize("nx,turn", [(5, 0.3), (52, -3.0), (53, 3.0), (54, 0.0), (63, -0.4), (64, 20.0), (65, -20.0),
+                                     (106, 1.0), (107, -1.0)])
+def test_fused_z_x_pass_fp64(geo, eos, nx, turn):
+    """The fused Z/X pass where a ring is one zone around a wave's 53 zones, two such segments and its window of 64."""
+    print("fused z/x pass", geo, eos, nx, turn, flush=True)
+    prob = W.random_problem(geo, nx=nx, ny=5, nz=7, eos=eos, seed=nx, fargo=geo != "cart",
+                            bc=SIDES["periodic" if geo == "cart" else "reflect"])
+    if geo != "cart":
+        prob.fields["vx"] += turn
+    assert _step(prob) <= 1e-12
+
+
 @pytest.mark.parametrize("nx,ny,nz,eos,v0", [(1, 2100, 1, "adi", "minmax"), (2, 700, 3, "iso", "minmax"),
                                               (127, 2048, 1, "iso", "mean"), (129, 300, 7, "adi", "minmax"),
                                               (641, 1100, 2 + 1, "iso", "mean"), (1281, 12, 1, "adi", "mean"),
