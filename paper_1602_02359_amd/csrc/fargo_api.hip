@@ -928,7 +928,7 @@ int batch_capture(fargo_batch *b, int lanes) {
 size_t field_bytes(const fargo_ctx *c) { return (size_t)c->m.pitch * c->m.nyg * c->m.nzg * c->esize; }
 
 // ---- fused mode ----
-enum { FU_CFL, FU_DT, FU_SRC, FU_SRCG, FU_VISC, FU_SY, FU_RX, FU_VEL, FU_N };
+enum { FU_CFL, FU_DT, FU_SRC, FU_VISC, FU_SY, FU_RX, FU_VEL, FU_N };
 
 bool fused_ok(fargo_ctx *const *c, int n) {
   const fargo_params &p0 = c[0]->p;
@@ -968,29 +968,33 @@ int fused_build(fargo_batch *b) {
   // argument blocks packed at their exact size: the kernels index them so
   H[FU_CFL].asz = cfl_args_bytes<F>();
   H[FU_DT].asz = dt_final_args_bytes();
-  H[FU_SRC].asz = H[FU_SRCG].asz = source_args_bytes<F>();
+  H[FU_SRC].asz = source_args_bytes<F>();
   H[FU_VISC].asz = visc_args_bytes<F>();
   H[FU_SY].asz = sweep_y_args_bytes<F>();
   H[FU_RX].asz = ring_x_args_bytes<F>();
   H[FU_VEL].asz = vel_args_bytes<F>();
   b->nxmax = 0;
+  // shorter chunks where the batch leaves the chip idle
+  std::vector<Mesh> ms;
+  for (fargo_ctx *c : b->ctx) ms.push_back(c->m);
+  const int rows_src = source_rows<F>(ms), rows_visc = visc_rows<F>(ms);
+  const int rows_sweep = sweep_y_rows<F>(ms, *std::max_element(b->chunk.begin(), b->chunk.end()));
   for (unsigned d = 0; d < n; d++) {
     fargo_ctx *c = b->ctx[d];
     Mesh m = c->m;
-    m.chunk = b->chunk[d];
+    m.chunk = std::min(b->chunk[d], rows_sweep);
     b->nxmax = std::max(b->nxmax, m.nx);
     const StateT<F> S = state_of<F>(c, &b->st[d]);
     const double *dtp = c->w.dt;
     F *v2[4] = {(F *)c->v2[0], (F *)c->v2[1], (F *)c->v2[2], (F *)c->v2[3]};
     H[FU_CFL].blocks(d, cfl_args<F>(m, S, c->v0, c->ringrate, c->ringshear, c->w.err, H[FU_CFL].slot(d)));
     H[FU_DT].blocks(d, dt_final_args(m, c->w, c->ringrate, c->ringshear, H[FU_DT].slot(d)));
-    H[FU_SRC].blocks(d, source_args<F>(m, S, c->w, v2[0], v2[1], v2[2], v2[3], H[FU_SRC].slot(d)));
-    H[FU_SRCG].blocks(d, source_ghosts_args<F>(m, S, v2[0], v2[1], v2[2], v2[3], H[FU_SRCG].slot(d)));
+    H[FU_SRC].blocks(d, source_args<F>(m, S, c->w, v2[0], v2[1], v2[3], rows_src, H[FU_SRC].slot(d)));
     StateT<F> P = S; // post-source fields, as in the step
     P.vx = v2[0];
     P.vy = v2[1];
     if (m.visc) {
-      H[FU_VISC].blocks(d, visc_args<F>(m, S, v2[0], v2[1], (F *)c->v3[0], (F *)c->v3[1], dtp, H[FU_VISC].slot(d)));
+      H[FU_VISC].blocks(d, visc_args<F>(m, S, v2[0], v2[1], (F *)c->v3[0], (F *)c->v3[1], dtp, rows_visc, H[FU_VISC].slot(d)));
       P.vx = (F *)c->v3[0];
       P.vy = (F *)c->v3[1];
     }
@@ -1033,7 +1037,7 @@ void fused_step(fargo_batch *b, Launch &L) {
   const Mesh &m0 = b->ctx[0]->m;
   launch_cfl_many<F>(L, m0, b->g[FU_CFL], b->nxmax);                               // boxes 3, 4, 6
   launch_dt_final_many(L, b->g[FU_DT]);
-  launch_source_many<F>(L, m0, b->g[FU_SRC], b->g[FU_SRCG]);                        // boxes 7a-7c
+  launch_source_many<F>(L, m0, b->g[FU_SRC]);                        // boxes 7a-7c
   if (m0.visc) launch_visc_many<F>(L, b->g[FU_VISC]);                              // box 7d
   launch_sweep_y_many<F>(L, m0, b->g[FU_SY]);                                       // boxes 12a-c, Y
   launch_ring_x_many<F>(L, b->ctx[0]->nq, b->g[FU_RX]);                              // X, split, FARGO, 12d

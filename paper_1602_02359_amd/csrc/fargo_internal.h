@@ -8,6 +8,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <vector>
+
 #include "../../include/fargo.h"
 
 namespace fargo {
@@ -274,6 +276,26 @@ inline int fill_chunks(int n, int most, int least, long each, long slots, int ov
       best = k;
     }
     if (k == hi) break;
+  }
+  return best;
+}
+// The same for one launch over the 2D meshes of a batch: the chunk length, at
+// most `most`, with `segs(m)` workers per chunk of mesh m.
+template <class SEGS>
+int fill_chunk_length(const std::vector<Mesh> &ms, int most, long slots, int over, const SEGS &segs) {
+  int longest = 1;
+  for (const Mesh &m : ms) longest = m.ny > longest ? m.ny : longest;
+  most = most < longest ? most : longest;
+  int best = most;
+  long cost = 0;
+  for (int len = most; len >= 1; len--) {
+    long n = 0;
+    for (const Mesh &m : ms) n += (long)segs(m) * ((m.ny + len - 1) / len);
+    const long c = ((n - 1) / slots + 1) * (len + over);
+    if (len == most || c < cost) {
+      cost = c;
+      best = len;
+    }
   }
   return best;
 }
@@ -552,20 +574,24 @@ void launch_dt_final_many(Launch &L, const ManyGrid &g);
 template <typename F>
 size_t source_args_bytes();
 template <typename F>
-unsigned source_args(const Mesh &m, const StateT<F> &s, const DevWords &w, F *vx2, F *vy2, F *vz2, F *e2, void *dst);
+int source_rows(const std::vector<Mesh> &ms); // rows of a chunk in the launch over a batch's meshes
 template <typename F>
-unsigned source_ghosts_args(const Mesh &m, const StateT<F> &s, F *vx2, F *vy2, F *vz2, F *e2, void *dst);
+unsigned source_args(const Mesh &m, const StateT<F> &s, const DevWords &w, F *vx2, F *vy2, F *e2, int rows, void *dst);
 template <typename F>
-void launch_source_many(Launch &L, const Mesh &m0, const ManyGrid &g, const ManyGrid &ghosts);
+void launch_source_many(Launch &L, const Mesh &m0, const ManyGrid &g);
 template <typename F>
 size_t visc_args_bytes();
 template <typename F>
+int visc_rows(const std::vector<Mesh> &ms);
+template <typename F>
 unsigned visc_args(const Mesh &m, const StateT<F> &s, const F *vx2, const F *vy2, F *vx3, F *vy3, const double *dt,
-                   void *dst);
+                   int rows, void *dst);
 template <typename F>
 void launch_visc_many(Launch &L, const ManyGrid &g);
 template <typename F>
 size_t sweep_y_args_bytes();
+template <typename F>
+int sweep_y_rows(const std::vector<Mesh> &ms, int most);
 template <typename F>
 unsigned sweep_y_args(const Mesh &m, const StateT<F> &s, const TSetT<F> &out, const double *dt, void *dst);
 template <typename F>

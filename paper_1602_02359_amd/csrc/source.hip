@@ -13,8 +13,8 @@
 // a periodic direction); faces that are not owned keep v^n.  Results go to
 // separate arrays (v'', e''), so the pass reads the state while it writes.
 //
-// Layout of the work: a workgroup takes a tile of TX x TY zones of one (X, Y)
-// plane and marches through the Z planes.  For each plane the tile and a halo
+// Layout of the work on 3D meshes (2D meshes: k_source2): a workgroup takes a
+// tile of TX x TY zones of one (X, Y) plane and marches through the Z planes.  For each plane the tile and a halo
 // of two zones in X and Y are staged in LDS; the v' of every X and Y face of
 // the tile (and of the halo faces its stencil needs) is computed once and
 // kept in LDS (with the reciprocal of its density sum where room is left),
@@ -43,30 +43,29 @@ constexpr int TX = 64, SX = TX + 4; // tile width, with two halo zones on each s
 // Tile height (one wave per tile row).  The Y halo of a tile is read once per
 // tile, so taller tiles read less of it.  The FP64 3D march takes 16 rows
 // (1024 threads, at most 128 registers a thread), or 12 where the spherical or
-// adiabatic terms need more registers; FP32 marches and 2D meshes take 8
-// (two workgroups per compute unit; the FP32 march measured slower with
-// taller tiles).
-template <typename F, bool D3, int GEO, bool ADI>
+// adiabatic terms need more registers; FP32 marches take 8 (two workgroups per
+// compute unit; measured slower with taller tiles).
+template <typename F, int GEO, bool ADI>
 constexpr int tile_rows() {
-  if (!D3 || sizeof(F) == 4) return 8;
+  if (sizeof(F) == 4) return 8;
   return ADI || GEO == FARGO_SPHERICAL ? 12 : 16;
 }
-template <typename F, bool D3, int GEO, bool ADI>
-constexpr int src_threads() { return 64 * tile_rows<F, D3, GEO, ADI>(); }
+template <typename F, int GEO, bool ADI>
+constexpr int src_threads() { return 64 * tile_rows<F, GEO, ADI>(); }
 // minimum waves per SIMD: one workgroup of the FP64 march per compute unit,
 // at least four waves of the others
-template <typename F, bool D3, int GEO, bool ADI>
+template <typename F, int GEO, bool ADI>
 constexpr int src_waves() {
-  return sizeof(F) == 8 && D3 ? src_threads<F, D3, GEO, ADI>() / 256 : 4;
+  return sizeof(F) == 8 ? src_threads<F, GEO, ADI>() / 256 : 4;
 }
 
 template <typename F>
 __device__ inline F qvisc(F c2, F rho, F dv) { return dv < F(0) ? c2 * rho * dv * dv : F(0); }
 
-template <typename F, int TY, int NB, bool SPH, bool KI>
+template <typename F, int TY, bool SPH, bool KI>
 struct Lds {
-  // staging of a plane (NB planes in flight; density NB + 1 when NB > 1)
-  static constexpr int SY = TY + 4, NR = NB > 1 ? NB + 1 : 1;
+  // staging of a plane (NB planes in flight; density one more)
+  static constexpr int SY = TY + 4, NB = 2, NR = NB + 1;
   F R[NR][SY][SX];      // density
   F P[NB][SY][SX];      // pressure
   double Ph[NB][SY][SX]; // potential (FP64 in every mode)
@@ -80,13 +79,11 @@ struct Lds {
   F IY[KI ? NB : 1][KI ? SY : 1][KI ? TX : 1]; // KI: 1 / ((rho_j + rho_{j-1}) h_y) on the Y faces
   double DX[NB][TY];    // 1 / dX of the tile rows, for the halo X faces
 };
-// (a 2D mesh has a single plane: one buffer of each, so that several
-// workgroups share a compute unit)
 constexpr size_t LDS_CU = 160 * 1024;
 // the reciprocals of the faces' density sums are kept in LDS where they fit
 // beside the rest, else formed again by the zones that use them
-template <typename F, int TY, int NB, bool SPH>
-constexpr bool keep_inv() { return sizeof(Lds<F, TY, NB, SPH, true>) <= LDS_CU; }
+template <typename F, int TY, bool SPH>
+constexpr bool keep_inv() { return sizeof(Lds<F, TY, SPH, true>) <= LDS_CU; }
 
 // An explicit register move.  The march keeps a window of plane records in
 // registers and rotates it once per plane; moving the newest record out of its
@@ -122,11 +119,14 @@ struct Zv {
 // 9 fills the others), and next to the Y sides those that box 7d reads first.
 // Y ghost rows of planes [ka, kb) (extended over FIXED Z sides), then the Z
 // ghost planes of rows [jt, jt + h); y0, y1: whether the Y sides belong to it.
+__host__ __device__ inline bool ghost_rows(const Mesh &m, int side) { // of a Y side
+  return m.visc || m.bc[side] == FARGO_BC_FIXED;
+}
 struct GhostRows {
   int jn, kn, nyl, nyr, nzl, nzr, kl, nk;
   __host__ __device__ GhostRows(const Mesh &m, bool y0, bool y1, int ka, int kb) : jn(m.jn), kn(m.kn) {
-    nyl = y0 && (m.visc || m.bc[0] == FARGO_BC_FIXED) ? NGH : 0;
-    nyr = nyl + (y1 && (m.visc || m.bc[1] == FARGO_BC_FIXED) ? NGH : 0);
+    nyl = y0 && ghost_rows(m, 0) ? NGH : 0;
+    nyr = nyl + (y1 && ghost_rows(m, 1) ? NGH : 0);
     nzl = m.d3 && ka == m.k0 && m.bc[2] == FARGO_BC_FIXED ? NGH : 0;
     nzr = nzl + (m.d3 && kb == m.kn && m.bc[3] == FARGO_BC_FIXED ? NGH : 0);
     kl = ka - nzl;
@@ -162,14 +162,13 @@ __device__ inline void carry_ghost(const StateT<F> &s, unsigned o, F *__restrict
 // plane costs one barrier and the three phases overlap.
 // The geometry and the equation of state are template parameters: fewer
 // run-time conditions leave more scalar registers for the march.
-template <typename F, bool D3, int GEO, bool ADI>
-__device__ __forceinline__ void source_body(Mesh m, StateT<F> s, DtIn in, DevWords dw,
-                                                  F *__restrict__ vx2, F *__restrict__ vy2, F *__restrict__ vz2,
+template <typename F, int GEO, bool ADI>
+__device__ __forceinline__ void source_body(Mesh m, StateT<F> s, DevWords dw, F *__restrict__ vx2, F *__restrict__ vy2, F *__restrict__ vz2,
                                                   F *__restrict__ e2, int nbx, int nby, int zlen, int ghosts,
                                                   unsigned bid_, unsigned nbk_) {
-  constexpr int TY = tile_rows<F, D3, GEO, ADI>(), NB = D3 ? 2 : 1;
-  constexpr bool KI = keep_inv<F, TY, NB, GEO == FARGO_SPHERICAL>();
-  __shared__ Lds<F, TY, NB, GEO == FARGO_SPHERICAL, KI> L;
+  constexpr int TY = tile_rows<F, GEO, ADI>();
+  constexpr bool KI = keep_inv<F, TY, GEO == FARGO_SPHERICAL>();
+  __shared__ Lds<F, TY, GEO == FARGO_SPHERICAL, KI> L;
   static_assert(sizeof(L) <= LDS_CU, "source step tile exceeds the LDS of a compute unit");
   // the row is the wave index: uniform, so that geometric factors of the
   // row come through scalar loads, which do not stall behind the prefetches
@@ -180,49 +179,22 @@ __device__ __forceinline__ void source_body(Mesh m, StateT<F> s, DtIn in, DevWor
   // reads (each a 128-byte line of its neighbour's row) are mostly a running
   // neighbour's own, still in L2 (2.60 to 2.36 ms on the 2048 x 768 x 96 disk).
   // The FP32 march (two workgroups per compute unit) takes groups of 4 as well:
-  // 29 % fewer bytes fetched, about as fast.  The 12-row spherical march and
-  // 2D meshes keep Y fastest over the whole mesh (G = nby), which measured
-  // faster for the former.
-  const int G = TY == 16 || (D3 && sizeof(F) == 4) ? 4 : nby;
+  // 29 % fewer bytes fetched, about as fast.  The 12-row march keeps Y fastest
+  // over the whole mesh (G = nby), which measured faster.
+  const int G = TY == 16 || sizeof(F) == 4 ? 4 : nby;
   const unsigned Lc = xcd_remap(bid_, nbk_), ntile = (unsigned)(nbx * nby), gsz = (unsigned)(G * nbx);
-  const unsigned zc = D3 ? Lc / ntile : 0u, Lb = D3 ? Lc % ntile : Lc;
+  const unsigned zc = Lc / ntile, Lb = Lc % ntile;
   const unsigned grp = Lb / gsz, idx = Lb % gsz, gy = (unsigned)min(G, nby - (int)grp * G);
   const int ty = (int)(grp * (unsigned)G + idx % gy), tx = (int)(idx / gy);
   const int i0 = tx * TX, jt0 = m.j0 + ty * TY;
   // the workgroup's active planes
-  const int k0_ = D3 ? m.k0 + (int)zc * zlen : 0, kn_ = D3 ? min(k0_ + zlen, m.kn) : 1;
+  const int k0 = m.k0 + (int)zc * zlen, kn = min(k0 + zlen, m.kn);
   const int w = min(TX, m.nx - i0), h = min(TY, m.jn - jt0);
   const bool act = r < h && c < w;
   const int i = i0 + c, j = jt0 + r;
   constexpr bool adi = ADI;
   constexpr bool sph = GEO == FARGO_SPHERICAL, cyl = GEO == FARGO_CYLINDRICAL;
-  // dt: the device word, or, on 2D meshes of few rings, formed here from the
-  // time-step pass's slots by the first wave of every workgroup, which saves a
-  // launch of one workgroup (DT_SLOTS); the first workgroup leaves it in the
-  // word for the kernels that follow
-  __shared__ double dt_sh;
-  const bool slots = !D3 && in.nslot > 0;
-  F dt = slots ? F(0) : vreg((F)*dw.dt);
-  auto form_dt = [&]() {
-    if (!slots || r != 0) return;
-    const DtSlots sl = dt_slots(m, in);
-    double rmax, smax;
-    slot_extremes(sl, c, WAVE, rmax, smax);
-    rmax = lane63(wave_reduce_dpp(rmax, Max(), 0.0));
-    smax = lane63(wave_reduce_dpp(smax, Max(), 0.0));
-    bool bad;
-    const double d = dt_of_extremes(sl, rmax, smax, &bad);
-    if (c == 0) {
-      dt_sh = d;
-      if (bid_ == 0) {
-        if (bad) atomicOr(dw.err, 2);
-        *dw.dt = d;
-      }
-    }
-  };
-  auto take_dt = [&]() { // after a barrier
-    if (slots) dt = vreg((F)dt_sh);
-  };
+  const F dt = vreg((F)*dw.dt);
   const F c2 = vreg((F)(m.cvnr * m.cvnr)), om = vreg((F)m.omega), gm1 = vreg((F)(m.gamma - 1.0));
   const unsigned plane = (unsigned)m.plane();
   // geometric factors of the thread's row (the products with the plane
@@ -255,7 +227,7 @@ __device__ __forceinline__ void source_body(Mesh m, StateT<F> s, DtIn in, DevWor
     z.rho = s.rho[o];
     z.q = adi ? s.e[o] : s.cs[o];
     z.pot = s.pot[o];
-    z.vz = D3 ? s.vz[o] : F(0);
+    z.vz = s.vz[o];
     z.vx = s.vx[o];
     z.vxp = sph ? s.vx[o - (unsigned)i + (unsigned)ip] : F(0);
   };
@@ -336,7 +308,7 @@ __device__ __forceinline__ void source_body(Mesh m, StateT<F> s, DtIn in, DevWor
       }
       if (hvy) n.hy = s.vy[o];
       if (hvt) {
-        const int kp = D3 ? m.kabove(kk) : kk;
+        const int kp = m.kabove(kk);
         n.ht0 = s.vz[o];
         n.ht1 = s.vz[o + (unsigned)(kp - kk) * plane];
       }
@@ -485,12 +457,10 @@ __device__ __forceinline__ void source_body(Mesh m, StateT<F> s, DtIn in, DevWor
     vy2[o] = by1;
     heat += qy * dvy * (F)g_invLy;
     flux += (F)(g_syj1 * syk) * by2 - (F)(g_syj * syk) * by1;
-    if (D3) {
-      vz2[o] = zp.bz1;
-      const F iLz = sph ? (F)(m.g.inv_dz(kk) * g_iymed) : (F)m.g.inv_dz(kk);
-      heat += zp.qz * zp.dvz * iLz;
-      flux += (F)(g_szj * m.g.szk(kk + 1)) * zp.bz2 - (F)(g_szj * m.g.szk(kk)) * zp.bz1;
-    }
+    vz2[o] = zp.bz1;
+    const F iLz = sph ? (F)(m.g.inv_dz(kk) * g_iymed) : (F)m.g.inv_dz(kk);
+    heat += zp.qz * zp.dvz * iLz;
+    flux += (F)(g_szj * m.g.szk(kk + 1)) * zp.bz2 - (F)(g_szj * m.g.szk(kk)) * zp.bz1;
     if (adi) {
       const F e1 = e_old - dt * heat;
       const F a = F(0.5) * dt * gm1 * ((F)(g_invVj / syk) * flux);
@@ -498,26 +468,7 @@ __device__ __forceinline__ void source_body(Mesh m, StateT<F> s, DtIn in, DevWor
     }
   };
 
-  if constexpr (!D3) {
-    // a single plane: S, F, Z in turn
-    form_dt();
-    Zv<F> z0{};
-    Halo hv{};
-    F e_old = F(0);
-    if (act) {
-      loadz(0, z0);
-      e_old = z0.q;
-    }
-    load_halo(0, hv);
-    stage(0, 0, 0, z0, F(0), hv);
-    __syncthreads();
-    take_dt();
-    faces(0, 0, 0);
-    __syncthreads();
-    if (act) zones(0, 0, 0, ZPart{}, e_old);
-  } else {
   // ---- 3D march over the workgroup's active planes k0 .. kn-1
-  const int k0 = k0_, kn = kn_;
   // Z window of the thread's column at the top of interval kk:
   //   Z1, Z2 = records of planes kk+1, kk+2; vzk = v_z of plane kk;
   //   A[0..2] = v'_z of faces kk .. kk+2, IZ likewise; Q[0..2] = q_z of
@@ -616,127 +567,403 @@ __device__ __forceinline__ void source_body(Mesh m, StateT<F> s, DtIn in, DevWor
     sb = sb1;
     rb = rb1;
   }
-  }
   if (!ghosts) return;
   // the ghost rows next to the tile's, a row of its columns per wave
-  const GhostRows G_(m, ty == 0, ty == nby - 1, k0_, kn_);
+  const GhostRows G_(m, ty == 0, ty == nby - 1, k0, kn);
   for (int t = r; t < G_.rows(jt0, h); t += TY) {
     int jg_, kg_;
     G_.row(t, jt0, h, jg_, kg_);
-    if (c < w) carry_ghost<F, D3, ADI>(s, m.o32(i, jg_, kg_), vx2, vy2, vz2, e2);
+    if (c < w) carry_ghost<F, true, ADI>(s, m.o32(i, jg_, kg_), vx2, vy2, vz2, e2);
   }
 }
-template <typename F, bool D3, int GEO, bool ADI>
-__global__ __launch_bounds__((src_threads<F, D3, GEO, ADI>()), (src_waves<F, D3, GEO, ADI>())) void k_source(
-    Mesh m, StateT<F> s, DtIn in, DevWords dw, F *__restrict__ vx2, F *__restrict__ vy2, F *__restrict__ vz2,
+template <typename F, int GEO, bool ADI>
+__global__ __launch_bounds__((src_threads<F, GEO, ADI>()), (src_waves<F, GEO, ADI>())) void k_source(
+    Mesh m, StateT<F> s, DevWords dw, F *__restrict__ vx2, F *__restrict__ vy2, F *__restrict__ vz2,
     F *__restrict__ e2, int nbx, int nby, int zlen, int ghosts) {
-  source_body<F, D3, GEO, ADI>(m, s, in, dw, vx2, vy2, vz2, e2, nbx, nby, zlen, ghosts, blockIdx.x, gridDim.x);
+  source_body<F, GEO, ADI>(m, s, dw, vx2, vy2, vz2, e2, nbx, nby, zlen, ghosts, blockIdx.x, gridDim.x);
 }
 
 // The ghost rows alone, one block per row.
-template <typename F, bool D3, bool ADI>
-__device__ __forceinline__ void source_ghosts_body(const Mesh &m, const StateT<F> &s, F *__restrict__ vx2,
-                                                   F *__restrict__ vy2, F *__restrict__ vz2, F *__restrict__ e2,
-                                                   unsigned bid_) {
-  const GhostRows G(m, true, true, m.k0, m.kn);
-  int j, k;
-  G.row((int)bid_, m.j0, m.ny, j, k);
-  for (int i = threadIdx.x; i < m.nx; i += blockDim.x) carry_ghost<F, D3, ADI>(s, m.o32(i, j, k), vx2, vy2, vz2, e2);
-}
-template <typename F, bool D3, bool ADI>
+template <typename F, bool ADI>
 __global__ __launch_bounds__(256) void k_source_ghosts(Mesh m, StateT<F> s, F *__restrict__ vx2, F *__restrict__ vy2,
                                                        F *__restrict__ vz2, F *__restrict__ e2) {
-  source_ghosts_body<F, D3, ADI>(m, s, vx2, vy2, vz2, e2, blockIdx.x);
+  const GhostRows G(m, true, true, m.k0, m.kn);
+  int j, k;
+  G.row((int)blockIdx.x, m.j0, m.ny, j, k);
+  for (int i = threadIdx.x; i < m.nx; i += blockDim.x) carry_ghost<F, true, ADI>(s, m.o32(i, j, k), vx2, vy2, vz2, e2);
 }
 
-// multi-mesh forms (ManyGrid)
-template <typename F>
-struct SourceArgs {
-  Mesh m;
-  StateT<F> s;
-  DevWords dw;
-  F *vx2, *vy2, *vz2, *e2;
-  int nbx, nby;
-  unsigned nb;
-};
-template <typename F, bool D3, int GEO, bool ADI>
-__global__ __launch_bounds__((src_threads<F, D3, GEO, ADI>()), (src_waves<F, D3, GEO, ADI>())) void k_source_many(
-    const void *args, const uint2 *tab) {
-  const uint2 t = many_block(tab);
-  if (t.x == MANY_NONE) return;
-  const SourceArgs<F> a = many_args<SourceArgs<F>>(args, t.x);
-  source_body<F, D3, GEO, ADI>(a.m, a.s, DtIn{}, a.dw, a.vx2, a.vy2, a.vz2, a.e2, a.nbx, a.nby, 1, 0, t.y, a.nb);
-}
-template <typename F, bool ADI>
-__global__ __launch_bounds__(256) void k_source_ghosts_many(const void *args, const uint2 *tab) {
-  const uint2 t = many_block(tab);
-  if (t.x == MANY_NONE) return;
-  const SourceArgs<F> a = many_args<SourceArgs<F>>(args, t.x);
-  source_ghosts_body<F, false, ADI>(a.m, a.s, a.vx2, a.vy2, a.vz2, a.e2, t.y);
-}
-// tile rows of the source step's launch on mesh m
+// tile rows of the source step's launch on a 3D mesh
 template <typename F>
 int src_rows(const Mesh &m) {
-  if (!m.d3) return tile_rows<F, false, FARGO_CARTESIAN, false>();
   const bool tall = m.geo != FARGO_SPHERICAL && m.eos != FARGO_ADIABATIC;
-  return tall ? tile_rows<F, true, FARGO_CARTESIAN, false>() : tile_rows<F, true, FARGO_SPHERICAL, true>();
+  return tall ? tile_rows<F, FARGO_CARTESIAN, false>() : tile_rows<F, FARGO_SPHERICAL, true>();
 }
 
-// workgroups of the source step that the chip holds at once
-template <typename F, bool D3, int GEO, bool ADI>
-long src_slots() {
-  int per_cu = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_source<F, D3, GEO, ADI>, src_threads<F, D3, GEO, ADI>(), 0) !=
-          hipSuccess ||
-      per_cu < 1)
-    per_cu = 1;
-  return (long)per_cu * CHIP_CUS;
+// ------------------------------------------------------------------------
+// 2D meshes.  A wave walks a chunk of rows outwards over 64 columns, one per
+// lane: neighbours along X come by DPP lane moves, the row below and the faces
+// and terms that the next rows need stay in registers, and each face is formed
+// once.  Two lanes below and one above (two with an energy, which takes the
+// upper X face's final velocity) are halo.  Nothing goes through LDS and no wave
+// waits for another; the loads of four rows are in flight.  Bound by memory on
+// large meshes: 3072 x 1024 zones in FP64 47 + 8 (LDS tiles of 64 x 8 zones and a
+// launch for the ghost rows) to 34.7 us, 5.1 TB/s of its 7 words a zone; the
+// batch of 256 disks in FP32 770 + 9 to 534 us (4.2 TB/s), of 48 in FP64 239 + 7
+// to 186; 633 x 211 zones 7.2 to 6.5, 384 x 128 6.1 to 5.5.
+// ------------------------------------------------------------------------
+template <typename F>
+struct Source2 {
+  Mesh m;
+  StateT<F> s;
+  DtIn in;
+  DevWords dw;
+  F *vx2, *vy2, *e2;
+  int nseg, chunk, nchunk; // segments of a row, rows of a chunk, chunks
+};
+template <bool ADI>
+constexpr int src2_cols() { return WAVE - (ADI ? 4 : 3); }
+// The most rows of a chunk (which reads three or four beside its own), of one
+// mesh and of the meshes of a batch.  One mesh: 32 rows, or as many chunks as
+// make whole rounds of one wave per SIMD (3072 x 1024: 34.7 us; at most 16 rows
+// 38; as many chunks as waves fit 38); 633 x 211: 6.5 us (twice the waves 7.0).
+// A batch of 256 disks in FP32, which fills the chip at any length: 534 us at 16
+// rows, 559 at 24, 573 at 32, 537 at 8.
+constexpr int SRC2_ROWS = 32, SRC2_MANY = 16;
+constexpr long SRC2_WAVES = 4L * CHIP_CUS;
+
+template <typename F, bool CYL, bool ADI>
+__device__ __forceinline__ void source2_body(const Source2<F> &A, unsigned bid_, unsigned nbk_) {
+// Contraction is off: the rows of a turn of the march are compiled apart, and
+// the same rounding in all keeps the result independent of the chunk length.
+#pragma clang fp contract(off)
+  const Mesh &m = A.m;
+  const int lane = threadIdx.x & (WAVE - 1);
+  // wave-uniform, so that the rows' constants come through scalar loads
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+  const int gw = (int)xcd_remap(bid_, nbk_) * (int)(blockDim.x / WAVE) + wave;
+  const int seg = gw % A.nseg, ch = gw / A.nseg;
+  const int a0 = m.j0 + ch * A.chunk, a1 = min(a0 + A.chunk, m.jn), n = m.nx;
+  const int z = seg * src2_cols<ADI>() + lane - 2;
+  const int i = n > 1 ? (z < 0 ? z + n : (z >= n ? z % n : z)) : 0;
+  const bool useful = lane >= 2 && lane < 2 + src2_cols<ADI>() && z < n;
+  // rows a0 - 2 .. last are read; past the last the read is of the last again
+  const int last = ADI ? a1 + 1 : a1;
+  auto yrow = [&](int t) {
+    int y = min(t, last);
+    if (m.yper()) y = y < m.j0 ? y + m.ny : (y >= m.jn ? y - m.ny : y);
+    return y;
+  };
+  struct Row {
+    F rho, q, vx, vy;
+    double pot;
+  };
+  auto ld = [&](int t, Row &w) {
+    const unsigned c = m.o32(i, yrow(t), 0);
+    w.rho = A.s.rho[c];
+    w.q = ADI ? A.s.e[c] : A.s.cs[c];
+    w.pot = A.s.pot[c];
+    w.vx = A.s.vx[c];
+    w.vy = A.s.vy[c];
+  };
+  Row W[4];
+  const bool live = ch < A.nchunk;
+  if (live) {
+#pragma unroll
+    for (int q = 0; q < 4; q++) ld(a0 - 2 + q, W[q]);
+  }
+  // dt: the device word, or, on meshes of few rings, formed here from the
+  // time-step pass's slots by the first wave of every workgroup, which saves a
+  // launch of one workgroup (DT_SLOTS); the first workgroup leaves it in the
+  // word for the kernels that follow
+  __shared__ double dt_sh;
+  F dt;
+  if (A.in.nslot > 0) {
+    if (wave == 0) {
+      const DtSlots sl = dt_slots(m, A.in);
+      // all slots read at once, the last one again past the end: a loop waits
+      // for memory up to four times (2 us)
+      constexpr int P = DT_SLOTS / WAVE;
+      double rr[P], ss[P], rmax = 0.0, smax = 0.0;
+#pragma unroll
+      for (int q = 0; q < P; q++) {
+        const int x = min(lane + q * WAVE, sl.nslot - 1);
+        rr[q] = sl.rate[x];
+        ss[q] = sl.shear[x];
+      }
+#pragma unroll
+      for (int q = 0; q < P; q++) {
+        rmax = rr[q] > rmax ? rr[q] : rmax;
+        smax = ss[q] > smax ? ss[q] : smax;
+      }
+      rmax = lane63(wave_reduce_dpp(rmax, Max(), 0.0));
+      smax = lane63(wave_reduce_dpp(smax, Max(), 0.0));
+      bool bad;
+      const double d = dt_of_extremes(sl, rmax, smax, &bad);
+      if (lane == 0) {
+        dt_sh = d;
+        if (bid_ == 0) {
+          if (bad) atomicOr(A.dw.err, 2);
+          *A.dw.dt = d;
+        }
+      }
+    }
+    __syncthreads();
+    dt = (F)dt_sh;
+  } else {
+    dt = (F)*A.dw.dt;
+  }
+  if (!live) return;
+  const F c2 = (F)(m.cvnr * m.cvnr), om = (F)m.omega, gm1 = (F)(m.gamma - 1.0), dt2 = dt * F(2);
+  const double syk = m.g.syk(0), sxk = m.g.sxk(0);
+  auto yowned = [&](int f) { return f >= m.ylo() && f < m.jn; };
+  auto pres = [&](F rho, F q) { return ADI ? gm1 * q : q * q * rho; };
+  // a row's constants, read a row ahead
+  struct Geo {
+    double ihd, idX, ymed, iymin, vb, cb;
+  };
+  auto geo = [&](int t) {
+    const int y = yrow(t);
+    Geo g{};
+    g.ihd = m.g.inv_hy(y);
+    g.idX = m.g.inv_dxlen((size_t)y);
+    if (CYL) {
+      g.iymin = m.g.inv_ymin(y);
+      if (sizeof(F) == 8) {
+        g.ymed = m.g.ymed(y);
+      } else {
+        g.vb = m.bg(BG_VT, y, 0);
+        g.cb = m.bg(BG_CY, y, 0);
+      }
+    }
+    return g;
+  };
+  // v_x of the zone's two X faces, summed, with the frame velocity in FP64
+  auto vsum = [&](F vx, const Geo &g) {
+    const F vxn = from_next_lane(vx);
+    if constexpr (CYL && sizeof(F) == 8) {
+      const F o = (F)g.ymed * om;
+      return (vx + o) + (vxn + o);
+    } else {
+      return vx + vxn;
+    }
+  };
+  Geo gn = geo(a0 - 1);
+  const Geo g0 = geo(a0 - 2);
+  // of the row below: density, pressure, potential, summed v_x, mean background,
+  // storage row
+  F rho_s = W[0].rho, p_s = pres(W[0].rho, W[0].q), vt_s = vsum(W[0].vx, g0);
+  double pot_s = W[0].pot, vb_s = g0.vb;
+  int y_s = yrow(a0 - 2);
+  // v'_y of its lower face, 1 / ((rho + rho below) h) there; q_y of the zone below it
+  F b_s = F(0), iy_s = F(0), q_s = F(0);
+  // ADI, [0] of the row below, [1] of the row two below: what X adds to heating
+  // and divergence, the energy; of the row two below: v''_y of its lower face,
+  // q_y and the velocity step of it
+  F hx[2] = {}, fx[2] = {}, eo[2] = {}, by_s = F(0), dv_s = F(0);
+  auto row = [&](int t, Row &w) {
+    const int y = yrow(t);
+    const F rho = w.rho, q = w.q, vx = w.vx, vy = w.vy;
+    const double pot = w.pot;
+    ld(t + 4, w);
+    const Geo g = gn;
+    gn = geo(t + 1);
+    const F p = pres(rho, q), vt = vsum(vx, g);
+    // Y: v' of the row's lower face, then 7b on the face below
+    const double ihd = g.ihd;
+    const F iy = (F)ihd / (rho + rho_s);
+    const F gradP = F(2) * (p - p_s) * iy;
+    F b;
+    if constexpr (CYL && sizeof(F) == 4) {
+      // an FP32 v_x is a deviation d from the ring's background: with W the
+      // mean background of the two rings, v^2 = W^2 + (2 W + d) d; the W^2
+      // part, which gravity cancels to order h^2 in a disk, is formed with
+      // the potential gradient in FP64 and rounded once
+      const F Wb = (F)(0.5 * (g.vb + vb_s)), d = F(0.25) * (vt + vt_s);
+      const F src = (F(2) * Wb + d) * d * (F)g.iymin + (F)(g.cb - (pot - pot_s) * ihd);
+      b = vy - dt * gradP + dt * src;
+    } else {
+      F acc = gradP + (F)((pot - pot_s) * ihd);
+      if constexpr (CYL) {
+        const F v = F(0.25) * (vt + vt_s);
+        acc = acc - v * v * (F)g.iymin;
+      }
+      b = vy - dt * acc;
+    }
+    if (!yowned(y)) b = vy;
+    const F dv = b - b_s, qy = qvisc(c2, rho_s, dv);
+    F by = b_s;
+    if (yowned(y_s)) by = b_s - dt2 * (qy - q_s) * iy_s;
+    if (t > a0 && t <= a1 && useful) A.vy2[m.o32(i, t - 1, 0)] = by;
+    // X: faces and zones of the row
+    F heat = F(0), flux = F(0);
+    if (t >= a0 && t < a1) {
+      const double idX = g.idX;
+      const F ix = (F)idX / (rho + from_prev_lane(rho));
+      const F gp = F(2) * (p - from_prev_lane(p)) * ix;
+      const F a = vx - dt * (gp + (F)((pot - from_prev_lane(pot)) * idX));
+      const F dvx = from_next_lane(a) - a, qx = qvisc(c2, rho, dvx);
+      const F bx = a - dt2 * (qx - from_prev_lane(qx)) * ix;
+      if (useful) A.vx2[m.o32(i, t, 0)] = bx;
+      if constexpr (ADI) {
+        heat = qx * dvx * (F)idX;
+        flux = (F)(m.g.sxj(y) * sxk) * (from_next_lane(bx) - bx);
+      }
+    }
+    if constexpr (ADI) {
+      // 7c of the row two below: [1] its X part, by_s and by its Y faces
+      if (t >= a0 + 2) {
+        const int j = t - 2;
+        const F ht = hx[1] + q_s * dv_s * (F)m.g.inv_Ly(j);
+        const F fl = fx[1] + ((F)(m.g.syj(j + 1) * syk) * by - (F)(m.g.syj(j) * syk) * by_s);
+        const F e1 = eo[1] - dt * ht;
+        const F al = F(0.5) * dt * gm1 * ((F)(m.g.invVj(j) / syk) * fl);
+        if (useful) A.e2[m.o32(i, j, 0)] = e1 * (F(1) - al) / (F(1) + al);
+      }
+      hx[1] = hx[0];
+      fx[1] = fx[0];
+      eo[1] = eo[0];
+      hx[0] = heat;
+      fx[0] = flux;
+      eo[0] = q;
+      by_s = by;
+      dv_s = dv;
+    }
+    rho_s = rho;
+    p_s = p;
+    vt_s = vt;
+    pot_s = pot;
+    y_s = y;
+    vb_s = g.vb;
+    b_s = b;
+    iy_s = iy;
+    q_s = qy;
+  };
+  ld(a0 + 2, W[0]);
+#pragma unroll 1
+  for (int t = a0 - 1; t <= last; t++) {
+    row(t, W[1]);
+    if (++t > last) break;
+    row(t, W[2]);
+    if (++t > last) break;
+    row(t, W[3]);
+    if (++t > last) break;
+    row(t, W[0]);
+  }
+  // the ghost rows that keep v^n and e, all read before the first is written
+  // (waves of their own for them, last in the launch, took 8 us longer on 3072 x
+  // 1024 zones)
+  auto carry = [&](int j0) {
+    F v[NGH][3];
+#pragma unroll
+    for (int g = 0; g < NGH; g++) {
+      const unsigned c = m.o32(i, j0 + g, 0);
+      v[g][0] = A.s.vx[c];
+      v[g][1] = A.s.vy[c];
+      v[g][2] = ADI ? A.s.e[c] : F(0);
+    }
+    if (!useful) return;
+#pragma unroll
+    for (int g = 0; g < NGH; g++) {
+      const unsigned c = m.o32(i, j0 + g, 0);
+      A.vx2[c] = v[g][0];
+      A.vy2[c] = v[g][1];
+      if (ADI) A.e2[c] = v[g][2];
+    }
+  };
+  if (ch == 0 && ghost_rows(m, 0)) carry(0);
+  if (ch == A.nchunk - 1 && ghost_rows(m, 1)) carry(m.jn);
+}
+template <typename F, bool CYL, bool ADI>
+__global__ __launch_bounds__(256) void k_source2(Source2<F> A) {
+  source2_body<F, CYL, ADI>(A, blockIdx.x, gridDim.x);
+}
+
+// multi-mesh form (ManyGrid)
+template <typename F>
+struct Source2Args {
+  Source2<F> A;
+  unsigned nb, pad_;
+};
+template <typename F, bool CYL, bool ADI>
+__global__ __launch_bounds__(256) void k_source2_many(const void *args, const uint2 *tab) {
+  const uint2 t = many_block(tab);
+  if (t.x == MANY_NONE) return;
+  const Source2Args<F> a = many_args<Source2Args<F>>(args, t.x);
+  source2_body<F, CYL, ADI>(a.A, t.y, a.nb);
+}
+
+inline int src2_segs(const Mesh &m) {
+  const int u = m.eos == FARGO_ADIABATIC ? src2_cols<true>() : src2_cols<false>();
+  return (m.nx + u - 1) / u;
+}
+// the step over 2D mesh m with chunks of at most `rows` rows, more to share out
+// over `slots` waves (0: as they are), and its blocks
+template <typename F>
+Source2<F> source2_of(const Mesh &m, const StateT<F> &s, const DtIn &in, const DevWords &w, F *vx2, F *vy2, F *e2,
+                      long slots, int rows, unsigned &nb) {
+  Source2<F> A{m, s, in, w, vx2, vy2, e2, src2_segs(m), 0, 0};
+  const int nch = slots ? fill_chunks(m.ny, rows, 1, A.nseg, slots, 4) : (m.ny + rows - 1) / rows;
+  A.chunk = (m.ny + nch - 1) / nch;
+  A.nchunk = (m.ny + A.chunk - 1) / A.chunk;
+  nb = (unsigned)(((long)A.nseg * A.nchunk + 3) / 4);
+  return A;
+}
+
+// go(cylindrical, adiabatic) with the compile-time constants of 2D mesh m
+template <class GO>
+void source2_form(const Mesh &m, const GO &go) {
+  const bool cyl = m.geo == FARGO_CYLINDRICAL;
+  if (m.eos == FARGO_ADIABATIC) {
+    if (cyl) go(std::true_type{}, std::true_type{});
+    else go(std::false_type{}, std::true_type{});
+  } else {
+    if (cyl) go(std::true_type{}, std::false_type{});
+    else go(std::false_type{}, std::false_type{});
+  }
 }
 } // namespace
 
 template <typename F>
 void launch_source(Launch &L, const Mesh &m, const StateT<F> &s, const DtIn &in, const DevWords &w, F *vx2, F *vy2,
                    F *vz2, F *e2) {
-  const int nbx = (m.nx + TX - 1) / TX, nby = (m.ny + src_rows<F>(m) - 1) / src_rows<F>(m);
   prof_begin(L, K_SRC);
-  auto go = [&](auto d3, auto geo, auto adi) {
-    constexpr bool D3 = decltype(d3)::value, ADI = decltype(adi)::value;
+  const int nbx = (m.nx + TX - 1) / TX, nby = (m.ny + src_rows<F>(m) - 1) / src_rows<F>(m);
+  auto go2 = [&](auto cyl, auto adi) {
+    unsigned nb;
+    const Source2<F> A = source2_of(m, s, in, w, vx2, vy2, e2, SRC2_WAVES, SRC2_ROWS, nb);
+    k_source2<F, decltype(cyl)::value, decltype(adi)::value><<<nb, 256, 0, L.s>>>(A);
+  };
+  auto go = [&](auto geo, auto adi) {
+    constexpr bool ADI = decltype(adi)::value;
     constexpr int GEO = decltype(geo)::value;
-    int zlen = 1;
-    unsigned nb = (unsigned)nbx * (unsigned)nby;
     const int ng = GhostRows(m, true, true, m.k0, m.kn).rows(m.j0, m.ny);
-    if constexpr (D3) {
-      // the march in chunks of planes where the tiles alone leave compute units
-      // idle, or a last round of workgroups nearly empty (a chunk reads five
-      // planes beside its own).  Box of 160 x 144 x 120 zones, 36 tiles: 311
-      // to 64 us; 501 x 167 x 43 FP32 spherical, 168 tiles on 512 slots: 147
-      // to 67 us; 1536 x 512 x 128, 1032 tiles on 256 slots: 2.52 to 2.42 ms;
-      // 2048 x 768 x 96, 1536 tiles: unchanged.
-      static const long slots = src_slots<F, D3, GEO, ADI>();
-      const int nzc = fill_chunks(m.nz, m.nz, 4, (long)nb, slots, 4);
-      zlen = (m.nz + nzc - 1) / nzc;
-      nb *= (unsigned)((m.nz + zlen - 1) / zlen);
-    }
+    // the march in chunks of planes where the tiles alone leave compute units
+    // idle, or a last round of workgroups nearly empty (a chunk reads five
+    // planes beside its own).  Box of 160 x 144 x 120 zones, 36 tiles: 311
+    // to 64 us; 501 x 167 x 43 FP32 spherical, 168 tiles on 512 slots: 147
+    // to 67 us; 1536 x 512 x 128, 1032 tiles on 256 slots: 2.52 to 2.42 ms;
+    // 2048 x 768 x 96, 1536 tiles: unchanged.
+    static const long slots = block_slots(k_source<F, GEO, ADI>, src_threads<F, GEO, ADI>());
+    unsigned nb = (unsigned)nbx * (unsigned)nby;
+    const int nzc = fill_chunks(m.nz, m.nz, 4, (long)nb, slots, 4);
+    const int zlen = (m.nz + nzc - 1) / nzc;
+    nb *= (unsigned)((m.nz + zlen - 1) / zlen);
     // The tiles at a side take its ghost rows along where a launch costs more
-    // than the tail they add (633 x 211, 270 tiles: 1 against 4 us alone; the
-    // batch of 256 disks 40 against 9; 2048 x 768 x 96, 1536 tiles, 69 against
-    // 14 us)
+    // than the tail they add (2048 x 768 x 96, 1536 tiles: 69 us against 14 alone)
     const bool here = nb <= 2 * CHIP_CUS;
-    k_source<F, D3, GEO, ADI><<<nb, src_threads<F, D3, GEO, ADI>(), 0, L.s>>>(m, s, in, w, vx2, vy2, vz2, e2, nbx, nby,
-                                                                              zlen, here ? 1 : 0);
-    if (!here && ng > 0) k_source_ghosts<F, D3, ADI><<<(unsigned)ng, 256, 0, L.s>>>(m, s, vx2, vy2, vz2, e2);
+    k_source<F, GEO, ADI><<<nb, src_threads<F, GEO, ADI>(), 0, L.s>>>(m, s, w, vx2, vy2, vz2, e2, nbx, nby, zlen,
+                                                                      here ? 1 : 0);
+    if (!here && ng > 0) k_source_ghosts<F, ADI><<<(unsigned)ng, 256, 0, L.s>>>(m, s, vx2, vy2, vz2, e2);
   };
-  auto by_eos = [&](auto d3, auto geo) {
-    if (m.eos == FARGO_ADIABATIC) go(d3, geo, std::true_type{});
-    else go(d3, geo, std::false_type{});
+  auto by_eos = [&](auto geo) {
+    if (m.eos == FARGO_ADIABATIC) go(geo, std::true_type{});
+    else go(geo, std::false_type{});
   };
-  auto by_geo = [&](auto d3) {
-    if (m.geo == FARGO_SPHERICAL) by_eos(d3, std::integral_constant<int, FARGO_SPHERICAL>{});
-    else if (m.geo == FARGO_CYLINDRICAL) by_eos(d3, std::integral_constant<int, FARGO_CYLINDRICAL>{});
-    else by_eos(d3, std::integral_constant<int, FARGO_CARTESIAN>{});
-  };
-  if (m.d3) by_geo(std::true_type{});
-  else by_geo(std::false_type{});
+  if (!m.d3) source2_form(m, go2);
+  else if (m.geo == FARGO_SPHERICAL) by_eos(std::integral_constant<int, FARGO_SPHERICAL>{});
+  else if (m.geo == FARGO_CYLINDRICAL) by_eos(std::integral_constant<int, FARGO_CYLINDRICAL>{});
+  else by_eos(std::integral_constant<int, FARGO_CARTESIAN>{});
   prof_end(L, K_SRC);
 }
 
@@ -746,47 +973,36 @@ template void launch_source<float>(Launch &, const Mesh &, const StateT<float> &
                                    float *, float *, float *, float *);
 
 template <typename F>
-size_t source_args_bytes() { return sizeof(SourceArgs<F>); }
+size_t source_args_bytes() { return sizeof(Source2Args<F>); }
 
 template <typename F>
-unsigned source_args(const Mesh &m, const StateT<F> &s, const DevWords &w, F *vx2, F *vy2, F *vz2, F *e2, void *dst) {
-  const int nbx = (m.nx + TX - 1) / TX, nby = (m.ny + src_rows<F>(m) - 1) / src_rows<F>(m);
-  const unsigned nb = (unsigned)nbx * (unsigned)nby;
-  *(SourceArgs<F> *)dst = SourceArgs<F>{m, s, w, vx2, vy2, vz2, e2, nbx, nby, nb};
-  return nb;
+int source_rows(const std::vector<Mesh> &ms) {
+  return fill_chunk_length(ms, SRC2_MANY, SRC2_WAVES, 4, [](const Mesh &m) { return src2_segs(m); });
 }
 
 template <typename F>
-unsigned source_ghosts_args(const Mesh &m, const StateT<F> &s, F *vx2, F *vy2, F *vz2, F *e2, void *dst) {
-  const unsigned ng = (unsigned)GhostRows(m, true, true, m.k0, m.kn).rows(m.j0, m.ny);
-  *(SourceArgs<F> *)dst = SourceArgs<F>{m, s, DevWords{}, vx2, vy2, vz2, e2, 0, 0, ng};
-  return ng;
+unsigned source_args(const Mesh &m, const StateT<F> &s, const DevWords &w, F *vx2, F *vy2, F *e2, int rows, void *dst) {
+  unsigned nb;
+  const Source2<F> A = source2_of(m, s, DtIn{}, w, vx2, vy2, e2, 0L, rows, nb);
+  *(Source2Args<F> *)dst = Source2Args<F>{A, nb, 0};
+  return nb;
 }
 
 // 2D meshes of one geometry and equation of state (those of m0)
 template <typename F>
-void launch_source_many(Launch &L, const Mesh &m0, const ManyGrid &g, const ManyGrid &ghosts) {
+void launch_source_many(Launch &L, const Mesh &m0, const ManyGrid &g) {
   prof_begin(L, K_SRC);
-  auto go = [&](auto geo, auto adi) {
-    k_source_many<F, false, decltype(geo)::value, decltype(adi)::value><<<g.nblk, src_threads<F, false, decltype(geo)::value, decltype(adi)::value>(), 0, L.s>>>(g.args, g.tab);
-  };
-  auto by_eos = [&](auto geo) {
-    if (m0.eos == FARGO_ADIABATIC) go(geo, std::true_type{});
-    else go(geo, std::false_type{});
-  };
-  if (m0.geo == FARGO_SPHERICAL) by_eos(std::integral_constant<int, FARGO_SPHERICAL>{});
-  else if (m0.geo == FARGO_CYLINDRICAL) by_eos(std::integral_constant<int, FARGO_CYLINDRICAL>{});
-  else by_eos(std::integral_constant<int, FARGO_CARTESIAN>{});
-  if (m0.eos == FARGO_ADIABATIC) k_source_ghosts_many<F, true><<<ghosts.nblk, 256, 0, L.s>>>(ghosts.args, ghosts.tab);
-  else k_source_ghosts_many<F, false><<<ghosts.nblk, 256, 0, L.s>>>(ghosts.args, ghosts.tab);
+  source2_form(m0, [&](auto cyl, auto adi) {
+    k_source2_many<F, decltype(cyl)::value, decltype(adi)::value><<<g.nblk, 256, 0, L.s>>>(g.args, g.tab);
+  });
   prof_end(L, K_SRC);
 }
 
 #define FARGO_SOURCE_MANY(F)                                                                                        \
   template size_t source_args_bytes<F>();                                                                          \
-  template unsigned source_args<F>(const Mesh &, const StateT<F> &, const DevWords &, F *, F *, F *, F *, void *); \
-  template unsigned source_ghosts_args<F>(const Mesh &, const StateT<F> &, F *, F *, F *, F *, void *);            \
-  template void launch_source_many<F>(Launch &, const Mesh &, const ManyGrid &, const ManyGrid &);
+  template int source_rows<F>(const std::vector<Mesh> &);                                                          \
+  template unsigned source_args<F>(const Mesh &, const StateT<F> &, const DevWords &, F *, F *, F *, int, void *); \
+  template void launch_source_many<F>(Launch &, const Mesh &, const ManyGrid &);
 FARGO_SOURCE_MANY(double)
 FARGO_SOURCE_MANY(float)
 #undef FARGO_SOURCE_MANY

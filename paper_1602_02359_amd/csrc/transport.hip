@@ -1149,6 +1149,15 @@ template <typename F>
 size_t sweep_y_args_bytes() { return sizeof(SweepYArgs<F>); }
 
 template <typename F>
+int sweep_y_rows(const std::vector<Mesh> &ms, int most) {
+  const bool adi = ms[0].eos == FARGO_ADIABATIC;
+  static const long slots[2] = {block_slots(k_sweep_y_many<F, 4, false, false>, MANY_BS),
+                                block_slots(k_sweep_y_many<F, 5, false, true>, MANY_BS)};
+  return fill_chunk_length(ms, most, slots[adi], SWEEP_OVER,
+                           [](const Mesh &m) { return (m.nx + MANY_BS - 1) / MANY_BS; });
+}
+
+template <typename F>
 unsigned sweep_y_args(const Mesh &m0, const StateT<F> &s, const TSetT<F> &out, const double *dt, void *dst) {
   int nchunk = (m0.ny + m0.chunk - 1) / m0.chunk;
   const Mesh m = chunked(m0, m0.ny, nchunk);
@@ -1207,6 +1216,7 @@ void launch_vel_many(Launch &L, const ManyGrid &g) {
 
 #define FARGO_TRANSPORT_MANY(F)                                                                                     \
   template size_t sweep_y_args_bytes<F>();                                                                         \
+  template int sweep_y_rows<F>(const std::vector<Mesh> &, int);                                                    \
   template unsigned sweep_y_args<F>(const Mesh &, const StateT<F> &, const TSetT<F> &, const double *, void *);    \
   template void launch_sweep_y_many<F>(Launch &, const Mesh &, const ManyGrid &);                                  \
   template size_t ring_x_args_bytes<F>();                                                                          \

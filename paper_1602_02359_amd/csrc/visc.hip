@@ -165,13 +165,13 @@ __global__ __launch_bounds__(256) void k_visc_many(const void *args, const uint2
   visc_body<F>(a.V, t.y, a.nb);
 }
 
-// the pass over mesh m with chunks of at most VISC_ROWS rows, as many as `slots`
+// the pass over mesh m with chunks of at most `rows` rows, as many as `slots`
 // waves can share (0: no more than that takes), and its blocks
 template <typename F>
 Visc<F> visc_of(const Mesh &m, const StateT<F> &s, const F *vx2, const F *vy2, F *vx3, F *vy3, const double *dt,
-                long slots, unsigned &nb) {
+                long slots, int rows, unsigned &nb) {
   Visc<F> V{m, s, vx2, vy2, dt, vx3, vy3, (m.nx + VISC_U - 1) / VISC_U, 0, 0};
-  int nch = slots ? fill_chunks(m.ny, VISC_ROWS, 1, V.nseg, slots, 2) : (m.ny + VISC_ROWS - 1) / VISC_ROWS;
+  int nch = slots ? fill_chunks(m.ny, rows, 1, V.nseg, slots, 2) : (m.ny + rows - 1) / rows;
   V.chunk = (m.ny + nch - 1) / nch;
   V.nchunk = (m.ny + V.chunk - 1) / V.chunk;
   nb = (unsigned)(((long)V.nseg * V.nchunk + 3) / 4);
@@ -185,7 +185,7 @@ void launch_visc(Launch &L, const Mesh &m, const StateT<F> &s, const F *vx2, con
                  const double *dt) {
   static const long slots = 4 * block_slots(k_visc<F>, 256);
   unsigned nb;
-  const Visc<F> V = visc_of(m, s, vx2, vy2, vx3, vy3, dt, slots, nb);
+  const Visc<F> V = visc_of(m, s, vx2, vy2, vx3, vy3, dt, slots, VISC_ROWS, nb);
   prof_begin(L, K_VISC);
   k_visc<F><<<nb, 256, 0, L.s>>>(V);
   prof_end(L, K_VISC);
@@ -195,10 +195,16 @@ template <typename F>
 size_t visc_args_bytes() { return sizeof(ViscArgs<F>); }
 
 template <typename F>
+int visc_rows(const std::vector<Mesh> &ms) {
+  static const long slots = 4 * block_slots(k_visc_many<F>, 256);
+  return fill_chunk_length(ms, VISC_ROWS, slots, 2, [](const Mesh &m) { return (m.nx + VISC_U - 1) / VISC_U; });
+}
+
+template <typename F>
 unsigned visc_args(const Mesh &m, const StateT<F> &s, const F *vx2, const F *vy2, F *vx3, F *vy3, const double *dt,
-                   void *dst) {
+                   int rows, void *dst) {
   unsigned nb;
-  const Visc<F> V = visc_of(m, s, vx2, vy2, vx3, vy3, dt, 0L, nb);
+  const Visc<F> V = visc_of(m, s, vx2, vy2, vx3, vy3, dt, 0L, rows, nb);
   *(ViscArgs<F> *)dst = ViscArgs<F>{V, nb, 0};
   return nb;
 }
@@ -214,8 +220,9 @@ void launch_visc_many(Launch &L, const ManyGrid &g) {
   template void launch_visc<F>(Launch &, const Mesh &, const StateT<F> &, const F *, const F *, F *, F *,          \
                                const double *);                                                                    \
   template size_t visc_args_bytes<F>();                                                                            \
+  template int visc_rows<F>(const std::vector<Mesh> &);                                                            \
   template unsigned visc_args<F>(const Mesh &, const StateT<F> &, const F *, const F *, F *, F *, const double *,  \
-                                 void *);                                                                          \
+                                 int, void *);                                                                        \
   template void launch_visc_many<F>(Launch &, const ManyGrid &);
 FARGO_VISC(double)
 FARGO_VISC(float)

@@ -100,6 +100,27 @@ def test_fused_z_x_pass_fp64(geo, eos, nx, turn):
     assert _step(prob) <= 1e-12
 
 
+@pytest.mark.parametrize("nx,ny", [(1, 5), (2, 4), (3, 3), (58, 33), (60, 70), (61, 32), (62, 9), (120, 40), (123, 31)])
+@pytest.mark.parametrize("geo,eos", [("cyl", "iso"), ("cyl", "adi"), ("cart", "iso"), ("cart", "adi")])
+@pytest.mark.parametrize("side", ["periodic", "fixed", "half"])
+def test_source_march_on_2d_meshes(nx, ny, geo, eos, side):
+    """Rings one zone around the 61 columns of a wave (60 with an energy) and two such segments, a wave's window longer
+    than the ring, few rows and several chunks, against the oracle."""
+    if geo == "cyl" and side == "periodic":
+        side = "outflow"
+    print("source march", nx, ny, geo, eos, side, flush=True)
+    prob = W.random_problem(geo, nx=nx, ny=ny, nz=1, eos=eos, seed=nx + ny, fargo=geo != "cart", bc=SIDES[side])
+    assert _step(prob) <= 1e-12
+
+
+@pytest.mark.parametrize("nx,ny", [(60, 70), (61, 32), (62, 9), (122, 33)])
+def test_source_march_on_2d_meshes_fp32(nx, ny):
+    print("source march fp32", nx, ny, flush=True)
+    prob = W.disk2d_cyl(nx=nx, ny=ny, noise=1e-2)
+    prob.params["precision"] = "fp32"
+    assert _step(prob) <= 2e-6
+
+
 @pytest.mark.parametrize("nx,ny,nz,eos,v0", [(1, 2100, 1, "adi", "minmax"), (2, 700, 3, "iso", "minmax"),
                                               (127, 2048, 1, "iso", "mean"), (129, 300, 7, "adi", "minmax"),
                                               (641, 1100, 2 + 1, "iso", "mean"), (1281, 12, 1, "adi", "mean"),
