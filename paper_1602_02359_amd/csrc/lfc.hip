@@ -311,16 +311,23 @@ __global__ __launch_bounds__(LB) void k_flux_grad(int nx, int ny, int nsamp, con
 // one 16-wide tile of output channels.  One partial sum per block, for the
 // reduction below, and the bias gradient (the sum of g) alongside.
 // ---------------------------------------------------------------------------
+// Bound by LDS until its bank conflicts went (8 samples of 768 x 256: 32 to 32
+// channels 65 to 50 us, 32 to 2 49 to 33, 4 to 32 31 to 30, against 33, 18 and 18
+// for the activations and gradients at the copy rate): operand reads that stay
+// 16 bytes wide, and rows and channel groups spaced so that the lanes of a read
+// or store fall into different banks.
 constexpr int CW_THREADS = 384, CW_RG = 4;
-constexpr int CW_AW = 80; // staged activation columns: pixel x0 - 1 + c - 7 at column c (7..72)
-constexpr int CW_GW = 72; // staged layer-gradient columns: pixel x0 + c (0..63)
+constexpr int CW_W = 80;   // row of a staged channel
+// columns: activations, pixel x0 - 1 + c - 7 at column c (7..72); layer
+// gradients, pixel x0 + c (0..63)
+// Rows of 160 bytes spread a wave's 16-byte operand reads over all banks; the
+// 32 bytes more after every eight channels do so for the staging's stores, whose
+// lanes hold four such groups.
+constexpr int cw_row(int ch) { return ch * CW_W + (ch >> 3) * 16; }
 
-// the B operand of tap column tx (0..2) from the window around LDS column c
-// (16-byte aligned): columns c - 1 + tx .. c + 6 + tx
-__device__ inline uint4 tap_run(const unsigned short *ap, int tx) {
-  const unsigned dm = *reinterpret_cast<const unsigned *>(ap - 2);
-  const uint4 d = *reinterpret_cast<const uint4 *>(ap);
-  const unsigned dp = *reinterpret_cast<const unsigned *>(ap + 8);
+// the B operand of tap column tx (0..2) from eight columns d (16-byte aligned in
+// LDS) and the two-column words below and above them
+__device__ inline uint4 tap_run(unsigned dm, const uint4 &d, unsigned dp, int tx) {
   if (tx == 1) return d;
   const bool lo = tx == 0;
   return make_uint4(__builtin_amdgcn_alignbyte(lo ? d.x : d.y, lo ? dm : d.x, 2),
@@ -353,12 +360,13 @@ __global__ __launch_bounds__(CW_THREADS) void k_conv_w(int nx, int ny, int rpc, 
   constexpr int NGT = CW_RG * 16 * GCH;  // layer-gradient tasks
   constexpr int NAL = (NAT + CW_THREADS - 1) / CW_THREADS;
   static_assert(NHT <= CW_THREADS && NGT <= CW_THREADS, "one halo and one gradient task per thread");
-  constexpr int A_BYTES = AR * CIN * CW_AW * 2, G_BYTES = CW_RG * 16 * MT * CW_GW * 2;
+  constexpr int AS = cw_row(CIN), GS = cw_row(16 * MT); // elements of a staged pixel row
+  constexpr int A_BYTES = AR * AS * 2, G_BYTES = CW_RG * GS * 2;
   constexpr int DB_BYTES = CW_THREADS * 8 * 4;
   constexpr int LDS_BYTES = A_BYTES + G_BYTES > DB_BYTES ? A_BYTES + G_BYTES : DB_BYTES;
   __shared__ __align__(16) unsigned char lds[LDS_BYTES];
-  auto At = reinterpret_cast<unsigned short(*)[CIN][CW_AW]>(lds);
-  auto Gt = reinterpret_cast<unsigned short(*)[16 * MT][CW_GW]>(lds + A_BYTES);
+  auto At = [&](int r, int ch) { return reinterpret_cast<unsigned short *>(lds) + r * AS + cw_row(ch); };
+  auto Gt = [&](int r, int ch) { return reinterpret_cast<unsigned short *>(lds + A_BYTES) + r * GS + cw_row(ch); };
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, ln = lane & 15, q = lane >> 4;
   const int strips = nx / 64;
   const int strip = blockIdx.x % strips, rc = (blockIdx.x / strips) % nrc, s = blockIdx.x / (strips * nrc);
@@ -366,9 +374,9 @@ __global__ __launch_bounds__(CW_THREADS) void k_conv_w(int nx, int ny, int rpc, 
   const size_t sb = (size_t)s * nx * ny;
   // rows of the output-channel tile beyond COUT stay zero
   if (COUT < 16 * MT)
-    for (int e = tid; e < CW_RG * (16 * MT - COUT) * CW_GW; e += CW_THREADS) {
-      const int b = e / ((16 * MT - COUT) * CW_GW), r = e % ((16 * MT - COUT) * CW_GW);
-      Gt[b][COUT + r / CW_GW][r % CW_GW] = 0;
+    for (int e = tid; e < CW_RG * (16 * MT - COUT) * CW_W; e += CW_THREADS) {
+      const int b = e / ((16 * MT - COUT) * CW_W), r = e % ((16 * MT - COUT) * CW_W);
+      Gt(b, COUT + r / CW_W)[r % CW_W] = 0;
     }
   auto ld = [&](const unsigned short *src, int wide) -> uint4 {
     if (wide) return *reinterpret_cast<const uint4 *>(src);
@@ -419,7 +427,7 @@ __global__ __launch_bounds__(CW_THREADS) void k_conv_w(int nx, int ny, int rpc, 
         const int r = t / (16 * ACH), w = t % (16 * ACH), m = w / ACH, c0 = 8 * (w % ACH);
 #pragma unroll
         for (int k = 0; k < (CIN == 32 ? 8 : 4); k++)
-          *reinterpret_cast<uint2 *>(&At[r][c0 + k][8 + 4 * m]) = chan4(ra[i][0], ra[i][1], ra[i][2], ra[i][3], k);
+          *reinterpret_cast<uint2 *>(At(r, c0 + k) + 8 + 4 * m) = chan4(ra[i][0], ra[i][1], ra[i][2], ra[i][3], k);
       }
     }
     if (tid < NHT) {
@@ -427,7 +435,7 @@ __global__ __launch_bounds__(CW_THREADS) void k_conv_w(int nx, int ny, int rpc, 
 #pragma unroll
       for (int k = 0; k < (CIN == 32 ? 8 : 4); k++) {
         const unsigned u = dword(rh, k >> 1);
-        At[r][c0 + k][side ? 72 : 7] = (unsigned short)(k & 1 ? u >> 16 : u & 0xFFFFu);
+        At(r, c0 + k)[side ? 72 : 7] = (unsigned short)(k & 1 ? u >> 16 : u & 0xFFFFu);
       }
     }
     if (tid < NGT) {
@@ -435,7 +443,7 @@ __global__ __launch_bounds__(CW_THREADS) void k_conv_w(int nx, int ny, int rpc, 
 #pragma unroll
       for (int k = 0; k < (GC == 32 ? 8 : COUT); k++) {
         const uint2 v = chan4(rg[0], rg[1], rg[2], rg[3], k);
-        *reinterpret_cast<uint2 *>(&Gt[r][c0 + k][4 * m]) = v;
+        *reinterpret_cast<uint2 *>(Gt(r, c0 + k) + 4 * m) = v;
         db[k] += (lo_bf16(v.x) + hi_bf16(v.x)) + (lo_bf16(v.y) + hi_bf16(v.y));
       }
     }
@@ -470,20 +478,30 @@ __global__ __launch_bounds__(CW_THREADS) void k_conv_w(int nx, int ny, int rpc, 
 #pragma unroll
       for (int ks = 0; ks < 2; ks++) {
         const int c0 = 32 * ks + 8 * q;
-        const unsigned short *ap = &At[rr + ty][ci][8 + c0];
+        const unsigned short *row = At(rr + ty, ci);
+        int below = 8 + c0 - 2, above = 8 + c0 + 8;
         if (CIN == 32) {
-          const uint4 b0 = tap_run(ap, 0), b1 = tap_run(ap, 1), b2 = tap_run(ap, 2);
+          // one 16-byte read and two of four bytes: the compiler would combine
+          // them into six reads of two words, with eight lanes to a bank
+          asm("" : "+v"(below));
+          asm("" : "+v"(above));
+        }
+        const unsigned dm = *reinterpret_cast<const unsigned *>(row + below);
+        const uint4 d = *reinterpret_cast<const uint4 *>(__builtin_assume_aligned(row + 8 + c0, 16));
+        const unsigned dp = *reinterpret_cast<const unsigned *>(row + above);
+        if (CIN == 32) {
+          const uint4 b0 = tap_run(dm, d, dp, 0), b2 = tap_run(dm, d, dp, 2);
 #pragma unroll
           for (int mt = 0; mt < MT; mt++) {
-            const uint4 a = *reinterpret_cast<const uint4 *>(&Gt[rr][16 * mt + ln][c0]);
+            const uint4 a = *reinterpret_cast<const uint4 *>(__builtin_assume_aligned(Gt(rr, 16 * mt + ln) + c0, 16));
             acc[0][mt] = mfma(a, b0, acc[0][mt]);
-            acc[1][mt] = mfma(a, b1, acc[1][mt]);
+            acc[1][mt] = mfma(a, d, acc[1][mt]);
             acc[2][mt] = mfma(a, b2, acc[2][mt]);
           }
         } else {
-          uint4 b = tap_run(ap, tx);
+          uint4 b = tap_run(dm, d, dp, tx);
           if (!kok) b = make_uint4(0u, 0u, 0u, 0u);
-          const uint4 a = *reinterpret_cast<const uint4 *>(&Gt[rr][16 * mt1 + ln][c0]);
+          const uint4 a = *reinterpret_cast<const uint4 *>(__builtin_assume_aligned(Gt(rr, 16 * mt1 + ln) + c0, 16));
           acc[0][0] = mfma(a, b, acc[0][0]);
         }
       }
