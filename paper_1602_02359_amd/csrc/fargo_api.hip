@@ -1427,16 +1427,21 @@ int fargo_lfc_get_grad(fargo_lfc *l, float *host, int32_t n) {
   return l ? lfc_copy_out(l->B.grad, host, n) : FARGO_EINVAL;
 }
 
-int fargo_lfc_forward_batch(fargo_lfc *l, const fargo_state *states, int32_t n, void *stream) {
+// the net and drho of n states; flag (may be null): the guard's result
+static int lfc_run(fargo_lfc *l, const fargo_state *states, int32_t n, void *stream, int *flag) {
   if (!l) return FARGO_EINVAL;
   LfcFeed in;
   int rc = lfc_feed(l, states, n, in);
   if (rc) return rc;
   Launch L{(hipStream_t)stream, &l->ctx->prof};
   const Mesh &m = l->ctx->m;
-  lfc_forward(L, m, in, n, l->sc, l->B);
-  lfc_drho(L, m, n, l->B, l->p.flux_scale, nullptr, l->p.sigma);
+  lfc_forward(L, m, in, n, l->sc, l->B, flag);
+  lfc_drho(L, m, in, n, l->B, l->p.flux_scale, nullptr, l->p.sigma, l->p.guard, flag);
   return hipGetLastError() == hipSuccess ? FARGO_OK : FARGO_EHIP;
+}
+
+int fargo_lfc_forward_batch(fargo_lfc *l, const fargo_state *states, int32_t n, void *stream) {
+  return lfc_run(l, states, n, stream, nullptr);
 }
 
 int fargo_lfc_forward(fargo_lfc *l, const fargo_state *state, void *stream) {
@@ -1456,12 +1461,11 @@ int fargo_lfc_train_batch(fargo_lfc *l, const fargo_state *states, const double 
   }
   Launch L{(hipStream_t)stream, &l->ctx->prof};
   const Mesh &m = l->ctx->m;
-  lfc_forward(L, m, in, n, l->sc, l->B);
-  lfc_drho(L, m, n, l->B, l->p.flux_scale, &tg, l->p.sigma);
-  lfc_backward(L, m, n, l->B, l->p.flux_scale);
+  lfc_forward(L, m, in, n, l->sc, l->B, nullptr);
+  lfc_drho(L, m, in, n, l->B, l->p.flux_scale, &tg, l->p.sigma, 0.0, nullptr);
   l->step++;
   const double c1 = 1.0 - std::pow(0.9, l->step), c2 = 1.0 - std::pow(0.999, l->step);
-  lfc_adam(L, l->B, (float)lr, (float)c1, (float)c2);
+  lfc_backward(L, m, n, l->B, l->p.flux_scale, (float)lr, (float)c1, (float)c2);
   lfc_pack(L, l->B);
   return hipGetLastError() == hipSuccess ? FARGO_OK : FARGO_EHIP;
 }
@@ -1471,10 +1475,11 @@ int fargo_lfc_train_step(fargo_lfc *l, const fargo_state *state, const double *t
 }
 
 int fargo_lfc_apply(fargo_lfc *l, fargo_state *state, void *stream) {
-  int rc = fargo_lfc_forward(l, state, stream);
+  if (!l) return FARGO_EINVAL;
+  int rc = lfc_run(l, state, 1, stream, l->flag);
   if (rc) return rc;
   Launch L{(hipStream_t)stream, &l->ctx->prof};
-  lfc_apply(L, l->ctx->m, l->B, (double *)state->rho, l->p.guard, l->flag);
+  lfc_apply(L, l->ctx->m, l->B, (double *)state->rho, l->flag);
   return hipGetLastError() == hipSuccess ? FARGO_OK : FARGO_EHIP;
 }
 

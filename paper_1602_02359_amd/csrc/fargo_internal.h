@@ -645,12 +645,17 @@ struct LfcTargets {
 // blocks of the weight-gradient kernels for nsamp samples (rows per block
 // and row chunks per strip returned through rpc, nrc)
 int lfc_wblocks(int nx, int ny, int nsamp, int *rpc, int *nrc);
-void lfc_forward(Launch &L, const Mesh &m, const LfcFeed &in, int nsamp, const LfcScales &sc, const LfcBufs &B);
-void lfc_drho(Launch &L, const Mesh &m, int nsamp, const LfcBufs &B, double sF, const LfcTargets *tg, double sigma);
-void lfc_backward(Launch &L, const Mesh &m, int nsamp, const LfcBufs &B, double sF);
-void lfc_adam(Launch &L, const LfcBufs &B, float lr, float c1, float c2);
+// the net on nsamp samples; flag (may be null) is cleared
+void lfc_forward(Launch &L, const Mesh &m, const LfcFeed &in, int nsamp, const LfcScales &sc, const LfcBufs &B,
+                 int *flag);
+// drho from the net's output, with targets the loss and its gradient; flag (may
+// be null) is set where drho fails the guard
+void lfc_drho(Launch &L, const Mesh &m, const LfcFeed &in, int nsamp, const LfcBufs &B, double sF,
+              const LfcTargets *tg, double sigma, double guard, int *flag);
+// the gradients and the Adam update (lr; c1, c2: bias corrections)
+void lfc_backward(Launch &L, const Mesh &m, int nsamp, const LfcBufs &B, double sF, float lr, float c1, float c2);
 void lfc_pack(Launch &L, const LfcBufs &B);
-void lfc_apply(Launch &L, const Mesh &m, const LfcBufs &B, double *rho, double guard, int *flag);
+void lfc_apply(Launch &L, const Mesh &m, const LfcBufs &B, double *rho, const int *flag); // unless *flag
 void lfc_restrict(Launch &L, const Mesh &mf, const double *rf, const double *vxf, const double *vyf, const Mesh &mc,
                   double *rc, double *vxc, double *vyc);
 void lfc_target(Launch &L, const Mesh &m, const double *ref, const double *plain, double *t);

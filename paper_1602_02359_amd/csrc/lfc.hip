@@ -51,17 +51,37 @@ __device__ inline f4 mfma(uint4 a, uint4 b, f4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8, a), __builtin_bit_cast(bf8, b), c, 0, 0, 0);
 }
 
+// The pixel of a thread of the elementwise kernels.  A wave's 64 pixels lie in
+// one row of one sample (a row is a multiple of 64), so sample and row are
+// formed once per wave and what is indexed by them comes through scalar loads.
+// (32 bits hold any count of pixels whose activations fit in memory.)
+struct Pixel {
+  unsigned P;    // pixel of the batch
+  int s, j, i;   // sample, row, column
+  bool in;       // within the batch
+  __device__ inline Pixel(int nx, int ny, int nsamp) {
+    const unsigned npix = (unsigned)nx * (unsigned)ny, lane = threadIdx.x & 63u;
+    const unsigned P0 = __builtin_amdgcn_readfirstlane(blockIdx.x * (unsigned)LB + threadIdx.x - lane);
+    in = P0 < npix * (unsigned)nsamp;
+    s = (int)(P0 / npix);
+    const unsigned p0 = P0 - (unsigned)s * npix;
+    j = (int)(p0 / (unsigned)nx);
+    i = (int)(p0 - (unsigned)j * (unsigned)nx + lane);
+    P = P0 + lane;
+  }
+};
+
 // ---------------------------------------------------------------------------
-// features (FP64 arithmetic, rounded to FP32 then to bfloat16), all samples
+// features (FP64 arithmetic, rounded to FP32 then to bfloat16), all samples;
+// flag, if given, is cleared for the guard of the pass that follows
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(LB) void k_features(Mesh m, LfcFeed in, int nsamp, LfcScales sc,
-                                                 unsigned short *__restrict__ f) {
+                                                 unsigned short *__restrict__ f, int *flag) {
 #pragma clang fp contract(off)
-  const int npix = m.nx * m.ny;
-  const long P = (long)blockIdx.x * LB + threadIdx.x;
-  if (P >= (long)npix * nsamp) return;
-  const int s = (int)(P / npix), p = (int)(P - (long)s * npix);
-  const int j = p / m.nx, i = p - j * m.nx;
+  const Pixel px(m.nx, m.ny, nsamp);
+  if (flag && blockIdx.x == 0 && threadIdx.x == 0) *flag = 0;
+  if (!px.in) return;
+  const int s = px.s, j = px.j, i = px.i;
   const unsigned c = m.o32(i, j + m.j0, 0);
   const double f0 = in.rho[s][c] / sc.rho_s - 1.0;
   const double f1 = in.vy[s][c] / sc.u_s;
@@ -70,7 +90,7 @@ __global__ __launch_bounds__(LB) void k_features(Mesh m, LfcFeed in, int nsamp, 
   uint2 v;
   v.x = (unsigned)to_bf16((float)f0) | ((unsigned)to_bf16((float)f1) << 16);
   v.y = (unsigned)to_bf16((float)f2) | ((unsigned)to_bf16((float)f3) << 16);
-  *reinterpret_cast<uint2 *>(f + (size_t)P * 4) = v;
+  *reinterpret_cast<uint2 *>(f + (size_t)px.P * 4) = v;
 }
 
 // ---------------------------------------------------------------------------
@@ -231,34 +251,39 @@ __device__ inline double block_sum(double v, double *lds) {
   return s; // in thread 0
 }
 
-__global__ __launch_bounds__(LB) void k_drho(Mesh m, int nsamp, const float *__restrict__ o, double sF,
-                                             LfcTargets tg, int with_target, double sigma,
+// with flag, the guard of the update that follows: rho + drho positive and
+// |drho| at most guard rho in every zone, else the flag is set
+__global__ __launch_bounds__(LB) void k_drho(Mesh m, LfcFeed in, int nsamp, const float *__restrict__ o, double sF,
+                                             LfcTargets tg, int with_target, double sigma, double guard,
                                              double *__restrict__ drho, double *__restrict__ gD,
-                                             double *__restrict__ lpart) {
+                                             double *__restrict__ lpart, int *flag) {
 #pragma clang fp contract(off)
   __shared__ double red[LB / 64];
-  const int nx = m.nx, ny = m.ny, npix = nx * ny;
-  const long ntot = (long)npix * nsamp;
-  const long P = (long)blockIdx.x * LB + threadIdx.x;
+  const int nx = m.nx, ny = m.ny;
+  const Pixel px(nx, ny, nsamp);
   double e2 = 0.0;
-  if (P < ntot) {
-    const int s = (int)(P / npix), p = (int)(P - (long)s * npix);
-    const int j = p / nx, i = p - j * nx;
-    const long b = (long)s * npix;
-    const long pr = b + j * nx + (i + 1 == nx ? 0 : i + 1), pu = P + nx;
-    const double fx0 = sF * (double)o[2 * P], fx1 = sF * (double)o[2 * pr];
-    const double fy0 = j == 0 ? 0.0 : sF * (double)o[2 * P + 1];
-    const double fy1 = j + 1 == ny ? 0.0 : sF * (double)o[2 * pu + 1];
+  if (px.in) {
+    const unsigned P = px.P;
+    const int j = px.j, i = px.i;
+    const unsigned pr = P - (unsigned)i + (unsigned)(i + 1 == nx ? 0 : i + 1), pu = P + (unsigned)nx;
+    const double fx0 = sF * (double)o[2 * (size_t)P], fx1 = sF * (double)o[2 * (size_t)pr];
+    const double fy0 = j == 0 ? 0.0 : sF * (double)o[2 * (size_t)P + 1];
+    const double fy1 = j + 1 == ny ? 0.0 : sF * (double)o[2 * (size_t)pu + 1];
     const double div = (fx1 - fx0) + (fy1 - fy0);
     const double iv = m.g.invVj(j + m.j0);
     const double d = (-iv) * div;
     drho[P] = d;
     if (with_target) {
-      const double t = tg.t[s][p];
+      const double t = tg.t[px.s][j * nx + i];
       const double e = (d - t) / sigma;
       e2 = e * e;
-      const double g = 2.0 * (d - t) / ((double)ntot * sigma * sigma);
+      const double ntot = (double)((long)nx * ny * nsamp);
+      const double g = 2.0 * (d - t) / (ntot * sigma * sigma);
       gD[P] = (-iv) * g;
+    }
+    if (flag) {
+      const double r = in.rho[px.s][m.o32(i, j + m.j0, 0)];
+      if (!(r + d > 0.0) || !(fabs(d) <= guard * r)) atomicOr(flag, 1);
     }
   }
   if (!with_target) return;
@@ -270,7 +295,8 @@ __global__ __launch_bounds__(256) void k_loss_final(const double *__restrict__ l
                                                     double *__restrict__ loss) {
   __shared__ double red[4];
   double s = 0.0;
-  for (int q = threadIdx.x; q < n; q += blockDim.x) s += lpart[q];
+#pragma unroll 8
+  for (int q = threadIdx.x; q < n; q += 256) s += lpart[q]; // (eight loads in flight; the order of the sum is kept)
   s = block_sum(s, red);
   if (threadIdx.x == 0) *loss = s / (double)ntot;
 }
@@ -280,14 +306,12 @@ __global__ __launch_bounds__(256) void k_loss_final(const double *__restrict__ l
 __global__ __launch_bounds__(LB) void k_flux_grad(int nx, int ny, int nsamp, const double *__restrict__ gD, double sF,
                                                   unsigned short *__restrict__ g3) {
 #pragma clang fp contract(off)
-  const int npix = nx * ny;
-  const long P = (long)blockIdx.x * LB + threadIdx.x;
-  if (P >= (long)npix * nsamp) return;
-  const int s = (int)(P / npix), p = (int)(P - (long)s * npix);
-  const int j = p / nx, i = p - j * nx;
-  const long b = (long)s * npix;
-  const double gx = gD[b + j * nx + (i == 0 ? nx - 1 : i - 1)] - gD[P];
-  const double gy = j == 0 ? 0.0 : gD[P - nx] - gD[P];
+  const Pixel px(nx, ny, nsamp);
+  if (!px.in) return;
+  const unsigned P = px.P;
+  const int i = px.i;
+  const double gx = gD[P - (unsigned)i + (unsigned)(i == 0 ? nx - 1 : i - 1)] - gD[P];
+  const double gy = px.j == 0 ? 0.0 : gD[P - (unsigned)nx] - gD[P];
   uint2 v;
   v.x = (unsigned)to_bf16((float)(sF * gx)) | ((unsigned)to_bf16((float)(sF * gy)) << 16);
   v.y = 0u;
@@ -547,10 +571,21 @@ __global__ __launch_bounds__(CW_THREADS) void k_conv_w(int nx, int ny, int rpc, 
 // kernels' partials (one row of LFC_NPARAM per block, all three layers in one
 // launch).  A block takes RE consecutive parameters; its RG thread groups sum
 // interleaved subsets of the rows, and the group sums are added in a fixed
-// order (deterministic).
+// order (deterministic).  The parameters' Adam update follows in the same launch.
 constexpr int RE = 64, RG = 16;
+struct AdamArgs {
+  float *w, *mo, *ve; // FP32 master parameters and moments
+  float lr, b1, b2, c1, c2, eps;
+};
+__device__ inline void adam(const AdamArgs &A, int e, float ge) {
+  const float mn = A.b1 * A.mo[e] + (1.f - A.b1) * ge;
+  const float vn = A.b2 * A.ve[e] + (1.f - A.b2) * ge * ge;
+  A.mo[e] = mn;
+  A.ve[e] = vn;
+  A.w[e] = A.w[e] - A.lr * (mn / A.c1) / (sqrtf(vn / A.c2) + A.eps);
+}
 __global__ __launch_bounds__(RE * RG) void k_reduce_w(int nchunk, const float *__restrict__ part,
-                                                      float *__restrict__ grad) {
+                                                      float *__restrict__ grad, AdamArgs A) {
   __shared__ float red[RG][RE];
   const int el = threadIdx.x % RE, g = threadIdx.x / RE;
   const int e = blockIdx.x * RE + el;
@@ -565,23 +600,8 @@ __global__ __launch_bounds__(RE * RG) void k_reduce_w(int nchunk, const float *_
     float t = 0.f;
     for (int q = 0; q < RG; q++) t += red[q][el];
     grad[e] = t;
+    adam(A, e, t);
   }
-}
-
-// ---------------------------------------------------------------------------
-// Adam on the FP32 master parameters, and the bfloat16 copies of the weights
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(LB) void k_adam(int n, float *__restrict__ w, float *__restrict__ mo,
-                                             float *__restrict__ ve, const float *__restrict__ g, float lr,
-                                             float b1, float b2, float c1, float c2, float eps) {
-  const int e = blockIdx.x * LB + threadIdx.x;
-  if (e >= n) return;
-  const float ge = g[e];
-  const float mn = b1 * mo[e] + (1.f - b1) * ge;
-  const float vn = b2 * ve[e] + (1.f - b2) * ge * ge;
-  mo[e] = mn;
-  ve[e] = vn;
-  w[e] = w[e] - lr * (mn / c1) / (sqrtf(vn / c2) + eps);
 }
 
 // bfloat16 weight matrices of the five convolutions, packed as MFMA A
@@ -623,27 +643,14 @@ __global__ __launch_bounds__(LB) void k_pack(const float *__restrict__ w, LfcWei
 }
 
 // ---------------------------------------------------------------------------
-// guard and conservative update; restriction
+// conservative update, unless the guard refused it; restriction
 // ---------------------------------------------------------------------------
-__global__ void k_flag_clear(int *flag) { *flag = 0; }
-
-__global__ __launch_bounds__(LB) void k_guard(Mesh m, const double *__restrict__ rho,
-                                              const double *__restrict__ d, double guard, int *flag) {
-#pragma clang fp contract(off)
-  const int p = blockIdx.x * LB + threadIdx.x;
-  if (p >= m.nx * m.ny) return;
-  const int j = p / m.nx, i = p - j * m.nx;
-  const double r = rho[m.o32(i, j + m.j0, 0)], dd = d[p];
-  if (!(r + dd > 0.0) || !(fabs(dd) <= guard * r)) atomicOr(flag, 1);
-}
-
 __global__ __launch_bounds__(LB) void k_commit(Mesh m, double *__restrict__ rho, const double *__restrict__ d,
                                                const int *__restrict__ flag) {
-  const int p = blockIdx.x * LB + threadIdx.x;
-  if (p >= m.nx * m.ny || *flag) return;
-  const int j = p / m.nx, i = p - j * m.nx;
-  const unsigned c = m.o32(i, j + m.j0, 0);
-  rho[c] = rho[c] + d[p];
+  const Pixel px(m.nx, m.ny, 1);
+  if (!px.in || *flag) return;
+  const unsigned c = m.o32(px.i, px.j + m.j0, 0);
+  rho[c] = rho[c] + d[px.P];
 }
 
 __global__ __launch_bounds__(LB) void k_restrict(Mesh mf, Mesh mc, int R, const double *__restrict__ rf,
@@ -711,10 +718,11 @@ int lfc_wblocks(int nx, int ny, int nsamp, int *rpc, int *nrc) {
   return strips * ((ny + r - 1) / r);
 }
 
-void lfc_forward(Launch &L, const Mesh &m, const LfcFeed &in, int nsamp, const LfcScales &sc, const LfcBufs &B) {
+void lfc_forward(Launch &L, const Mesh &m, const LfcFeed &in, int nsamp, const LfcScales &sc, const LfcBufs &B,
+                 int *flag) {
   const long ntot = (long)m.nx * m.ny * nsamp;
   prof_begin(L, K_LFC_FEATURES);
-  k_features<<<nblk(ntot, LB), LB, 0, L.s>>>(m, in, nsamp, sc, B.f);
+  k_features<<<nblk(ntot, LB), LB, 0, L.s>>>(m, in, nsamp, sc, B.f, flag);
   prof_end(L, K_LFC_FEATURES);
   const int nt = conv_tiles(m, nsamp);
   const unsigned nb = conv_grid(nt, 2), nb3 = conv_grid(nt, 3), nb5 = conv_grid(nt, 5);
@@ -730,13 +738,14 @@ void lfc_forward(Launch &L, const Mesh &m, const LfcFeed &in, int nsamp, const L
   prof_end(L, K_LFC_FWD3);
 }
 
-void lfc_drho(Launch &L, const Mesh &m, int nsamp, const LfcBufs &B, double sF, const LfcTargets *tg,
-              double sigma) {
+void lfc_drho(Launch &L, const Mesh &m, const LfcFeed &in, int nsamp, const LfcBufs &B, double sF,
+              const LfcTargets *tg, double sigma, double guard, int *flag) {
   const long ntot = (long)m.nx * m.ny * nsamp;
   const unsigned nb = nblk(ntot, LB);
   LfcTargets none{};
   prof_begin(L, K_LFC_DRHO);
-  k_drho<<<nb, LB, 0, L.s>>>(m, nsamp, B.o, sF, tg ? *tg : none, tg ? 1 : 0, sigma, B.drho, B.gD, B.lpart);
+  k_drho<<<nb, LB, 0, L.s>>>(m, in, nsamp, B.o, sF, tg ? *tg : none, tg ? 1 : 0, sigma, guard, B.drho, B.gD, B.lpart,
+                             flag);
   prof_end(L, K_LFC_DRHO);
   if (tg) {
     prof_begin(L, K_LFC_DRHO);
@@ -745,7 +754,7 @@ void lfc_drho(Launch &L, const Mesh &m, int nsamp, const LfcBufs &B, double sF, 
   }
 }
 
-void lfc_backward(Launch &L, const Mesh &m, int nsamp, const LfcBufs &B, double sF) {
+void lfc_backward(Launch &L, const Mesh &m, int nsamp, const LfcBufs &B, double sF, float lr, float c1, float c2) {
   const int nx = m.nx, ny = m.ny;
   const long ntot = (long)nx * ny * nsamp;
   const int nt = conv_tiles(m, nsamp);
@@ -776,17 +785,11 @@ void lfc_backward(Launch &L, const Mesh &m, int nsamp, const LfcBufs &B, double 
   k_conv_w<4, 32, 32><<<nw, CW_THREADS, 0, L.s>>>(nx, ny, rpc, nrc, B.g1, B.f, B.part + LFC_OFF_W1,
                                                   B.part + LFC_OFF_B1);
   prof_end(L, K_LFC_W1);
-  // every parameter's gradient in one reduction
+  // every parameter's gradient in one reduction, and its Adam update
   prof_begin(L, K_LFC_REDUCE);
-  k_reduce_w<<<nblk(LFC_NPARAM, RE), RE * RG, 0, L.s>>>(nw, B.part, B.grad);
+  k_reduce_w<<<nblk(LFC_NPARAM, RE), RE * RG, 0, L.s>>>(
+      nw, B.part, B.grad, AdamArgs{B.w, B.mo, B.ve, lr, 0.9f, 0.999f, c1, c2, 1e-8f});
   prof_end(L, K_LFC_REDUCE);
-}
-
-void lfc_adam(Launch &L, const LfcBufs &B, float lr, float c1, float c2) {
-  prof_begin(L, K_LFC_ADAM);
-  k_adam<<<nblk(LFC_NPARAM, LB), LB, 0, L.s>>>(LFC_NPARAM, B.w, B.mo, B.ve, B.grad, lr, 0.9f, 0.999f, c1, c2,
-                                               1e-8f);
-  prof_end(L, K_LFC_ADAM);
 }
 
 void lfc_pack(Launch &L, const LfcBufs &B) {
@@ -795,16 +798,9 @@ void lfc_pack(Launch &L, const LfcBufs &B) {
   prof_end(L, K_LFC_ADAM);
 }
 
-void lfc_apply(Launch &L, const Mesh &m, const LfcBufs &B, double *rho, double guard, int *flag) {
-  const int npix = m.nx * m.ny;
+void lfc_apply(Launch &L, const Mesh &m, const LfcBufs &B, double *rho, const int *flag) {
   prof_begin(L, K_LFC_APPLY);
-  k_flag_clear<<<1, 1, 0, L.s>>>(flag);
-  prof_end(L, K_LFC_APPLY);
-  prof_begin(L, K_LFC_APPLY);
-  k_guard<<<nblk(npix, LB), LB, 0, L.s>>>(m, rho, B.drho, guard, flag);
-  prof_end(L, K_LFC_APPLY);
-  prof_begin(L, K_LFC_APPLY);
-  k_commit<<<nblk(npix, LB), LB, 0, L.s>>>(m, rho, B.drho, flag);
+  k_commit<<<nblk((long)m.nx * m.ny, LB), LB, 0, L.s>>>(m, rho, B.drho, flag);
   prof_end(L, K_LFC_APPLY);
 }
 
