@@ -646,8 +646,11 @@ void step_impl(fargo_ctx *ctx, const fargo_state *state, double dt, Launch &L) {
   launch_bc(L, m, P.rho, P.e, P.vx, P.vy, P.vz, true);                             // box 9
   const TSetT<F> TA = tset<F>(ctx, ctx->TA), TB = tset<F>(ctx, ctx->TB);
   launch_sweep_y(L, m, P, TB, dtp);                                                // boxes 12a-c, Y
-  if (m.d3) launch_zx(L, m, (const F *)P.vx, (const F *)P.vz, TB, TA, S, ctx->v0, dtp); // Z, X, split, FARGO, 12d (v_x)
-  else launch_ring_x(L, m, (const F *)P.vx, TB, TA, S, ctx->v0, dtp);              // X, split, FARGO, 12d (v_x)
+  if (!m.d3) {
+    launch_ring_x(L, m, (const F *)P.vx, TB, S, ctx->v0, dtp);                     // X, split, FARGO, 12d
+    return;
+  }
+  launch_zx(L, m, (const F *)P.vx, (const F *)P.vz, TB, TA, S, ctx->v0, dtp);      // Z, X, split, FARGO, 12d (v_x)
   launch_vel(L, m, S, TA);                                                         // 12d (v_y, v_z)
 }
 
@@ -928,7 +931,7 @@ int batch_capture(fargo_batch *b, int lanes) {
 size_t field_bytes(const fargo_ctx *c) { return (size_t)c->m.pitch * c->m.nyg * c->m.nzg * c->esize; }
 
 // ---- fused mode ----
-enum { FU_CFL, FU_DT, FU_SRC, FU_VISC, FU_SY, FU_RX, FU_VEL, FU_N };
+enum { FU_CFL, FU_DT, FU_SRC, FU_VISC, FU_SY, FU_RX, FU_N };
 
 bool fused_ok(fargo_ctx *const *c, int n) {
   const fargo_params &p0 = c[0]->p;
@@ -972,12 +975,11 @@ int fused_build(fargo_batch *b) {
   H[FU_VISC].asz = visc_args_bytes<F>();
   H[FU_SY].asz = sweep_y_args_bytes<F>();
   H[FU_RX].asz = ring_x_args_bytes<F>();
-  H[FU_VEL].asz = vel_args_bytes<F>();
   b->nxmax = 0;
   // shorter chunks where the batch leaves the chip idle
   std::vector<Mesh> ms;
   for (fargo_ctx *c : b->ctx) ms.push_back(c->m);
-  const int rows_src = source_rows<F>(ms), rows_visc = visc_rows<F>(ms);
+  const int rows_src = source_rows<F>(ms), rows_visc = visc_rows<F>(ms), rows_ring = ring_x_rows<F>(ms);
   const int rows_sweep = sweep_y_rows<F>(ms, *std::max_element(b->chunk.begin(), b->chunk.end()));
   for (unsigned d = 0; d < n; d++) {
     fargo_ctx *c = b->ctx[d];
@@ -1000,10 +1002,9 @@ int fused_build(fargo_batch *b) {
     }
     P.vz = v2[2];
     P.e = v2[3];
-    const TSetT<F> TA = tset<F>(c, c->TA), TB = tset<F>(c, c->TB);
+    const TSetT<F> TB = tset<F>(c, c->TB);
     H[FU_SY].blocks(d, sweep_y_args<F>(m, P, TB, dtp, H[FU_SY].slot(d)));
-    H[FU_RX].blocks(d, ring_x_args<F>(m, (const F *)P.vx, TB, TA, S, c->v0, dtp, H[FU_RX].slot(d)));
-    H[FU_VEL].blocks(d, vel_args<F>(m, S, TA, H[FU_VEL].slot(d)));
+    H[FU_RX].blocks(d, ring_x_args<F>(m, (const F *)P.vx, TB, S, c->v0, dtp, rows_ring, H[FU_RX].slot(d)));
   }
   size_t total = 0;
   for (auto &h : H) total += al(h.args.size()) + al(h.tab.size() * sizeof(uint2));
@@ -1041,7 +1042,6 @@ void fused_step(fargo_batch *b, Launch &L) {
   if (m0.visc) launch_visc_many<F>(L, b->g[FU_VISC]);                              // box 7d
   launch_sweep_y_many<F>(L, m0, b->g[FU_SY]);                                       // boxes 12a-c, Y
   launch_ring_x_many<F>(L, b->ctx[0]->nq, b->g[FU_RX]);                              // X, split, FARGO, 12d
-  launch_vel_many<F>(L, b->g[FU_VEL]);                                              // 12d (v_y)
 }
 
 int fused_capture(fargo_batch *b) {

@@ -525,13 +525,14 @@ void launch_visc(Launch &L, const Mesh &m, const StateT<R> &s, const R *vx2, con
 // box 12
 template <typename R>
 void launch_sweep_y(Launch &L, const Mesh &m, const StateT<R> &s, const TSetT<R> &out, const double *dt);
-// X sweep, split of Eq. 29, FARGO and 12d along X: reads T, writes rho, v_x, e
-// of the state and the Y/Z momenta into Tout (out of place, shifted)
+// 2D: X sweep, split of Eq. 29, FARGO and 12d: reads T, writes rho, v_x, v_y, e
+// of the state
 template <typename R>
-void launch_ring_x(Launch &L, const Mesh &m, const R *vx2, const TSetT<R> &T, const TSetT<R> &Tout,
-                   const StateT<R> &s, const double *v0, const double *dt);
-// 3D: the Z sweep of the Y-swept set T fused with the X transport of
-// launch_ring_x
+void launch_ring_x(Launch &L, const Mesh &m, const R *vx2, const TSetT<R> &T, const StateT<R> &s, const double *v0,
+                   const double *dt);
+// 3D: the Z sweep of the Y-swept set T, X sweep, split, FARGO and 12d along X:
+// writes rho, v_x, e of the state and the Y/Z momenta into Tout (out of place,
+// shifted), from which launch_vel forms v_y and v_z
 template <typename R>
 void launch_zx(Launch &L, const Mesh &m, const R *vx2, const R *vz, const TSetT<R> &T, const TSetT<R> &Tout,
                const StateT<R> &s, const double *v0, const double *dt);
@@ -599,16 +600,12 @@ void launch_sweep_y_many(Launch &L, const Mesh &m0, const ManyGrid &g);
 template <typename F>
 size_t ring_x_args_bytes();
 template <typename F>
-unsigned ring_x_args(const Mesh &m, const F *vx2, const TSetT<F> &T, const TSetT<F> &Tout, const StateT<F> &s,
-                     const double *v0, const double *dt, void *dst);
+int ring_x_rows(const std::vector<Mesh> &ms);
+template <typename F>
+unsigned ring_x_args(const Mesh &m, const F *vx2, const TSetT<F> &T, const StateT<F> &s, const double *v0,
+                     const double *dt, int rows, void *dst);
 template <typename F>
 void launch_ring_x_many(Launch &L, int nq, const ManyGrid &g);
-template <typename F>
-size_t vel_args_bytes();
-template <typename F>
-unsigned vel_args(const Mesh &m, const StateT<F> &s, const TSetT<F> &T, void *dst);
-template <typename F>
-void launch_vel_many(Launch &L, const ManyGrid &g);
 
 // ------------------------------------------------------------------------
 // Learned flux correction (2D cylindrical FP64 state)

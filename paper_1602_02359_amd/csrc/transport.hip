@@ -308,13 +308,12 @@ __global__ __launch_bounds__(256) void k_sweep_y(Mesh m, const F *__restrict__ r
 // Outputs are written out of place (shifted by N on store), so that the
 // segments of a ring can run in any order.
 // ------------------------------------------------------------------------
-// Zones per lane.  The ring kernel takes two in FP64 and four in FP32, where
-// they fit in registers (five waves per SIMD) and save half the lane moves a
-// zone and a third of the halo: the batch of 256 disks 834 to 760 us.  The fused
-// Z/X pass, which also holds the window of the Z sweep, takes one in FP64 (162
-// registers, three waves per SIMD; two needed 310, one wave) and two in FP32.
-template <typename F>
-constexpr int ring_m() { return sizeof(F) == 8 ? 2 : 4; }
+// Zones per lane.  The ring kernel takes two.  (Four in FP32 save lane moves and
+// halo, but cost it half its waves: the batch of 256 disks 820 us against 768.)
+// The fused Z/X pass, which also holds the window of the Z sweep, takes one in
+// FP64 (162 registers, three waves per SIMD; two needed 310, one wave) and two
+// in FP32.
+constexpr int RING_M = 2;
 template <typename F>
 constexpr int zx_m() { return sizeof(F) == 8 ? 1 : 2; }
 // halo lanes below and above: a zone's result depends on zones z - 6 .. z + 5
@@ -443,30 +442,33 @@ __device__ inline T *at(T *p, unsigned i) {
 }
 
 // The lane's place in a segment of a ring: its M zones start at window (=
-// ring) coordinate zl, iz[] are their ring indices (wrapped into [0, n)), and
-// contig tells whether they are consecutive in memory.  Only the lanes outside
-// the halo store, and only zones before the end of the segment.
+// ring) coordinate zl, iz[] are the ring indices `off` zones before them
+// (wrapped into [0, n)), and contig tells whether they are consecutive in
+// memory.  Only the lanes outside the halo store, and only zones before the end
+// of the segment.
 template <typename F, int M_>
 struct RingLane {
   static constexpr int M = M_, HLL = halo_below(M), HRL = halo_above(M);
   static constexpr int U = (WAVE - HLL - HRL) * M; // output zones per wave
   int n, lane, zl, aend, iz[M];
   bool contig;
-  __device__ inline RingLane(int nx, int seg, int ln) : n(nx), lane(ln) {
+  __device__ inline RingLane(int nx, int seg, int ln, int off = 0) : n(nx), lane(ln) {
     const int a0 = seg * U;      // first output zone of the segment
     zl = a0 - HLL * M + ln * M;  // first zone of the lane
     aend = min(a0 + U, n);
-    contig = zl >= 0 && zl + M <= n;
 #pragma unroll
     for (int q = 0; q < M; q++) {
-      const int z = zl + q;
-      if (n >= WAVE * M) { // the window is no longer than the ring: one wrap at most
-        iz[q] = z < 0 ? z + n : (z >= n ? z - n : z);
+      int z = zl + q - off;
+      if (n >= WAVE * M) { // the window is no longer than the ring: one wrap at most for it, one for the offset
+        z = z < 0 ? z + n : z;
+        z = z < 0 ? z + n : (z >= n ? z - n : z);
+        iz[q] = z;
       } else {
         const int y = z % n;
         iz[q] = y < 0 ? y + n : y;
       }
     }
+    contig = iz[0] + M <= n;
   }
   __device__ inline bool useful(int q) const { return lane >= HLL && lane < WAVE - HRL && zl + q < aend; }
   // the lane's zones of the row that starts at p, one load per zone and no
@@ -475,13 +477,13 @@ struct RingLane {
 #pragma unroll
     for (int q = 0; q < M; q++) out[q] = *at(p, (unsigned)iz[q]);
   }
-  // the lane's zones of the row that starts at p (two-element vector loads
-  // where they are consecutive)
+  // the lane's zones of the row that starts at p (loads of two elements, at any
+  // alignment, where they are consecutive)
   __device__ inline void load(const F *p, F (&out)[M]) const {
     static_assert(M % 2 == 0, "pairs of zones per lane");
     if (contig) {
-      using V2 = typename std::conditional<sizeof(F) == 8, double2, float2>::type;
-      const V2 *v = reinterpret_cast<const V2 *>(at(p, (unsigned)zl));
+      using V2 = F __attribute__((ext_vector_type(2), aligned(sizeof(F))));
+      const V2 *v = reinterpret_cast<const V2 *>(at(p, (unsigned)iz[0]));
 #pragma unroll
       for (int q = 0; q < M / 2; q++) {
         const V2 t = v[q];
@@ -528,6 +530,36 @@ struct RingOut {
         *at(p, o[h]) = v[2 * h];
         if (wrap[h]) *at(p, 0u) = v[2 * h + 1];
       }
+    }
+  }
+};
+
+// as the fused Z/X pass stores: the momenta into Tout
+template <typename F, int M>
+struct RingShift : RingOut<F, M> {
+  const TSetT<F> &T;
+  __device__ inline RingShift(const RingLane<F, M> &L, int Nm, const TSetT<F> &Tout) : RingOut<F, M>(L, Nm), T(Tout) {}
+  __device__ inline void momentum(int qi, unsigned base, const F (&v)[M]) const { (*this)(T.q[qi] + base, v); }
+  __device__ inline void density(F *p, const F (&v)[M]) const { (*this)(p, v); }
+};
+// The same where the lane's zones are already those that it stores.
+template <typename F, int M>
+struct RingPut {
+  unsigned o;
+  bool one[M / 2], two[M / 2];
+  __device__ inline explicit RingPut(const RingLane<F, M> &L) : o((unsigned)L.zl) {
+#pragma unroll
+    for (int h = 0; h < M / 2; h++) {
+      two[h] = L.useful(2 * h + 1);
+      one[h] = L.useful(2 * h) && !two[h];
+    }
+  }
+  __device__ inline void operator()(F *p, const F (&v)[M]) const {
+    using V2 = F __attribute__((ext_vector_type(2), aligned(sizeof(F))));
+#pragma unroll
+    for (int h = 0; h < M / 2; h++) {
+      if (two[h]) *reinterpret_cast<V2 *>(at(p, o + 2 * h)) = V2{v[2 * h], v[2 * h + 1]};
+      else if (one[h]) *at(p, o + 2 * h) = v[2 * h];
     }
   }
 };
@@ -611,14 +643,11 @@ __device__ constexpr int ring_qorder(int t) { return t + 2 < NQ ? t + 2 : t + 2 
 // reciprocal's series, one wrap instead of a modulo, stores in pairs): the
 // 2048 x 768 x 96 disk 3.62 to 3.17 ms, where its 14 words a zone move at 5.3
 // TB/s; 1536 x 512 x 128 2.78 to 2.43; FP32 Z/X pass 3.26 to 2.88; the FP32
-// batch of 256 disks 962 to 834 us (then four zones a lane).
-template <bool RIGHT, typename F, int NQ, int M>
-__device__ inline void ring_update_dir(const RingLane<F, M> &L, const RingConst<F> &C, unsigned base,
-                                       const F (&Ra)[M], F (&w)[M],
-                                       const F (&Qall)[NQ][M], const TSetT<F> &Tout, bool has_e,
-                                       const StateT<F> &s) {
+// batch of 256 disks 962 to 834 us.
+template <bool RIGHT, typename F, int NQ, int M, class PUT>
+__device__ inline void ring_update_dir(const RingConst<F> &C, unsigned base, const F (&Ra)[M], F (&w)[M],
+                                       const F (&Qall)[NQ][M], bool has_e, const StateT<F> &s, const PUT &put) {
   const F vinv = C.vinv;
-  const RingOut<F, M> put(L, C.Nm);
   F ri0[M], Fl[M], ri1[M], El[M], Eh[M], rf[M];
   // ---- density: van Leer residual sweep, then the PPA residual
   Upwind<F, M> Uw;
@@ -687,7 +716,8 @@ __device__ inline void ring_update_dir(const RingLane<F, M> &L, const RingConst<
 #pragma unroll
       for (int q = 0; q < M; q++) pxp[q] = Qv[q];
     } else {
-      put(((has_e && qi == NQ - 1) ? s.e : Tout.q[qi]) + base, Qv);
+      if (has_e && qi == NQ - 1) put(s.e + base, Qv);
+      else put.momentum(qi, base, Qv);
     }
   }
   // ---- box 12d along X (Eq. 18) on the shifted ring: face i + N takes zones i - 1, i
@@ -703,48 +733,132 @@ __device__ inline void ring_update_dir(const RingLane<F, M> &L, const RingConst<
     else vx[q] = mom / C.R - C.Rw;
   }
   put(s.vx + base, vx);
-  put(s.rho + base, rf);
+  put.density(s.rho + base, rf);
 }
 // xi has one sign on a ring: a wave takes one of the two forms.
-template <typename F, int NQ, int M>
-__device__ inline void ring_update(const RingLane<F, M> &L, const RingConst<F> &C, unsigned base,
-                                   const F (&Ra)[M], F (&w)[M],
-                                   const F (&Qall)[NQ][M], const TSetT<F> &Tout, bool has_e,
-                                   const StateT<F> &s) {
-  if (C.X.right) ring_update_dir<true, F, NQ, M>(L, C, base, Ra, w, Qall, Tout, has_e, s);
-  else ring_update_dir<false, F, NQ, M>(L, C, base, Ra, w, Qall, Tout, has_e, s);
+template <typename F, int NQ, int M, class PUT>
+__device__ inline void ring_update(const RingConst<F> &C, unsigned base, const F (&Ra)[M], F (&w)[M],
+                                   const F (&Qall)[NQ][M], bool has_e, const StateT<F> &s, const PUT &put) {
+  if (C.X.right) ring_update_dir<true, F, NQ, M>(C, base, Ra, w, Qall, has_e, s, put);
+  else ring_update_dir<false, F, NQ, M>(C, base, Ra, w, Qall, has_e, s, put);
 }
 
-// X transport of every active ring (2D meshes, where there is no Z sweep).
+// X transport of every active ring and 12d, both velocities (2D meshes, where
+// there is no Z sweep).  v_y on a face takes the density and momentum of its two
+// rings after their shifts, so a wave's window is placed on the zones that it
+// stores: it reads each ring as far back as the ring shifts.  A workgroup of
+// RX_W waves takes RX_W rl consecutive rings of a segment, rl to a wave in
+// order; a ring hands its density and Pi+_y to the next one in registers, the
+// last one of a wave through LDS.  The first ring of a workgroup is only read
+// for the face above it (again the last one of the workgroup below).  A pass of
+// its own for v_y read and wrote 4 words a zone more and wrote and read the
+// momenta: 3072 x 1024 zones 66 + 19 to 68 us; the batches of 256 FP32 disks 765
+// + 279 to 768 us and of 48 FP64 disks 299 + 92 to 313; 384 x 128 6.6 + 2.7 to 6.4.
+// Eight waves: 68, 810, 326 and 7.7 us; eight rings a wave in place of at most
+// four: 72, 772, 321; one ring (then eight waves): 71, 992, 376 us.
+constexpr int RX_W = 4;
+template <typename F, int M>
+struct RingKeep : RingPut<F, M> {
+  F *pm, *pp, *rh; // where Pi-_y, Pi+_y and the density are left
+  bool keep_only;  // store nothing
+  __device__ inline RingKeep(const RingLane<F, M> &L, F *a, F *b, F *c, bool only)
+      : RingPut<F, M>(L), pm(a), pp(b), rh(c), keep_only(only) {
+    if (only) {
+#pragma unroll
+      for (int h = 0; h < M / 2; h++) this->one[h] = this->two[h] = false;
+    }
+  }
+  __device__ inline void momentum(int qi, unsigned, const F (&v)[M]) const {
+#pragma unroll
+    for (int q = 0; q < M; q++) (qi == 2 ? pm : pp)[q] = v[q];
+  }
+  __device__ inline void density(F *p, const F (&v)[M]) const {
+    (*this)(p, v);
+#pragma unroll
+    for (int q = 0; q < M; q++) rh[q] = v[q];
+  }
+};
 template <typename F, int NQ>
-__device__ __forceinline__ void ring_x_body(Mesh m, const F *__restrict__ vx2, TSetT<F> T, TSetT<F> Tout,
-                                                StateT<F> s, const double *__restrict__ v0,
-                                                const double *__restrict__ dtp, int nseg, unsigned bid_, unsigned nbk_) {
-  constexpr int M = ring_m<F>();
+__device__ __forceinline__ void ring_x_body(Mesh m, const F *__restrict__ vx2, TSetT<F> T, StateT<F> s,
+                                                const double *__restrict__ v0, const double *__restrict__ dtp,
+                                                int nseg, int rl, unsigned bid_, unsigned nbk_) {
+  constexpr int M = RING_M;
+  __shared__ F edge[RX_W][2][M][WAVE];
   const unsigned blk = xcd_remap(bid_, nbk_);
   const int lane = threadIdx.x & (WAVE - 1);
   // wave-uniform (readfirstlane), so that the ring's constants come through
   // scalar loads
-  const long gw = (long)blk * (blockDim.x / WAVE) + __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
-  if (gw >= (long)m.nring * nseg) return;
-  const int r = (int)(gw / nseg), seg = (int)(gw % nseg);
-  const int j = m.j0 + r % m.ny, k = m.k0 + r / m.ny;
-  const unsigned base = m.o32(0, j, k);
-  const RingLane<F, M> L(m.nx, seg, lane);
-  const RingConst<F> C = ring_const<F>(m, j, k, r, *dtp, v0);
-  // every load of the window is issued before the first use
-  F w[M], Ra[M], Qall[NQ][M];
-  L.load(T.a[T_RHO] + base, Ra);
-  L.load(vx2 + base, w);
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+  const int seg = (int)(blk % (unsigned)nseg), first = m.j0 + (int)(blk / (unsigned)nseg) * (RX_W * rl - 1);
+  const double dtd = *dtp;
+  const bool has_e = T.a[T_E] != nullptr;
+  F rho_b[M], pp_b[M]; // of the ring below
+  F rho_1[M], pm_1[M]; // of the wave's first ring
+  int j1 = m.jn;       // the wave's first ring, if it owns the face below
+  auto store_vy = [&](int j, const RingPut<F, M> &put, const F (&pp)[M], const F (&rb)[M], const F (&pm)[M],
+                      const F (&r)[M]) {
+    F v[M];
 #pragma unroll
-  for (int t = 0; t < NQ; t++) L.load(T.q[ring_qorder<NQ>(t)] + base, Qall[t]);
-  ring_update<F, NQ, M>(L, C, base, Ra, w, Qall, Tout, T.a[T_E] != nullptr, s);
+    for (int q = 0; q < M; q++) v[q] = (pp[q] + pm[q]) / (rb[q] + r[q]);
+    put(s.vy + m.o32(0, j, 0), v);
+  };
+  const RingLane<F, M> L0(m.nx, seg, lane);
+  const RingPut<F, M> put(L0);
+#pragma unroll 1
+  for (int t = 0; t < rl; t++) {
+    const int u = wv * rl + t, jr = first - 1 + u; // the workgroup's ring u
+    if (jr >= m.jn || (u == 0 && first == m.j0 && !m.yper())) continue;
+    const int j = u == 0 ? m.jbelow(first) : jr;
+    const RingConst<F> C = ring_const<F>(m, j, 0, j - m.j0, dtd, v0);
+    const RingLane<F, M> L(m.nx, seg, lane, C.Nm);
+    const unsigned base = m.o32(0, j, 0);
+    // every load of the window is issued before the first use
+    F w[M], Ra[M], Qall[NQ][M];
+    L.load(T.a[T_RHO] + base, Ra);
+    L.load(vx2 + base, w);
+#pragma unroll
+    for (int q = 0; q < NQ; q++) L.load(T.q[ring_qorder<NQ>(q)] + base, Qall[q]);
+    F pm[M], pp[M], rh[M];
+    const RingKeep<F, M> keep(L, pm, pp, rh, u == 0);
+    ring_update<F, NQ, M>(C, base, Ra, w, Qall, has_e, s, keep);
+    if (u > 0 && j >= m.ylo()) {
+      if (t > 0) {
+        store_vy(j, put, pp_b, rho_b, pm, rh);
+      } else {
+        j1 = j;
+#pragma unroll
+        for (int q = 0; q < M; q++) {
+          rho_1[q] = rh[q];
+          pm_1[q] = pm[q];
+        }
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < M; q++) {
+      rho_b[q] = rh[q];
+      pp_b[q] = pp[q];
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < M; q++) {
+    edge[wv][0][q][lane] = rho_b[q];
+    edge[wv][1][q][lane] = pp_b[q];
+  }
+  __syncthreads();
+  if (j1 < m.jn) {
+#pragma unroll
+    for (int q = 0; q < M; q++) {
+      rho_b[q] = edge[wv - 1][0][q][lane];
+      pp_b[q] = edge[wv - 1][1][q][lane];
+    }
+    store_vy(j1, put, pp_b, rho_b, pm_1, rho_1);
+  }
 }
 template <typename F, int NQ>
-__global__ __launch_bounds__(256, 3) void k_ring_x(Mesh m, const F *__restrict__ vx2, TSetT<F> T, TSetT<F> Tout,
-                                                StateT<F> s, const double *__restrict__ v0,
-                                                const double *__restrict__ dtp, int nseg) {
-  ring_x_body<F, NQ>(m, vx2, T, Tout, s, v0, dtp, nseg, blockIdx.x, gridDim.x);
+__global__ __launch_bounds__(RX_W * WAVE, 4) void k_ring_x(Mesh m, const F *__restrict__ vx2, TSetT<F> T, StateT<F> s,
+                                                           const double *__restrict__ v0,
+                                                           const double *__restrict__ dtp, int nseg, int rl) {
+  ring_x_body<F, NQ>(m, vx2, T, s, v0, dtp, nseg, rl, blockIdx.x, gridDim.x);
 }
 
 // Z sweep and X transport fused (3D meshes).  A wave owns one segment of the
@@ -888,7 +1002,7 @@ __global__ __launch_bounds__(256, (sizeof(F) == 8 && NQ == 7 ? 2 : 3)) void k_zx
       }
       const int r = (k - m.k0) * m.ny + (j - m.j0);
       const RingConst<F> C = ring_const<F>(m, j, k, r, dtd, v0);
-      ring_update<F, NQ, M>(L, C, m.o32(0, j, k), Ra, w, Qall, Tout, has_e, s);
+      ring_update<F, NQ, M>(C, m.o32(0, j, k), Ra, w, Qall, has_e, s, RingShift<F, M>(L, C.Nm, Tout));
     }
 #pragma unroll
     for (int c = 0; c < M; c++) {
@@ -919,7 +1033,7 @@ __device__ __forceinline__ void vel_body(Mesh m, StateT<F> s, TSetT<F> T, unsign
   if (i >= m.nx) return;
   int j = m.j0 + jj, k = m.k0 + kk;
   unsigned c = m.o32(i, j, k);
-  const bool dy = j >= m.ylo(), dz = m.d3 && k >= m.zlo();
+  const bool dy = j >= m.ylo(), dz = k >= m.zlo();
   // all loads first: the stores below may alias them as far as the compiler
   // knows, and would otherwise hold the Z loads back behind the Y store
   F rc = s.rho[c], ry = F(0), py = F(0), my = F(0), rz = F(0), pz = F(0), mz = F(0);
@@ -999,17 +1113,27 @@ void launch_sweep_y(Launch &L, const Mesh &m, const StateT<F> &s, const TSetT<F>
   prof_end(L, K_SWEEP_Y);
 }
 
-// Waves of 64 lanes, four per block; ceil(nx / U) waves per ring.
+// The most rings per wave: twice as many while that leaves two workgroups for
+// each compute unit; and the workgroups per segment.
+constexpr int RX_RINGS = 4;
+inline int ring_blocks(int ny, int rl) { return (ny + RX_W * rl - 2) / (RX_W * rl - 1); }
+
+inline int ring_rows(long nring, int nseg, int most) {
+  int rl = 1;
+  while (rl < most && nseg * ((nring + 2 * RX_W * rl - 2) / (2 * RX_W * rl - 1)) >= 2 * CHIP_CUS) rl *= 2;
+  return rl;
+}
+
 template <typename F>
-void launch_ring_x(Launch &L, const Mesh &m, const F *vx2, const TSetT<F> &T, const TSetT<F> &Tout,
-                   const StateT<F> &s, const double *v0, const double *dt) {
-  constexpr int U = RingLane<F, ring_m<F>()>::U;
+void launch_ring_x(Launch &L, const Mesh &m, const F *vx2, const TSetT<F> &T, const StateT<F> &s, const double *v0,
+                   const double *dt) {
+  constexpr int U = RingLane<F, RING_M>::U;
   const int nseg = (m.nx + U - 1) / U;
-  const long waves = (long)m.nring * nseg;
-  const unsigned nb = (unsigned)((waves + 3) / 4);
+  const int rl = ring_rows(m.ny, nseg, RX_RINGS);
+  const unsigned nb = (unsigned)(nseg * ring_blocks(m.ny, rl));
   prof_begin(L, K_RING_X);
-  if (T.nq == 5) k_ring_x<F, 5><<<nb, 256, 0, L.s>>>(m, vx2, T, Tout, s, v0, dt, nseg); // Pi-+_x, Pi-+_y, e
-  else k_ring_x<F, 4><<<nb, 256, 0, L.s>>>(m, vx2, T, Tout, s, v0, dt, nseg);
+  if (T.nq == 5) k_ring_x<F, 5><<<nb, RX_W * WAVE, 0, L.s>>>(m, vx2, T, s, v0, dt, nseg, rl); // Pi-+_x, Pi-+_y, e
+  else k_ring_x<F, 4><<<nb, RX_W * WAVE, 0, L.s>>>(m, vx2, T, s, v0, dt, nseg, rl);
   prof_end(L, K_RING_X);
 }
 
@@ -1043,7 +1167,7 @@ __device__ __forceinline__ void vel2_body(Mesh m, StateT<F> s, TSetT<F> T, unsig
   if (i >= m.nx) return;
   int j = m.j0 + jj, k = m.k0 + kk;
   unsigned c = m.o32(i, j, k);
-  const bool dy = j >= m.ylo(), dz = m.d3 && k >= m.zlo();
+  const bool dy = j >= m.ylo(), dz = k >= m.zlo();
   auto ld = [&](const F *p, unsigned o) { return *reinterpret_cast<const V2 *>(p + o); };
   const V2 zero{F(0), F(0)};
   V2 rc = ld(s.rho, c), ry = zero, py = zero, my = zero, rz = zero, pz = zero, mz = zero;
@@ -1096,33 +1220,18 @@ template <typename F>
 struct RingArgs {
   Mesh m;
   const F *vx2;
-  TSetT<F> T, Tout;
+  TSetT<F> T;
   StateT<F> s;
   const double *v0, *dt;
-  int nseg;
-  unsigned nb;
+  int nseg, rl;
+  unsigned nb, pad_;
 };
 template <typename F, int NQ>
-__global__ __launch_bounds__(256, 3) void k_ring_x_many(const void *args, const uint2 *tab) {
+__global__ __launch_bounds__(RX_W * WAVE, 4) void k_ring_x_many(const void *args, const uint2 *tab) {
   const uint2 t = many_block(tab);
   if (t.x == MANY_NONE) return;
   const RingArgs<F> a = many_args<RingArgs<F>>(args, t.x);
-  ring_x_body<F, NQ>(a.m, a.vx2, a.T, a.Tout, a.s, a.v0, a.dt, a.nseg, t.y, a.nb);
-}
-template <typename F>
-struct VelArgs {
-  Mesh m;
-  StateT<F> s;
-  TSetT<F> T;
-  unsigned nb;
-};
-template <typename F>
-__global__ __launch_bounds__(256) void k_vel_many(const void *args, const uint2 *tab) {
-  const uint2 t = many_block(tab);
-  if (t.x == MANY_NONE) return;
-  const VelArgs<F> a = many_args<VelArgs<F>>(args, t.x);
-  if (a.m.nx % 2 == 0) vel2_body<F>(a.m, a.s, a.T, t.y, a.nb); // two zones per thread
-  else vel_body<F>(a.m, a.s, a.T, t.y, a.nb);
+  ring_x_body<F, NQ>(a.m, a.vx2, a.T, a.s, a.v0, a.dt, a.nseg, a.rl, t.y, a.nb);
 }
 
 template <typename F>
@@ -1142,7 +1251,7 @@ void launch_vel(Launch &L, const Mesh &m, const StateT<F> &s, const TSetT<F> &T)
 }
 
 // multi-mesh launches (ManyGrid) on 2D meshes: blocks of one wave for the
-// column sweep and 12d, so that narrow meshes leave few threads idle
+// column sweep, so that narrow meshes leave few threads idle
 constexpr int MANY_BS = 64;
 
 template <typename F>
@@ -1178,40 +1287,29 @@ template <typename F>
 size_t ring_x_args_bytes() { return sizeof(RingArgs<F>); }
 
 template <typename F>
-unsigned ring_x_args(const Mesh &m, const F *vx2, const TSetT<F> &T, const TSetT<F> &Tout, const StateT<F> &s,
-                     const double *v0, const double *dt, void *dst) {
-  constexpr int U = RingLane<F, ring_m<F>()>::U;
+int ring_x_rows(const std::vector<Mesh> &ms) {
+  constexpr int U = RingLane<F, RING_M>::U;
+  long n = 0;
+  for (const Mesh &m : ms) n += (long)((m.nx + U - 1) / U) * m.ny;
+  return ring_rows(n, 1, RX_RINGS);
+}
+
+template <typename F>
+unsigned ring_x_args(const Mesh &m, const F *vx2, const TSetT<F> &T, const StateT<F> &s, const double *v0,
+                     const double *dt, int rl, void *dst) {
+  constexpr int U = RingLane<F, RING_M>::U;
   const int nseg = (m.nx + U - 1) / U;
-  const unsigned nb = (unsigned)(((long)m.nring * nseg + 3) / 4);
-  *(RingArgs<F> *)dst = RingArgs<F>{m, vx2, T, Tout, s, v0, dt, nseg, nb};
+  const unsigned nb = (unsigned)(nseg * ring_blocks(m.ny, rl));
+  *(RingArgs<F> *)dst = RingArgs<F>{m, vx2, T, s, v0, dt, nseg, rl, nb, 0};
   return nb;
 }
 
 template <typename F>
 void launch_ring_x_many(Launch &L, int nq, const ManyGrid &g) {
   prof_begin(L, K_RING_X);
-  if (nq == 5) k_ring_x_many<F, 5><<<g.nblk, 256, 0, L.s>>>(g.args, g.tab);
-  else k_ring_x_many<F, 4><<<g.nblk, 256, 0, L.s>>>(g.args, g.tab);
+  if (nq == 5) k_ring_x_many<F, 5><<<g.nblk, RX_W * WAVE, 0, L.s>>>(g.args, g.tab);
+  else k_ring_x_many<F, 4><<<g.nblk, RX_W * WAVE, 0, L.s>>>(g.args, g.tab);
   prof_end(L, K_RING_X);
-}
-
-template <typename F>
-size_t vel_args_bytes() { return sizeof(VelArgs<F>); }
-
-// two zones per thread on rows of an even number of zones, else one
-template <typename F>
-unsigned vel_args(const Mesh &m, const StateT<F> &s, const TSetT<F> &T, void *dst) {
-  const int w = m.nx % 2 == 0 ? m.nx / 2 : m.nx;
-  const unsigned nb = (unsigned)((w + MANY_BS - 1) / MANY_BS) * (unsigned)m.ny * (unsigned)m.nz;
-  *(VelArgs<F> *)dst = VelArgs<F>{m, s, T, nb};
-  return nb;
-}
-
-template <typename F>
-void launch_vel_many(Launch &L, const ManyGrid &g) {
-  prof_begin(L, K_VEL);
-  k_vel_many<F><<<g.nblk, MANY_BS, 0, L.s>>>(g.args, g.tab);
-  prof_end(L, K_VEL);
 }
 
 #define FARGO_TRANSPORT_MANY(F)                                                                                     \
@@ -1220,20 +1318,18 @@ void launch_vel_many(Launch &L, const ManyGrid &g) {
   template unsigned sweep_y_args<F>(const Mesh &, const StateT<F> &, const TSetT<F> &, const double *, void *);    \
   template void launch_sweep_y_many<F>(Launch &, const Mesh &, const ManyGrid &);                                  \
   template size_t ring_x_args_bytes<F>();                                                                          \
-  template unsigned ring_x_args<F>(const Mesh &, const F *, const TSetT<F> &, const TSetT<F> &, const StateT<F> &, \
-                                   const double *, const double *, void *);                                        \
-  template void launch_ring_x_many<F>(Launch &, int, const ManyGrid &);                                            \
-  template size_t vel_args_bytes<F>();                                                                             \
-  template unsigned vel_args<F>(const Mesh &, const StateT<F> &, const TSetT<F> &, void *);                        \
-  template void launch_vel_many<F>(Launch &, const ManyGrid &);
+  template int ring_x_rows<F>(const std::vector<Mesh> &);                                                          \
+  template unsigned ring_x_args<F>(const Mesh &, const F *, const TSetT<F> &, const StateT<F> &, const double *,   \
+                                   const double *, int, void *);                                                   \
+  template void launch_ring_x_many<F>(Launch &, int, const ManyGrid &);
 FARGO_TRANSPORT_MANY(double)
 FARGO_TRANSPORT_MANY(float)
 #undef FARGO_TRANSPORT_MANY
 
 #define FARGO_TRANSPORT_INST(F)                                                                                    \
   template void launch_sweep_y<F>(Launch &, const Mesh &, const StateT<F> &, const TSetT<F> &, const double *);   \
-  template void launch_ring_x<F>(Launch &, const Mesh &, const F *, const TSetT<F> &, const TSetT<F> &,         \
-                                 const StateT<F> &, const double *, const double *);                             \
+  template void launch_ring_x<F>(Launch &, const Mesh &, const F *, const TSetT<F> &, const StateT<F> &,         \
+                                 const double *, const double *);                                                \
   template void launch_zx<F>(Launch &, const Mesh &, const F *, const F *, const TSetT<F> &, const TSetT<F> &,    \
                              const StateT<F> &, const double *, const double *);                                  \
   template void launch_vel<F>(Launch &, const Mesh &, const StateT<F> &, const TSetT<F> &);

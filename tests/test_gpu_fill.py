@@ -75,8 +75,8 @@ def test_viscous_pass_at_segment_edges(nx, ny, side):
                                      (480, 7.0), (481, -0.01)])
 @pytest.mark.parametrize("precision", ["fp64", "fp32"])
 def test_ring_segments_and_windows(nx, turn, precision):
-    """Rings one zone around a wave's segment (116 zones in FP64, 240 in FP32) and around its window (128 and 256), the
-    frame turned so that the circular shift goes either way, far and not at all, against the oracle."""
+    """Rings one zone around a wave's segment (116 zones), two of them, its window (128) and two of those, the frame
+    turned so that the circular shift goes either way, far and not at all, against the oracle."""
     print("ring segments", nx, turn, precision, flush=True)
     if precision == "fp64":
         prob = W.random_problem("cyl", nx=nx, ny=6, nz=1, eos="adi", seed=nx, fargo=True, bc=SIDES["reflect"])
@@ -85,6 +85,18 @@ def test_ring_segments_and_windows(nx, turn, precision):
         prob = W.disk2d_cyl(nx=nx, ny=12, noise=1e-2)
         prob.params["precision"] = "fp32"
     assert _step(prob) <= (1e-12 if precision == "fp64" else 2e-6)
+
+
+@pytest.mark.parametrize("geo,nx,ny,eos,side", [("cyl", 40, 3, "iso", "reflect"), ("cyl", 130, 4, "adi", "fixed"),
+                                                ("cart", 150, 3, "iso", "periodic"), ("cart", 233, 7, "adi", "periodic"),
+                                                ("cyl", 2000, 300, "iso", "half"), ("cart", 1900, 301, "adi", "periodic"),
+                                                ("cyl", 3100, 286, "adi", "outflow"), ("cart", 3100, 285, "iso", "periodic")])
+def test_ring_groups(geo, nx, ny, eos, side):
+    """v_y across the workgroups of the 2D ring pass (3, 7 or 15 rings each) and over a periodic side, one ring more than
+    a whole number of workgroups and exactly that, against the oracle."""
+    print("ring groups", geo, nx, ny, eos, side, flush=True)
+    prob = W.random_problem(geo, nx=nx, ny=ny, nz=1, eos=eos, seed=nx + ny, fargo=geo != "cart", bc=SIDES[side])
+    assert _step(prob) <= 1e-12
 
 
 @pytest.mark.parametrize("geo,eos", [("cyl", "iso"), ("sph", "adi"), ("cart", "adi")])
