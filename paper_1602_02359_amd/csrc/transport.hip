@@ -868,16 +868,16 @@ __global__ __launch_bounds__(RX_W * WAVE, 4) void k_ring_x(Mesh m, const F *__re
 // through face k are known the Z update of plane k - 1 is complete, and it is
 // handed, in registers, to the X transport of ring (j, k - 1).  The Z-swept
 // quantities never go through memory.  The halo zones of the segment are
-// swept along Z as well, so segments stay independent.  The conserved
-// quantities handed on are formed again as rho (Q/rho).
-// Its quotients, in the Z part as in the X part, are those of ring_div.
+// swept along Z as well, so segments stay independent.
+// The quotients of its slopes, as those of the X part, are those of ring_div; in
+// FP64 a zone's 1 / rho is correctly rounded.
 // Bound by its vector instructions (some 850 a wave and plane in FP64, 4 cycles
 // each), and yet faster than a Z sweep and a ring kernel apart, whose 29 words a
 // zone between them become 16: 2048 x 768 x 96 in FP64 3.78 + 3.19 ms apart, 5.42
-// fused, 5.14 with the stores' places formed once per ring, the half step's
+// fused, 5.2 with the stores' places formed once per ring, the half step's
 // factors once per face and the halo a lane shorter; 1536 x 512 x 128 adiabatic
-// 2.85 + 2.45, 4.61, 4.17 (at two waves per SIMD, where the three that the
-// launch bound would allow spill: 4.74); 160 x 144 x 120: 96 + 83, 143, 132 us.
+// 2.85 + 2.45, 4.61, 4.3 (at two waves per SIMD, where the three that the
+// launch bound would allow spill: 4.74); 160 x 144 x 120: 96 + 83, 143, 135 us.
 // In FP32 2.90 to 2.87 ms.  Selects in place of the branches around quotients
 // cost registers and gained nothing, nor did two or three planes per turn of the
 // loop, which save the window's moves but spill.
@@ -898,10 +898,18 @@ __global__ __launch_bounds__(256, (sizeof(F) == 8 && NQ == 7 ? 2 : 3)) void k_zx
   const double dtd = *dtp;
   const F dt = (F)dtd;
   const bool has_e = T.a[T_E] != nullptr;
-  // a zone of the window (M columns): density, Q/rho, v_z on the lower face,
-  // v_x on the lower X face (for the X transport)
+  // a zone of the window (M columns): density, Q/rho (CT: the reciprocal of the
+  // density and the conserved Q, which is then handed on as loaded), v_z on the
+  // lower face, v_x on the lower X face (for the X transport).  CT where it costs
+  // no occupancy: FP64 with an energy, two waves per SIMD either way (4.26 and
+  // 4.33 ms on 1536 x 512 x 128); without one its 176 registers for 168 lose the
+  // third wave (5.18 and 5.70 ms on 2048 x 768 x 96), and Q is formed again as
+  // rho (Q/rho): the step's error against 64 bits is the same 5.8e-16.
+  constexpr bool CT = sizeof(F) == 8 && NQ == 7;
   struct Zw {
-    F rho[M], q[NQ][M], w[M], vx[M];
+    F rho[M], ri[CT ? M : 1], v[NQ][M], w[M], vx[M];
+    __device__ inline F q(int t, int c) const { return CT ? v[t][c] * ri[CT ? c : 0] : v[t][c]; }
+    __device__ inline F Q(int t, int c) const { return CT ? v[t][c] : rho[c] * v[t][c]; }
   };
   struct Zr {
     F rho[M], T[NQ][M], w[M], vx[M];
@@ -917,12 +925,13 @@ __global__ __launch_bounds__(256, (sizeof(F) == 8 && NQ == 7 ? 2 : 3)) void k_zx
   auto derive = [&](const Zr &r, Zw &z) {
 #pragma unroll
     for (int c = 0; c < M; c++) {
-      const F ri = ring_rcp(r.rho[c]);
       z.rho[c] = r.rho[c];
+      const F ri = sizeof(F) == 8 ? F(1) / r.rho[c] : ring_rcp(r.rho[c]);
+      if (CT) z.ri[CT ? c : 0] = ri;
       z.w[c] = r.w[c];
       z.vx[c] = r.vx[c];
 #pragma unroll
-      for (int q = 0; q < NQ; q++) z.q[q][c] = r.T[q][c] * ri;
+      for (int q = 0; q < NQ; q++) z.v[q][c] = CT ? r.T[q][c] : r.T[q][c] * ri;
     }
   };
   auto Lz = [&](int a) { return (F)m.Lz(j, a); };
@@ -950,8 +959,8 @@ __global__ __launch_bounds__(256, (sizeof(F) == 8 && NQ == 7 ? 2 : 3)) void k_zx
       sm[NQ][c] = vl_slope<RingDiv>(zp.rho[c], zm.rho[c], z0.rho[c], hm, hp);
 #pragma unroll
       for (int q = 0; q < NQ; q++)
-        sm[q][c] = (DEV && q < 2) ? vl_slope_b<RingDiv>(zp.q[q][c], zm.q[q][c], z0.q[q][c], hm, hp, dlm, dlf)
-                                  : vl_slope<RingDiv>(zp.q[q][c], zm.q[q][c], z0.q[q][c], hm, hp);
+        sm[q][c] = (DEV && q < 2) ? vl_slope_b<RingDiv>(zp.q(q, c), zm.q(q, c), z0.q(q, c), hm, hp, dlm, dlf)
+                                  : vl_slope<RingDiv>(zp.q(q, c), zm.q(q, c), z0.q(q, c), hm, hp);
     }
   }
   F Fp[M], FQp[NQ][M];
@@ -973,16 +982,16 @@ __global__ __launch_bounds__(256, (sizeof(F) == 8 && NQ == 7 ? 2 : 3)) void k_zx
       s0[NQ][c] = vl_slope<RingDiv>(zm.rho[c], z0.rho[c], zp.rho[c], hm, hp);
 #pragma unroll
       for (int q = 0; q < NQ; q++)
-        s0[q][c] = (DEV && q < 2) ? vl_slope_b<RingDiv>(zm.q[q][c], z0.q[q][c], zp.q[q][c], hm, hp, dlf, dlf1)
-                                  : vl_slope<RingDiv>(zm.q[q][c], z0.q[q][c], zp.q[q][c], hm, hp);
+        s0[q][c] = (DEV && q < 2) ? vl_slope_b<RingDiv>(zm.q(q, c), z0.q(q, c), zp.q(q, c), hm, hp, dlf, dlf1)
+                                  : vl_slope<RingDiv>(zm.q(q, c), z0.q(q, c), zp.q(q, c), hm, hp);
       const F w = z0.w[c];
       const Upface<F> U(w, dt, Lm, L0);
       Fr[c] = w * U.star(zm.rho[c], sm[NQ][c], z0.rho[c], s0[NQ][c]) * Sf * dt;
 #pragma unroll
       for (int q = 0; q < NQ; q++) {
         // relative to the background of the face's lower zone
-        const F qr = (DEV && q < 2) ? z0.q[q][c] + dlf : z0.q[q][c];
-        FQ[q][c] = U.star(zm.q[q][c], sm[q][c], qr, s0[q][c]) * Fr[c];
+        const F qr = (DEV && q < 2) ? z0.q(q, c) + dlf : z0.q(q, c);
+        FQ[q][c] = U.star(zm.q(q, c), sm[q][c], qr, s0[q][c]) * Fr[c];
       }
     }
     if (f > a0) {
@@ -997,7 +1006,7 @@ __global__ __launch_bounds__(256, (sizeof(F) == 8 && NQ == 7 ? 2 : 3)) void k_zx
 #pragma unroll
         for (int t = 0; t < NQ; t++) {
           const int q = ring_qorder<NQ>(t);
-          Qall[t][c] = zm.rho[c] * zm.q[q][c] - vi * (FQ[q][c] - FQp[q][c]);
+          Qall[t][c] = zm.Q(q, c) - vi * (FQ[q][c] - FQp[q][c]);
         }
       }
       const int r = (k - m.k0) * m.ny + (j - m.j0);
