@@ -57,9 +57,9 @@ def words_per_unit(p):
         "cfl": (2 + nvel, act),                              # rho, cs|e, velocities
         "source": ((2 + pw + nvel) + (nvel + adi), act),     # rho, cs|e, pot, v -> v'', e''
         "sweep_y": ((1 + nvel + adi) + nT, y_rows),          # rho, v'', e'' -> T (momenta formed on the fly)
-        "ring_x": ((nT + 1) + (2 + adi + 2 + (2 if d3 else 0)), act),  # T, v_x -> rho, v_x, e, Pi_y, Pi_z
-        "zx_ring": ((nT + 2 + 2 + adi + 4) if d3 else 0, act),   # Y-swept T, v_z, v_x -> rho, v_x, e, Pi_y, Pi_z
-        "vel_yz": ((1 + 2 + (2 if d3 else 0)) + (nvel - 1), act),      # rho, Pi_y, Pi_z -> v_y, v_z
+        "ring_x": ((nT + 1) + (3 + adi), act),               # 2D: T, v_x -> rho, v_x, v_y, e
+        "zx_ring": ((nT + 2 + 2 + adi + 4) if d3 else 0, act),  # Y-swept T, v_z, v_x -> rho, v_x, e, Pi_y, Pi_z
+        "vel_yz": (7 if d3 else 0, act),                     # rho, Pi_y, Pi_z -> v_y, v_z
     }
 
 
@@ -730,10 +730,10 @@ def main():
         # the ceiling of the largest kernel's own access pattern: the fused Z
         # sweep and X transport reads density, v_z, v_x and NQ conserved fields
         # and writes NQ (the Y/Z momenta, e, density and v_x: 2 NQ + 3 words a
-        # zone), walking up the planes
+        # zone), walking up the planes (the probe reads nine fields at most)
         kz = head["kernels"]["zx_ring"]
         nq = (round(kz["alg_bytes"] / (cells * 8)) - 3) // 2
-        pats = {"zx_ring": dict(pattern_bandwidth(p["nx"], p["ny"], p["nz"], nq + 3, nq), walk="column")}
+        pats = {"zx_ring": dict(pattern_bandwidth(p["nx"], p["ny"], p["nz"], min(nq + 3, 9), nq), walk="column")}
         for name, pat in pats.items():
             ceil_k = pat["column_march_GBs"] if pat["walk"] == "column" else pat["flat_GBs"]
             pat["kernel_GBs"] = head["kernels"][name]["GBs"]

@@ -292,7 +292,7 @@ int fargo_timings(fargo_ctx *ctx, const char **names, int64_t *counts, double *t
    graph.
    lanes == 0 selects the fused form: each kernel of the step is launched once
    for all contexts, its workgroups mapped to (context, workgroup) through a
-   device table, so a step is seven or eight launches (captured into one
+   device table, so a step is five or six launches (captured into one
    graph) whatever the number of disks; the results are those of fargo_step
    context by context, bit for bit.  It requires 2D meshes (nz == 1) of one
    configuration (precision, geometry, equation of state, viscosity, orbital

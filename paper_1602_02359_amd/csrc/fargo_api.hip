@@ -845,7 +845,7 @@ int fargo_timings(fargo_ctx *ctx, const char **names, int64_t *counts, double *t
 //
 // Fused mode (lanes == 0): each kernel of the step runs once for all disks,
 // its blocks mapped to (disk, block) through a table (ManyGrid), so that a
-// step is seven or eight launches whatever the number of disks, captured into
+// step is five or six launches whatever the number of disks, captured into
 // one graph.  Every zone takes the arithmetic of its disk's own step, so the
 // results are those of fargo_step disk by disk, bit for bit.  It takes 2D
 // meshes of one configuration (precision, geometry, equation of state,
