@@ -44,7 +44,8 @@ constexpr int TX = 64, SX = TX + 4; // tile width, with two halo zones on each s
 // tile, so taller tiles read less of it.  The FP64 3D march takes 16 rows
 // (1024 threads, at most 128 registers a thread), or 12 where the spherical or
 // adiabatic terms need more registers; FP32 marches take 8 (two workgroups per
-// compute unit; measured slower with taller tiles).
+// compute unit, three with neither an energy nor the spherical terms; measured
+// slower with taller tiles).
 template <typename F, int GEO, bool ADI>
 constexpr int tile_rows() {
   if (sizeof(F) == 4) return 8;
@@ -80,10 +81,17 @@ struct Lds {
   double DX[NB][TY];    // 1 / dX of the tile rows, for the halo X faces
 };
 constexpr size_t LDS_CU = 160 * 1024;
-// the reciprocals of the faces' density sums are kept in LDS where they fit
-// beside the rest, else formed again by the zones that use them
-template <typename F, int TY, bool SPH>
-constexpr bool keep_inv() { return sizeof(Lds<F, TY, SPH, true>) <= LDS_CU; }
+// The reciprocals of the faces' density sums are kept in LDS where they fit
+// beside the rest, else formed again by the zones that use them (the same bits);
+// formed again also where a compute unit then holds one workgroup more: FP32
+// without the spherical terms and, for its registers (73, with an energy 97),
+// without an energy.  2048 x 768 x 96: 1.85 to 1.47 ms; where no workgroup is
+// gained it costs (501 x 167 x 43 spherical 72 to 77 us).
+template <typename F, int TY, bool SPH, bool ADI>
+constexpr bool keep_inv() {
+  constexpr size_t with = sizeof(Lds<F, TY, SPH, true>), without = sizeof(Lds<F, TY, SPH, false>);
+  return with <= LDS_CU && (sizeof(F) == 8 || ADI || LDS_CU / without == LDS_CU / with);
+}
 
 // An explicit register move.  The march keeps a window of plane records in
 // registers and rotates it once per plane; moving the newest record out of its
@@ -167,7 +175,7 @@ __device__ __forceinline__ void source_body(Mesh m, StateT<F> s, DevWords dw, F 
                                                   F *__restrict__ e2, int nbx, int nby, int zlen, int ghosts,
                                                   unsigned bid_, unsigned nbk_) {
   constexpr int TY = tile_rows<F, GEO, ADI>();
-  constexpr bool KI = keep_inv<F, TY, GEO == FARGO_SPHERICAL>();
+  constexpr bool KI = keep_inv<F, TY, GEO == FARGO_SPHERICAL, ADI>();
   __shared__ Lds<F, TY, GEO == FARGO_SPHERICAL, KI> L;
   static_assert(sizeof(L) <= LDS_CU, "source step tile exceeds the LDS of a compute unit");
   // the row is the wave index: uniform, so that geometric factors of the
@@ -178,7 +186,7 @@ __device__ __forceinline__ void source_body(Mesh m, StateT<F> s, DevWords dw, F 
   // cover a patch 8 tiles wide and 4 tall, so that the X halo zones a tile
   // reads (each a 128-byte line of its neighbour's row) are mostly a running
   // neighbour's own, still in L2 (2.60 to 2.36 ms on the 2048 x 768 x 96 disk).
-  // The FP32 march (two workgroups per compute unit) takes groups of 4 as well:
+  // The FP32 march takes groups of 4 as well:
   // 29 % fewer bytes fetched, about as fast.  The 12-row march keeps Y fastest
   // over the whole mesh (G = nby), which measured faster.
   const int G = TY == 16 || sizeof(F) == 4 ? 4 : nby;
