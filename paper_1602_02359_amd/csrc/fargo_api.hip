@@ -85,6 +85,7 @@ struct fargo_ctx {
   DevWords w{};
   double *v0 = nullptr, *ringrate = nullptr, *ringshear = nullptr;
   double *partial = nullptr, *sums_out = nullptr;
+  double *dtg = nullptr; // the time-step slots' extremes by groups (2 * DT_GROUPS)
   size_t esize = 8;                                    // bytes per state element
   void *v2[4] = {nullptr, nullptr, nullptr, nullptr}; // post-source vx, vy, vz, e
   void *v3[2] = {nullptr, nullptr};                   // after box 7d: vx, vy (viscosity only)
@@ -261,7 +262,7 @@ size_t geo_doubles(int nyg, int nzg) {
 }
 
 struct Layout {
-  size_t geo, words, v0, ringrate, ringshear, segmm, partial, sums, bg, v2, T, total;
+  size_t geo, words, v0, ringrate, ringshear, segmm, dtg, partial, sums, bg, v2, T, total;
 };
 
 Layout layout(const fargo_params *p) {
@@ -285,6 +286,11 @@ Layout layout(const fargo_params *p) {
   o += al(nring * cseg * 8);
   L.segmm = o;
   if (cseg > 1) o += al(nring * cseg * 2 * 8);
+  // (a place of its own: the slots are counted by ring and segment, so that few
+  // rings, whose partial sums are small, have groups too, and the sums of another
+  // stream leave it alone)
+  L.dtg = o;
+  o += al(2 * DT_GROUPS * 8);
   L.partial = o;
   o += al(nring * 10 * 8);
   L.sums = o;
@@ -387,8 +393,7 @@ DtIn timestep_phase(fargo_ctx *c, Launch &L, const StateT<F> &S, double dt, bool
   launch_bc(L, m, S.rho, S.e, S.vx, S.vy, S.vz, false);
   launch_cfl(L, m, S, 1, c->v0, c->ringrate, c->ringshear, c->w.err);
   if (dt > 0.0) return DtIn{nullptr, nullptr, 0};
-  // (the sums' partials hold nothing during a step)
-  return launch_dt(L, m, c->w, c->ringrate, c->ringshear, c->partial, in_word);
+  return launch_dt(L, m, c->w, c->ringrate, c->ringshear, c->dtg, in_word);
 }
 
 } // namespace
@@ -550,6 +555,7 @@ int fargo_init(const fargo_params *params, void *workspace, size_t ws_bytes, far
   c->v0 = (double *)(base + Lo.v0);
   c->ringrate = (double *)(base + Lo.ringrate);
   c->ringshear = (double *)(base + Lo.ringshear);
+  c->dtg = (double *)(base + Lo.dtg);
   c->partial = (double *)(base + Lo.partial);
   c->sums_out = (double *)(base + Lo.sums);
   size_t nc = (size_t)pitch * nyg * nzg;

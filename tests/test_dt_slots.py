@@ -1,0 +1,113 @@
+"""The time step from many slots (one per ring, or per segment of a long ring), which are reduced by groups first: the
+workspace's room for the groups, the limiting ring anywhere among them, and few rings of millions of zones."""
+import numpy as np
+import pytest
+
+from oracle import oracle as O
+from paper_1602_02359_amd import workloads as W
+
+NG = W.NGH
+GROUPS = 64  # groups of slots, a rate and a shear each
+
+
+def _al(b):
+    return (b + 255) // 256 * 256
+
+
+def _long_rings(ny, nx, precision="fp64", nz=1):
+    return W.default_params(nx=nx, ny=ny, nz=nz, geometry="cyl", eos="iso", precision=precision, xmin=0.0, xmax=6.0,
+                            ymin=W.uniform_faces(1.0, 1.5, ny), fargo=True, bc=("fixed",) * 4,
+                            zmin=W.uniform_faces(-0.1, 0.1, nz) if nz > 1 else np.array([0.0, 1.0]))
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("ny,nx,nz", [(5, 1 << 22, 1), (6, 1 << 22, 1), (9, 1 << 22, 1), (5, 4096001, 1), (3, 1 << 22, 3),
+                                      (5, 64, 1), (20001, 16, 1), (150, 16, 140)])
+def test_workspace_holds_every_buffer(ny, nx, nz, precision):
+    """The bytes asked for hold each of a step's buffers in a place of its own (256-byte slots): the geometric tables,
+    the device words, per ring v0 and the ten partial sums, per slot the largest rate and shear (long rings: two more),
+    the groups of slots, the five sums, the FP32 background tables, the post-source fields and two transport sets."""
+    from paper_1602_02359_amd import fargo as F
+    p = _long_rings(ny, nx, precision, nz)
+    pitch, nyg, nzg = F.fargo_layout(p)
+    elem = 4 if precision == "fp32" else 8
+    nring, seg = ny * nz, 1 if nx <= 4096 else -(-nx // 1024)
+    need = [8 * (12 * (nyg + 1) + 10 * (nzg + 1) + 2 * nzg * nyg), 256, 8 * nring, 80 * nring, 40]
+    need += [8 * nring * seg] * 2 + ([16 * nring * seg] if seg > 1 else []) + [2 * GROUPS * 8]
+    need += [8 * 7 * nzg * nyg] if precision == "fp32" else []
+    fields = (3 if nz > 1 else 2) + 2 * (7 if nz > 1 else 5)
+    assert F.fargo_workspace_bytes(p) >= sum(map(_al, need)) + fields * _al(elem * pitch * nyg * nzg)
+
+
+def _groups_cases():
+    # rings in the order of their slots: ragged groups on a 2D mesh, and on a 3D one (tiles of 16 planes, k fastest)
+    yield "2d", 20001, 1, 3e3, lambda L: (0, L)
+    yield "3d", 150, 140, 30.0, lambda L: (16 * (L // 2400) + (L % 2400) % min(16, 140 - 16 * (L // 2400)),
+                                     (L % 2400) // min(16, 140 - 16 * (L // 2400)))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name,ny,nz,raised,place", list(_groups_cases()), ids=lambda v: v if isinstance(v, str) else "")
+def test_dt_by_groups(name, ny, nz, raised, place):
+    """dt of Eq. cfl2 with one zone's sound speed raised in the first ring, on both sides of the first and the
+    last whole group's end and in the last ring, and the shear limit of one ring, against the oracle."""
+    from gpu_common import dt_close, gpu_solver
+    nring = ny * nz
+    per = -(-nring // GROUPS)
+    prob = W.random_problem("cyl", nx=16, ny=ny, nz=nz, eos="iso", seed=ny, fargo=True,
+                            bc=("fixed", "fixed", "reflect", "reflect"))
+    last = nring // per * per
+    for L in (0, per - 1, per, last - 1, min(last, nring - 1), nring - 1):
+        k, j = place(L)
+        print("dt by groups", name, "ring", L, "at", j, k, flush=True)
+        f = prob.copy_fields()
+        f["cs"][(NG if nz > 1 else 0) + k, NG + j, 5] *= raised
+        s = gpu_solver(W.Problem(prob.name, prob.params, f, 1))
+        assert dt_close(s.fargo_cfl_dt(), O.cfl_dt(prob.params, s.download()))
+    for L in (per, nring - 2):  # a shear so large that Eq. 38 sets dt
+        k, j = place(L)
+        j = min(j, ny - 2)
+        print("shear by groups", name, "ring", L, "at", j, k, flush=True)
+        f = prob.copy_fields()
+        f["vx"][(NG if nz > 1 else 0) + k, NG + j + 1:, :] += 40.0
+        p = dict(prob.params, shear_c0=1e-5)
+        s = gpu_solver(W.Problem(prob.name, p, f, 1))
+        assert dt_close(s.fargo_cfl_dt(), O.cfl_dt(p, s.download()))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("ny,nx", [(5, 4100003), (7, 3000001)])
+def test_few_rings_of_millions_of_zones(ny, nx):
+    """FP32: a step with its own time step leaves the same bits as one with that step imposed, which forms nothing from the
+    slots: the groups write nothing but their own place."""
+    import torch
+    from paper_1602_02359_amd import fargo as F
+    print("long rings", ny, nx, flush=True)
+    p = _long_rings(ny, nx, "fp32")
+    y = W.centres(p["ymin"])
+    x = torch.arange(nx, dtype=torch.float32, device="cuda") * (6.0 / nx)
+    solvers = []
+    for _ in range(2):
+        s = F.Solver(p)
+        s.fargo_set_vx_background(y ** -0.5)
+        s.state = {n: None for n in F.FIELDS}
+        for n, v in (("rho", 1.0), ("vx", 0.0), ("vy", 0.0), ("cs", 0.1)):
+            s.state[n] = torch.full(s.shape, v, dtype=torch.float32, device="cuda")
+        s.state["pot"] = torch.from_numpy(-1.0 / y).cuda().reshape(1, -1, 1).expand(s.shape).contiguous()
+        s.state["rho"][0, :, :nx] += 0.1 * torch.sin(x)
+        s.state["vx"][0, :, :nx] += 0.01 * torch.sin(2 * x)
+        s._bind()
+        solvers.append(s)
+    a, b = solvers
+    a.fargo_step(0.0)
+    a.fargo_check()
+    dt = a.fargo_get_dt()
+    b.fargo_step(dt)
+    b.fargo_check()
+    for n in ("rho", "vx", "vy"):
+        assert torch.equal(a.state[n], b.state[n]), n
+    assert dt > 0.0
+    a.fargo_step(dt)
+    b.fargo_step(dt)
+    for n in ("rho", "vx", "vy"):
+        assert torch.equal(a.state[n], b.state[n]), n
