@@ -897,8 +897,8 @@ __global__ __launch_bounds__(256, (sizeof(F) == 8 && NQ == 7 ? 2 : 3)) void k_zx
                                             const double *__restrict__ dtp, int nseg, int nkc) {
   constexpr int M = zx_m<F>();
   const unsigned blk = xcd_remap(blockIdx.x, gridDim.x);
-  const int lane = threadIdx.x & (WAVE - 1);
-  const long gw = (long)blk * (blockDim.x / WAVE) + __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+  const int lane = threadIdx.x & (WAVE - 1), wv = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+  const long gw = (long)blk * (blockDim.x / WAVE) + wv;
   if (gw >= (long)nseg * m.ny * nkc) return;
   const int seg = (int)(gw % nseg);
   const long rest = gw / nseg;
@@ -909,13 +909,22 @@ __global__ __launch_bounds__(256, (sizeof(F) == 8 && NQ == 7 ? 2 : 3)) void k_zx
   const F dt = (F)dtd;
   const bool has_e = T.a[T_E] != nullptr;
   // a zone of the window (M columns): density, Q/rho (CT: the reciprocal of the
-  // density and the conserved Q, which is then handed on as loaded), v_z on the
-  // lower face, v_x on the lower X face (for the X transport).  CT where it costs
-  // no occupancy: FP64 with an energy, two waves per SIMD either way (4.26 and
-  // 4.33 ms on 1536 x 512 x 128); without one its 176 registers for 168 lose the
-  // third wave (5.18 and 5.70 ms on 2048 x 768 x 96), and Q is formed again as
-  // rho (Q/rho): the step's error against 64 bits is the same 5.8e-16.
-  constexpr bool CT = sizeof(F) == 8 && NQ == 7;
+  // density and the conserved Q), v_z on the lower face, v_x on the lower X face
+  // (for the X transport).  FP64 hands the conserved Q on as loaded: formed again
+  // as rho (Q/rho), the velocities of a step on 80 x 72 x 60 zones were 4 to 5 %
+  // further off in the mean square.  With an energy, at two waves per SIMD either
+  // way, Q comes from the window (CT).  Without one that would take 176 registers
+  // and the third wave (5.18 to 5.70 ms on 2048 x 768 x 96); each lane leaves Q in
+  // LDS for the two planes in between instead (KQ: 5.14 to 5.17 ms, 37 KB a
+  // workgroup, three of them a compute unit).  FP32 forms it again.
+  constexpr bool CT = sizeof(F) == 8 && NQ == 7, KQ = sizeof(F) == 8 && NQ == 6;
+  __shared__ F kept[KQ ? 4 : 1][KQ ? 3 : 1][KQ ? NQ : 1][KQ ? WAVE : 1];
+  auto keep = [&](const F (&T)[NQ][M], int slot) {
+    if constexpr (KQ) {
+#pragma unroll
+      for (int q = 0; q < NQ; q++) kept[wv][slot][q][lane] = T[q][0];
+    }
+  };
   struct Zw {
     F rho[M], ri[CT ? M : 1], v[NQ][M], w[M], vx[M];
     __device__ inline F q(int t, int c) const { return CT ? v[t][c] * ri[CT ? c : 0] : v[t][c]; }
@@ -959,6 +968,8 @@ __global__ __launch_bounds__(256, (sizeof(F) == 8 && NQ == 7 ? 2 : 3)) void k_zx
   derive(rn, zm);
   raw(a0, rn);
   derive(rn, z0);
+  keep(rn.T, 0);
+  int ks = 1; // the slot of zone f + 1; zone f - 1 has the one after it
   raw(a0 + 1, rn);
   F sm[NQ + 1][M], s0[NQ + 1][M];
   F dlf = dl(a0); // background increment at face f
@@ -984,6 +995,8 @@ __global__ __launch_bounds__(256, (sizeof(F) == 8 && NQ == 7 ? 2 : 3)) void k_zx
 #pragma unroll 1
   for (int f = a0; f <= a1; f++) {
     derive(rn, zp); // zone f + 1
+    keep(rn.T, ks);
+    const int kr = ks = ks == 2 ? 0 : ks + 1;
     if (f + 2 <= a1 + 1) raw(f + 2, rn);
     const F hm = hz(f), hp = hz(f + 1), L0 = Lz(f), Sf = (F)m.Sz(j, f), dlf1 = dl(f + 1);
     F Fr[M], FQ[NQ][M];
@@ -1016,7 +1029,10 @@ __global__ __launch_bounds__(256, (sizeof(F) == 8 && NQ == 7 ? 2 : 3)) void k_zx
 #pragma unroll
         for (int t = 0; t < NQ; t++) {
           const int q = ring_qorder<NQ>(t);
-          Qall[t][c] = zm.Q(q, c) - vi * (FQ[q][c] - FQp[q][c]);
+          F Qz;
+          if constexpr (KQ) Qz = kept[wv][kr][q][lane];
+          else Qz = zm.Q(q, c);
+          Qall[t][c] = Qz - vi * (FQ[q][c] - FQp[q][c]);
         }
       }
       const int r = (k - m.k0) * m.ny + (j - m.j0);
