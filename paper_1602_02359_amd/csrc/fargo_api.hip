@@ -159,7 +159,7 @@ size_t elem_bytes(const fargo_params *p) { return p->precision == FARGO_FP32_BUL
 // host tables, in the order of GeoTables
 struct HostGeo {
   std::vector<double> ymin, ymed, zmin, zmed, sinz, Ly, hy, sxj, syj, szj, invVj, sxk, syk, szk, dxlen;
-  std::vector<double> inv_dxlen, inv_hy, inv_Ly, inv_ymin, inv_ymed, cotz, inv_dzmed, inv_dz, inv_syk;
+  std::vector<double> inv_dxlen, inv_hy, inv_Ly, inv_ymin, inv_ymed, cotz, inv_dzmed, inv_dz, invV;
 };
 
 #pragma clang fp contract(off)
@@ -230,6 +230,9 @@ void make_geo(const fargo_params *p, HostGeo &G) {
       else v = G.ymed[j] * G.sinz[k] * dx;
       G.dxlen[(size_t)k * nyg + j] = v;
     }
+  G.invV.resize((size_t)nzg * nyg);
+  for (int k = 0; k < nzg; k++)
+    for (int j = 0; j < nyg; j++) G.invV[(size_t)k * nyg + j] = G.invVj[j] / G.syk[k];
   // reciprocals and the cotangent of the face colatitudes, so that kernels
   // multiply instead of dividing by geometric lengths
   auto inv = [](const std::vector<double> &a) {
@@ -243,7 +246,6 @@ void make_geo(const fargo_params *p, HostGeo &G) {
   G.inv_ymin.resize(nyg + 1);
   for (int j = 0; j <= nyg; j++) G.inv_ymin[j] = G.ymin[j] != 0.0 ? 1.0 / G.ymin[j] : 0.0;
   G.inv_ymed = inv(G.ymed);
-  G.inv_syk = inv(G.syk);
   G.cotz.resize(nzg + 1);
   for (int k = 0; k <= nzg; k++)
     G.cotz[k] = p->geometry == FARGO_SPHERICAL ? std::cos(G.zmin[k]) / std::sin(G.zmin[k]) : 0.0;
@@ -256,9 +258,10 @@ void make_geo(const fargo_params *p, HostGeo &G) {
 }
 
 // the block of GeoTables: GJ_N row tables of nyg + 1 entries, GK_N plane
-// tables of nzg + 1 entries, dxlen and its reciprocal (nzg * nyg each)
+// tables of nzg + 1 entries, dxlen, its reciprocal and the inverse volume (nzg *
+// nyg each)
 size_t geo_doubles(int nyg, int nzg) {
-  return (size_t)GJ_N * (nyg + 1) + (size_t)GK_N * (nzg + 1) + 2 * (size_t)nzg * nyg;
+  return (size_t)GJ_N * (nyg + 1) + (size_t)GK_N * (nzg + 1) + 3 * (size_t)nzg * nyg;
 }
 
 struct Layout {
@@ -476,14 +479,14 @@ int fargo_init(const fargo_params *params, void *workspace, size_t ws_bytes, far
   // geometry
   HostGeo G;
   make_geo(&c->p, G);
-  // one block in the order of GeoRow, GeoPlane, then dxlen, 1/dxlen; each
+  // one block in the order of GeoRow, GeoPlane, then dxlen, 1/dxlen, 1/V; each
   // row (plane) table padded to nyg + 1 (nzg + 1) entries
   std::vector<double> buf;
   buf.reserve(geo_doubles(nyg, nzg));
   const std::vector<double> *rows[GJ_N] = {&G.ymin, &G.ymed,  &G.Ly,     &G.hy,     &G.sxj,      &G.syj,
                                           &G.szj,  &G.invVj, &G.inv_hy, &G.inv_Ly, &G.inv_ymin, &G.inv_ymed};
   const std::vector<double> *planes[GK_N] = {&G.zmin, &G.zmed, &G.sinz, &G.sxk,      &G.syk,
-                                            &G.szk,  &G.cotz, &G.inv_dzmed, &G.inv_dz, &G.inv_syk};
+                                            &G.szk,  &G.cotz, &G.inv_dzmed, &G.inv_dz};
   for (const std::vector<double> *v : rows) {
     buf.insert(buf.end(), v->begin(), v->end());
     buf.resize(buf.size() + (nyg + 1) - v->size(), 0.0);
@@ -494,6 +497,7 @@ int fargo_init(const fargo_params *params, void *workspace, size_t ws_bytes, far
   }
   buf.insert(buf.end(), G.dxlen.begin(), G.dxlen.end());
   buf.insert(buf.end(), G.inv_dxlen.begin(), G.inv_dxlen.end());
+  buf.insert(buf.end(), G.invV.begin(), G.invV.end());
   double *gd = (double *)(base + Lo.geo);
   if (buf.size() != geo_doubles(nyg, nzg)) { // the workspace slot is sized by geo_doubles
     fargo_destroy(c);

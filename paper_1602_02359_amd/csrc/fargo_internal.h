@@ -26,10 +26,22 @@ enum { T_RHO = 0, T_PXM, T_PXP, T_PYM, T_PYP, T_PZM, T_PZP, T_E, T_MAX };
 using cdouble = const __attribute__((address_space(4))) double;
 __device__ inline double gk(const double *p, size_t i) { return ((cdouble *)p)[i]; }
 
+// x / L from a reciprocal r of L within an ulp or two: the quotient's remainder is
+// exact in one fused operation, and after two such corrections the result is
+// the correctly rounded quotient (Markstein 1990: the second one starts from a
+// faithful quotient), for finite x away from underflow.  Five instructions; the
+// division expands to more than twice that.
+__device__ inline double div_by(double x, double L, double r) {
+#pragma clang fp contract(off)
+  double q = x * r;
+  q = fma(fma(-q, L, x), r, q);
+  return fma(fma(-q, L, x), r, q);
+}
+
 // Device-resident geometric tables (FP64), computed on the host at init from
 // Appendix A (Tab. "geom", Eqs. 70-71) and the face coordinates, in one block:
 // the per-row tables (sj = nyg + 1 entries apart), the per-plane tables
-// (sk = nzg + 1 entries apart), then the two per-(plane, row) tables.  A
+// (sk = nzg + 1 entries apart), then the three per-(plane, row) tables.  A
 // kernel holds one base address and three sizes in scalar registers instead
 // of a pointer per table.
 enum GeoRow {
@@ -57,7 +69,6 @@ enum GeoPlane {
   GK_COTZ,      // cot(zmin) in spherical geometry (nzg + 1 entries)
   GK_INV_DZMED, // 1 / (zmed[k] - zmed[k-1])
   GK_INV_DZ,    // 1 / (zmin[k+1] - zmin[k])
-  GK_INV_SYK,   // 1 / GK_SYK
   GK_N
 };
 struct GeoTables {
@@ -90,10 +101,10 @@ struct GeoTables {
   __device__ inline double cotz(int k) const { return tk(GK_COTZ, k); }
   __device__ inline double inv_dzmed(int k) const { return tk(GK_INV_DZMED, k); }
   __device__ inline double inv_dz(int k) const { return tk(GK_INV_DZ, k); }
-  __device__ inline double inv_syk(int k) const { return tk(GK_INV_SYK, k); }
   // azimuthal zone length and its reciprocal at index k * nyg + j
   __device__ inline double dxlen(size_t i) const { return t2(0, i); }
   __device__ inline double inv_dxlen(size_t i) const { return t2(1, i); }
+  __device__ inline double invV(size_t i) const { return t2(2, i); } // inverse volume
 };
 
 // Background of the azimuthal velocity (FP32-bulk state only): per-ring FP64
@@ -159,7 +170,9 @@ struct Mesh {
   __device__ inline double Sx(int j, int k) const { return g.sxj(j) * g.sxk(k); }
   __device__ inline double Sy(int j, int k) const { return g.syj(j) * g.syk(k); }
   __device__ inline double Sz(int j, int k) const { return g.szj(j) * g.szk(k); }
-  __device__ inline double Vinv(int j, int k) const { return g.invVj(j) * g.inv_syk(k); }
+  // (the quotient, rounded once on the host, as in Vol: the product of two rounded
+  // reciprocals is off by up to three half ulps, in every zone of a row alike)
+  __device__ inline double Vinv(int j, int k) const { return g.invV((size_t)k * nyg + j); }
   __device__ inline double Vol(int j, int k) const { return g.syk(k) / g.invVj(j); }
   __device__ inline double DX(int j, int k) const { return g.dxlen((size_t)k * nyg + j); }
   __device__ inline double Lz(int j, int k) const {

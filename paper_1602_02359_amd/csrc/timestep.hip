@@ -95,16 +95,6 @@ __device__ inline double zone_rate2(const CflRing &C, double vb, double vxc, dou
   return rate2;
 }
 
-// x / L from L's correctly rounded reciprocal r: the quotient's remainder is
-// exact in one fused operation, and after two such corrections the result is
-// the correctly rounded quotient (Markstein 1990: the second one starts from a
-// faithful quotient), for finite x away from underflow.  Five instructions; the
-// division expands to more than twice that.
-__device__ inline double div_by(double x, double L, double r) {
-  double q = x * r;
-  q = fma(fma(-q, L, x), r, q);
-  return fma(fma(-q, L, x), r, q);
-}
 // Eq. 38 between a zone and its radial neighbour.  An infinite velocity, which
 // div_by would turn into a NaN, sets *inf (its shear rate is infinite).
 __device__ inline double shear_rate(const CflRing &C, double vxc, double vxn, int &inf) {

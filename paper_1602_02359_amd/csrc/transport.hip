@@ -622,14 +622,17 @@ __device__ inline RingConst<F> ring_const(const Mesh &m, int j, int k, int r, do
   const F xi = (F)xid;
   C.X = PpaX<F>{fabs(xi), F(1) - fabs(xi), xi >= F(0)};
   const double idX = m.g.inv_dxlen((size_t)k * m.nyg + j);
-  C.cdt = (F)(dtd * idX);
+  C.cdt = (F)div_by(dtd, dXd, idX);
   C.pfac = (F)(xid * dXd * Sd);
   if (m.geo == FARGO_CARTESIAN) {
     C.R = C.iR = F(1);
     C.Rw = F(0);
   } else {
-    C.R = (F)m.Rcyl(j, k);
-    C.iR = (F)(m.geo == FARGO_SPHERICAL ? m.dx * idX : m.g.inv_ymed(j));
+    const double R = m.Rcyl(j, k);
+    C.R = (F)R;
+    // (rounded once: dx idX itself, three roundings off, shows in v_x, whose error
+    // after one spherical step it raised by 6 % in the mean square)
+    C.iR = (F)(m.geo == FARGO_SPHERICAL ? div_by(1.0, R, m.dx * idX) : m.g.inv_ymed(j));
     // FP32: the X momenta are deviations R (v_x - vb) from the ring's
     // background, and so is the v_x formed from them (no frame term)
     C.Rw = sizeof(F) == 4 ? F(0) : C.R * (F)m.omega;

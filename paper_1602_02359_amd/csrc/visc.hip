@@ -48,7 +48,7 @@ __device__ __forceinline__ void visc_body(const Visc<F> &V, unsigned bid_, unsig
   const int i = z < 0 ? z + n : (z >= n ? z % n : z);
   const bool useful = lane >= 1 && lane <= VISC_U && z < n;
   const F dt = (F)*V.dt;
-  const double idphi = 1.0 / m.dx, isyk = m.g.inv_syk(0), syk = m.g.syk(0), sxk = m.g.sxk(0);
+  const double idphi = 1.0 / m.dx, syk = m.g.syk(0), sxk = m.g.sxk(0);
   struct Row {
     F rho, nu, vx, vy;
   };
@@ -66,7 +66,7 @@ __device__ __forceinline__ void visc_body(const Visc<F> &V, unsigned bid_, unsig
   auto diag = [&](int j, const Row &r, F vyn, F &tpp, F &trr) {
 #pragma clang fp contract(off)
     const F dvx = from_next_lane(r.vx) - r.vx;
-    const F div = (F)(m.g.invVj(j) * isyk) *
+    const F div = (F)m.Vinv(j, 0) *
                   ((F)(m.g.sxj(j) * sxk) * dvx + ((F)(m.g.syj(j + 1) * syk) * vyn - (F)(m.g.syj(j) * syk) * r.vy));
     const F rn = r.rho * r.nu, ur = F(0.5) * (r.vy + vyn), d3 = F(2) / F(3) * div;
     tpp = -rn * (F(2) * (dvx * (F)(m.g.inv_ymed(j) * idphi) + ur * (F)m.g.inv_ymed(j)) - d3);
