@@ -95,11 +95,12 @@ __device__ inline double zone_rate2(const CflRing &C, double vb, double vxc, dou
   return rate2;
 }
 
-// Eq. 38 between a zone and its radial neighbour.  An infinite velocity, which
-// div_by would turn into a NaN, sets *inf (its shear rate is infinite).
+// Eq. 38 between a zone and its radial neighbour.  An infinite quotient, of an
+// infinite velocity or of one too large for the zone's length, which div_by would
+// turn into a NaN, sets *inf (its shear rate is infinite).
 __device__ inline double shear_rate(const CflRing &C, double vxc, double vxn, int &inf) {
 #pragma clang fp contract(off)
-  inf |= __builtin_isinf(vxc) | __builtin_isinf(vxn);
+  inf |= __builtin_isinf(vxc * C.iLx) | __builtin_isinf(vxn * C.idXp);
   return fabs(div_by(vxc, C.Lx, C.iLx) - div_by(vxn, C.dXp, C.idXp));
 }
 
@@ -237,7 +238,7 @@ __device__ __forceinline__ void cfl_body(Mesh m, StateT<R> s, double *__restrict
   if (CFL) {
     const double vb = m.fargo ? vb_ring : 0.0;
     // the smallest step is 1 / sqrt of the largest sum of squared rates
-    // (taken in dt_of_slots)
+    // (taken in dt_of_extremes)
     const CflRing C = cfl_ring(m, j, k, shear_on);
     double sring = 0.0;
     auto one = [&](double x0, double x1, R rho, R q, R y0, R y1, R z0, R z1, R nu, R xs) {

@@ -111,3 +111,30 @@ def test_few_rings_of_millions_of_zones(ny, nx):
     b.fargo_step(dt)
     for n in ("rho", "vx", "vy"):
         assert torch.equal(a.state[n], b.state[n]), n
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("nx,ny", [(130, 20), (33, 2100), (4200, 4)])
+def test_shear_too_large_for_a_number_leaves_no_time_step(nx, ny):
+    """A ring of one finite speed, so large that v/X overflows: the shear rate of Eq. 38 is infinite and the time step
+    zero, which the oracle and the library both report; a ring short of that gives the oracle's step."""
+    from paper_1602_02359_amd import fargo as F
+    from gpu_common import dt_close, gpu_solver
+    for v, ok in ((1e300, False), (1e290, True)):
+        print("huge shear", nx, ny, v, flush=True)
+        p = W.default_params(nx=nx, ny=ny, nz=1, geometry="cyl", eos="iso", xmin=0.0, xmax=6.0, fargo=True,
+                             ymin=W.uniform_faces(1e-10, 2e-10, ny), zmin=np.array([0.0, 1.0]), bc=("fixed",) * 4)
+        shape = (1, ny + 2 * NG, nx)
+        f = {k: np.full(shape, x) for k, x in (("rho", 1.0), ("vx", 0.0), ("vy", 0.0), ("cs", 1.0), ("pot", 0.0))}
+        f["vx"][0, NG + 1] = v
+        s = gpu_solver(W.Problem("shear", p, f, 1))
+        ref = s.download()
+        if ok:
+            assert dt_close(s.fargo_cfl_dt(), O.cfl_dt(p, ref))
+            continue
+        with pytest.raises(O.OracleError) as e:
+            O.cfl_dt(p, ref)
+        assert e.value.code == -5
+        with pytest.raises(F.FargoError) as e:
+            s.fargo_cfl_dt()
+        assert e.value.code == -5 and s.fargo_get_dt() == 0.0
