@@ -303,19 +303,22 @@ int fargo_batch_create(fargo_ctx *const *ctxs, const fargo_state *states, int co
                        fargo_batch **out);
 /* One step of every context: a single graph launch on `stream`. */
 int fargo_batch_step(fargo_batch *batch, void *stream);
-/* The column sweeps' zones per thread each context uses in the batch (n ==
-   count entries). */
+/* The most zones per thread of the column sweeps of each context in the batch
+   (n == count entries): the launches take fewer where chunks of that length
+   would leave the device idle, and chunks of a context are of equal length. */
 int fargo_batch_chunks(const fargo_batch *batch, int32_t *chunk, int n);
 /* Autotuner (the block-size tuning of Sect. 4.2, for batches).  Fused form:
    the zones per thread of the column sweep are chosen per size class of
    contexts (floor(log2 ny)), class after class, from chunks[], each
    candidate timed over `steps` graph launches (lanes is ignored; best[0] =
-   0, best[1] = the last context's choice; fargo_batch_chunks gives all).
+   0, best[1] = the last context's choice; fargo_batch_chunks gives all).  A
+   candidate whose launches are those of an earlier one is not timed: of
+   equal ones the first is kept.
    Other forms: for every pair (lanes[a], chunks[c]) - the graph's stream count
    and the zones per thread of the Y/Z column sweeps - re-capture the batch,
    time `steps` graph launches with HIP events on `stream`, and keep the
-   fastest pair (written to best[0], best[1]) with the graph captured and
-   timed for it (a new capture of the same pair can run at another speed,
+   fastest pair (written to best[0], best[1]; equal launches as above) with
+   the graph captured and timed for it (a new capture of the same pair can run at another speed,
    since its streams differ).  The evolving fields of every
    state are saved first and restored after each candidate (one temporary
    device allocation), so the call leaves the states as it found them.

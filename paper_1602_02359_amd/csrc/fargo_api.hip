@@ -2,10 +2,12 @@
 // FP64 geometric tables of Appendix A, workspace layout and the sequence of
 // kernels of one full update (Sect. 3, Fig. "flowchart"), instantiated for
 // the FP64 state and for the FP32-bulk state.
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <map>
 #include <new>
 #include <vector>
 
@@ -873,7 +875,7 @@ struct fargo_batch {
   void *fmem = nullptr;
   ManyGrid g[9] = {};
   int nxmax = 0;
-  std::vector<int> chunk; // per disk (the sweep's chunk length, tuned per size class)
+  std::vector<int> chunk; // per disk (the sweep's chunk length at most, tuned per size class)
 };
 
 namespace {
@@ -974,6 +976,32 @@ struct ManyHost {
   }
 };
 
+// The sweep's chunk length of every disk: at most its b->chunk, fewer where chunks of
+// that length would leave the chip idle under the whole batch.
+template <typename F>
+std::vector<int> fused_lengths(const fargo_batch *b) {
+  std::vector<Mesh> ms;
+  for (const fargo_ctx *c : b->ctx) ms.push_back(c->m);
+  std::map<int, int> rows; // by the length asked for
+  for (int c : b->chunk)
+    if (!rows.count(c)) rows[c] = sweep_y_rows<F>(ms, c);
+  std::vector<int> len;
+  for (int c : b->chunk) len.push_back(rows[c]);
+  return len;
+}
+
+// What tells a size class's launches of two candidates apart: its disks' chunk
+// lengths, evened out over their rows.
+std::vector<int> fused_signature(const fargo_batch *b, const std::vector<int> &cls, int c) {
+  std::vector<int> len = fp32(b->ctx[0]) ? fused_lengths<float>(b) : fused_lengths<double>(b), out;
+  for (size_t d = 0; d < len.size(); d++)
+    if (cls[d] == c) {
+      const int ny = b->ctx[d]->m.ny, n = (ny + len[d] - 1) / len[d];
+      out.push_back((ny + n - 1) / n);
+    }
+  return out;
+}
+
 template <typename F>
 int fused_build(fargo_batch *b) {
   const unsigned n = (unsigned)b->ctx.size();
@@ -990,11 +1018,11 @@ int fused_build(fargo_batch *b) {
   std::vector<Mesh> ms;
   for (fargo_ctx *c : b->ctx) ms.push_back(c->m);
   const int rows_src = source_rows<F>(ms), rows_visc = visc_rows<F>(ms), rows_ring = ring_x_rows<F>(ms);
-  const int rows_sweep = sweep_y_rows<F>(ms, *std::max_element(b->chunk.begin(), b->chunk.end()));
+  const std::vector<int> rows_sweep = fused_lengths<F>(b);
   for (unsigned d = 0; d < n; d++) {
     fargo_ctx *c = b->ctx[d];
     Mesh m = c->m;
-    m.chunk = std::min(b->chunk[d], rows_sweep);
+    m.chunk = rows_sweep[d];
     b->nxmax = std::max(b->nxmax, m.nx);
     const StateT<F> S = state_of<F>(c, &b->st[d]);
     const double *dtp = c->w.dt;
@@ -1189,9 +1217,12 @@ int fargo_batch_tune(fargo_batch *b, const int32_t *lanes, int nlanes, const int
       if (!any) continue;
       float best_ms = 0.0f;
       int best_chunk = -1;
+      std::vector<std::vector<int>> seen;
       for (int ci = 0; ci < nchunks && !rc; ci++) {
         for (size_t d = 0; d < b->ctx.size(); d++)
           if (cls[d] == c) b->chunk[d] = chunks[ci];
+        seen.push_back(fused_signature(b, cls, c)); // the same launches as an earlier candidate's are not timed again
+        if (std::find(seen.begin(), seen.end() - 1, seen.back()) != seen.end() - 1) continue;
         rc = fused_capture(b);
         float ms = 0.0f;
         if (!rc) timed(ms);
@@ -1232,9 +1263,16 @@ int fargo_batch_tune(fargo_batch *b, const int32_t *lanes, int nlanes, const int
     kept_graph = nullptr;
     kept_ls.clear();
   };
-  for (int ci = 0; ci < nchunks && !rc; ci++)
+  std::vector<std::vector<std::pair<int, int>>> seen;
+  for (int ci = 0; ci < nchunks && !rc; ci++) {
+    seen.emplace_back();
+    for (auto *c : b->ctx) {
+      c->m.chunk = chunks[ci];
+      seen.back().push_back(fp32(c) ? sweep_lengths<float>(c->m) : sweep_lengths<double>(c->m));
+    }
+    // the same launches as an earlier candidate's are not timed again
+    if (std::find(seen.begin(), seen.end() - 1, seen.back()) != seen.end() - 1) continue;
     for (int li = 0; li < nlanes && !rc; li++) {
-      for (auto *c : b->ctx) c->m.chunk = chunks[ci];
       rc = batch_capture(b, lanes[li]);
       if (rc) break;
       if (hipGraphLaunch(b->exec, s) != hipSuccess) rc = FARGO_EHIP; // warm-up
@@ -1264,6 +1302,7 @@ int fargo_batch_tune(fargo_batch *b, const int32_t *lanes, int nlanes, const int
         o += f.second;
       }
     }
+  }
   if (e0) (void)hipEventDestroy(e0);
   if (e1) (void)hipEventDestroy(e1);
   if (hipStreamSynchronize(s) != hipSuccess && !rc) rc = FARGO_EHIP;
