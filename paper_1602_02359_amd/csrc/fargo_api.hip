@@ -863,6 +863,7 @@ int fargo_timings(fargo_ctx *ctx, const char **names, int64_t *counts, double *t
 // meshes of one configuration (precision, geometry, equation of state,
 // viscosity, orbital advection, v0 mode, boundary kinds) with FIXED radial
 // sides (boxes 2 and 9 then launch nothing) and rings of at most 1792 zones.
+enum { FU_CFL, FU_DT, FU_SRC, FU_VISC, FU_SY, FU_RX, FU_N }; // its launches
 struct fargo_batch {
   std::vector<fargo_ctx *> ctx;
   std::vector<fargo_state> st;
@@ -873,7 +874,7 @@ struct fargo_batch {
   hipGraphExec_t exec = nullptr;
   // fused mode: the launches' argument blocks and tables in one allocation
   void *fmem = nullptr;
-  ManyGrid g[9] = {};
+  ManyGrid g[FU_N] = {};
   int nxmax = 0;
   std::vector<int> chunk; // per disk (the sweep's chunk length at most, tuned per size class)
 };
@@ -943,8 +944,6 @@ int batch_capture(fargo_batch *b, int lanes) {
 size_t field_bytes(const fargo_ctx *c) { return (size_t)c->m.pitch * c->m.nyg * c->m.nzg * c->esize; }
 
 // ---- fused mode ----
-enum { FU_CFL, FU_DT, FU_SRC, FU_VISC, FU_SY, FU_RX, FU_N };
-
 bool fused_ok(fargo_ctx *const *c, int n) {
   const fargo_params &p0 = c[0]->p;
   for (int d = 0; d < n; d++) {

@@ -204,22 +204,8 @@ struct Mesh {
     return (F)Rcyl(j, k) * v;
   }
   template <typename F>
-  __device__ inline F vx_from(int j, int k, F m) const {
-    if (geo == FARGO_CARTESIAN) return m;
-    F R = (F)Rcyl(j, k);
-    return m / R - R * (F)omega;
-  }
-  template <typename F>
   __device__ inline F mz(int j, F v) const { return geo == FARGO_SPHERICAL ? (F)g.ymed(j) * v : v; }
 };
-
-__device__ inline int imod(int i, int n) {
-  int r = i % n;
-  return r < 0 ? r + n : r;
-}
-__device__ inline int iwrap1(int i, int n) { // i in [-n, 2n)
-  return i < 0 ? i + n : (i >= n ? i - n : i);
-}
 
 // The set of transported quantities (box 12a): rho plus nq others, stored
 // with element type R (double, or float for the FP32-bulk state).
@@ -416,9 +402,6 @@ __device__ inline double dt_of_extremes(const DtSlots &in, double rmax, double s
   *bad = !(dt > 0.0) || !isfinite(dt);
   return *bad ? 0.0 : dt;
 }
-
-// Order-preserving integer image of a non-negative double (for atomic min/max).
-__device__ inline unsigned long long dbits(double x) { return (unsigned long long)__double_as_longlong(x); }
 
 // ------------------------------------------------------------------------
 // Host-side launch API (one function per kernel family)
