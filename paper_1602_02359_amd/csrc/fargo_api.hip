@@ -1262,16 +1262,11 @@ int fargo_batch_tune(fargo_batch *b, const int32_t *lanes, int nlanes, const int
     kept_graph = nullptr;
     kept_ls.clear();
   };
-  std::vector<std::vector<std::pair<int, int>>> seen;
-  for (int ci = 0; ci < nchunks && !rc; ci++) {
-    seen.emplace_back();
-    for (auto *c : b->ctx) {
-      c->m.chunk = chunks[ci];
-      seen.back().push_back(fp32(c) ? sweep_lengths<float>(c->m) : sweep_lengths<double>(c->m));
-    }
-    // the same launches as an earlier candidate's are not timed again
-    if (std::find(seen.begin(), seen.end() - 1, seen.back()) != seen.end() - 1) continue;
+  // (every pair is captured and timed, also where chunks come to the same
+  // launches: captures of one pair differ in speed)
+  for (int ci = 0; ci < nchunks && !rc; ci++)
     for (int li = 0; li < nlanes && !rc; li++) {
+      for (auto *c : b->ctx) c->m.chunk = chunks[ci];
       rc = batch_capture(b, lanes[li]);
       if (rc) break;
       if (hipGraphLaunch(b->exec, s) != hipSuccess) rc = FARGO_EHIP; // warm-up
@@ -1301,7 +1296,6 @@ int fargo_batch_tune(fargo_batch *b, const int32_t *lanes, int nlanes, const int
         o += f.second;
       }
     }
-  }
   if (e0) (void)hipEventDestroy(e0);
   if (e1) (void)hipEventDestroy(e1);
   if (hipStreamSynchronize(s) != hipSuccess && !rc) rc = FARGO_EHIP;

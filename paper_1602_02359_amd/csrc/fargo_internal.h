@@ -8,7 +8,6 @@
 #include <stddef.h>
 #include <stdint.h>
 
-#include <utility>
 #include <vector>
 
 #include "../../include/fargo.h"
@@ -522,10 +521,6 @@ void launch_visc(Launch &L, const Mesh &m, const StateT<R> &s, const R *vx2, con
 // box 12
 template <typename R>
 void launch_sweep_y(Launch &L, const Mesh &m, const StateT<R> &s, const TSetT<R> &out, const double *dt);
-// zones of a chunk that the Y sweep and (3D) the fused Z/X pass take of mesh m: at
-// most m.chunk, fewer where those would leave the chip idle
-template <typename R>
-std::pair<int, int> sweep_lengths(const Mesh &m);
 // 2D: X sweep, split of Eq. 29, FARGO and 12d: reads T, writes rho, v_x, v_y, e
 // of the state
 template <typename R>

@@ -1121,44 +1121,17 @@ inline Mesh filled(const Mesh &m, int n, long each, long slots, int &nchunk) {
   return chunked(m, n, nchunk);
 }
 
-// The Y sweep's launch: blocks of a row, their threads, chunks, and the mesh with
-// their length.
-struct SweepY {
-  int nib, bs, nchunk, nrows;
-  Mesh m;
-};
 template <typename F, int NQ, bool D3, bool ADI>
-SweepY sweep_y_shape(const Mesh &m0) {
+void sweep_y_launch(Launch &L, const Mesh &m0, const StateT<F> &s, const TSetT<F> &out, const double *dt) {
   constexpr auto kern = k_sweep_y<F, NQ, D3, ADI>;
   static const long slots[4] = {block_slots(kern, 64), block_slots(kern, 128), block_slots(kern, 192),
                                 block_slots(kern, 256)};
-  SweepY S;
-  row_blocks(m0.nx, S.nib, S.bs);
-  S.nrows = D3 ? m0.nz + 4 : 1;
-  S.m = filled(m0, m0.ny, (long)S.nib * S.nrows, slots[S.bs / WAVE - 1], S.nchunk);
-  return S;
-}
-
-// go(quantities, 3D, adiabatic) with the compile-time constants of mesh m
-template <class GO>
-void sweep_y_form(const Mesh &m, const GO &go) {
-  auto by_eos = [&](auto nq, auto d3) {
-    constexpr int NQ = decltype(nq)::value;
-    if (m.eos == FARGO_ADIABATIC) go(std::integral_constant<int, NQ + 1>{}, d3, std::true_type{});
-    else go(nq, d3, std::false_type{});
-  };
-  if (m.d3) by_eos(std::integral_constant<int, 6>{}, std::true_type{});
-  else by_eos(std::integral_constant<int, 4>{}, std::false_type{});
-}
-
-// The fused pass's launch: segments of a ring, chunks of planes, and the mesh with
-// their length.
-template <typename F>
-Mesh zx_shape(const Mesh &m0, int &nseg, int &nkc) {
-  constexpr int U = RingLane<F, zx_m<F>()>::U;
-  static const long slots[2] = {4 * block_slots(k_zx<F, 6>, 256), 4 * block_slots(k_zx<F, 7>, 256)};
-  nseg = (m0.nx + U - 1) / U;
-  return filled(m0, m0.nz, (long)nseg * m0.ny, slots[m0.eos == FARGO_ADIABATIC], nkc);
+  int nib, bs, nchunk;
+  row_blocks(m0.nx, nib, bs);
+  const int nrows = D3 ? m0.nz + 4 : 1;
+  const Mesh m = filled(m0, m0.ny, (long)nib * nrows, slots[bs / WAVE - 1], nchunk);
+  unsigned nb = (unsigned)nib * (unsigned)nchunk * (unsigned)nrows;
+  k_sweep_y<F, NQ, D3, ADI><<<nb, bs, 0, L.s>>>(m, s.rho, s.vx, s.vy, s.vz, s.e, out, dt, nchunk);
 }
 
 } // namespace
@@ -1167,25 +1140,15 @@ Mesh zx_shape(const Mesh &m0, int &nseg, int &nkc) {
 template <typename F>
 void launch_sweep_y(Launch &L, const Mesh &m, const StateT<F> &s, const TSetT<F> &out, const double *dt) {
   prof_begin(L, K_SWEEP_Y);
-  sweep_y_form(m, [&](auto nq, auto d3, auto adi) {
-    constexpr int NQ = decltype(nq)::value;
-    constexpr bool D3 = decltype(d3)::value, ADI = decltype(adi)::value;
-    const SweepY S = sweep_y_shape<F, NQ, D3, ADI>(m);
-    const unsigned nb = (unsigned)S.nib * (unsigned)S.nchunk * (unsigned)S.nrows;
-    k_sweep_y<F, NQ, D3, ADI><<<nb, S.bs, 0, L.s>>>(S.m, s.rho, s.vx, s.vy, s.vz, s.e, out, dt, S.nchunk);
-  });
+  bool adi = m.eos == FARGO_ADIABATIC;
+  if (m.d3) {
+    if (adi) sweep_y_launch<F, 7, true, true>(L, m, s, out, dt);
+    else sweep_y_launch<F, 6, true, false>(L, m, s, out, dt);
+  } else {
+    if (adi) sweep_y_launch<F, 5, false, true>(L, m, s, out, dt);
+    else sweep_y_launch<F, 4, false, false>(L, m, s, out, dt);
+  }
   prof_end(L, K_SWEEP_Y);
-}
-
-template <typename F>
-std::pair<int, int> sweep_lengths(const Mesh &m) {
-  std::pair<int, int> len(0, 0);
-  sweep_y_form(m, [&](auto nq, auto d3, auto adi) {
-    len.first = sweep_y_shape<F, decltype(nq)::value, decltype(d3)::value, decltype(adi)::value>(m).m.chunk;
-  });
-  int nseg, nkc;
-  if (m.d3) len.second = zx_shape<F>(m, nseg, nkc).chunk;
-  return len;
 }
 
 // The most rings per wave: twice as many while that leaves two workgroups for
@@ -1216,8 +1179,11 @@ void launch_ring_x(Launch &L, const Mesh &m, const F *vx2, const TSetT<F> &T, co
 template <typename F>
 void launch_zx(Launch &L, const Mesh &m0, const F *vx2, const F *vz, const TSetT<F> &T, const TSetT<F> &Tout,
                const StateT<F> &s, const double *v0, const double *dt) {
-  int nseg, nkc;
-  const Mesh m = zx_shape<F>(m0, nseg, nkc);
+  constexpr int U = RingLane<F, zx_m<F>()>::U;
+  static const long slots[2] = {4 * block_slots(k_zx<F, 6>, 256), 4 * block_slots(k_zx<F, 7>, 256)};
+  int nkc;
+  const int nseg = (m0.nx + U - 1) / U;
+  const Mesh m = filled(m0, m0.nz, (long)nseg * m0.ny, slots[T.nq == 7], nkc);
   const long waves = (long)nseg * m.ny * nkc;
   const unsigned nb = (unsigned)((waves + 3) / 4);
   prof_begin(L, K_ZX);
@@ -1400,7 +1366,6 @@ FARGO_TRANSPORT_MANY(float)
 
 #define FARGO_TRANSPORT_INST(F)                                                                                    \
   template void launch_sweep_y<F>(Launch &, const Mesh &, const StateT<F> &, const TSetT<F> &, const double *);   \
-  template std::pair<int, int> sweep_lengths<F>(const Mesh &);                                                    \
   template void launch_ring_x<F>(Launch &, const Mesh &, const F *, const TSetT<F> &, const StateT<F> &,         \
                                  const double *, const double *);                                                \
   template void launch_zx<F>(Launch &, const Mesh &, const F *, const F *, const TSetT<F> &, const TSetT<F> &,    \

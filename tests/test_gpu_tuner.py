@@ -1,4 +1,4 @@
-"""The batch autotuner where candidates come to the same launches: disks of at most 32 rows, which any chunk length from
+"""The fused batch's autotuner where candidates come to the same launches: disks of at most 32 rows, which any chunk length from
 32 up sweeps as one chunk or, where that leaves the device idle, as the same shorter ones.  Nothing is to choose, and the
 first candidate is kept, in whatever order they are given."""
 import numpy as np
@@ -20,13 +20,12 @@ def _solvers(precision, count=9, seed=8):
 
 
 @pytest.mark.parametrize("precision", ["fp64", "fp32"])
-@pytest.mark.parametrize("lanes", [0, 2])
-def test_first_of_equal_candidates_is_kept(lanes, precision):
+def test_first_of_equal_candidates_is_kept(precision):
     from paper_1602_02359_amd import fargo as F
     for chunks in ((64, 32, 33, 40, 48, 56, 63, 96), (32, 96, 64, 33, 40, 48, 56, 63), (48, 32, 33, 40, 56, 63, 64, 96)):
-        print("tuner", lanes, precision, chunks, flush=True)
-        b = F.Batch(_solvers(precision), lanes=lanes)
-        best = b.fargo_batch_tune(lanes=(max(lanes, 1),), chunks=chunks, steps=1)
+        print("tuner", precision, chunks, flush=True)
+        b = F.Batch(_solvers(precision), lanes=0)
+        best = b.fargo_batch_tune(lanes=(0,), chunks=chunks, steps=1)
         assert best[1] == chunks[0] and list(b.chunks()) == [chunks[0]] * 9
         del b
 
