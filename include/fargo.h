@@ -275,7 +275,12 @@ int fargo_check(fargo_ctx *ctx);
    fargo_profile_enable waits for the device and resets the accumulators;
    fargo_timings (which waits for the stream) returns, for up to `cap` kernel
    kinds, their names (static strings), launch counts and total milliseconds
-   since the last fargo_profile_enable, and the number of kinds returned. */
+   since the last fargo_profile_enable, and the number of kinds returned.  The
+   kinds are the launches the library makes, and change with its kernels: bc is
+   boundary faces and ghosts, source includes its ghost rows, zx_ring the Z sweep
+   with the X transport of 3D meshes, ring_x the X transport of 2D ones with both
+   velocities, lfc_reduce the sum of the gradients' partials and the Adam update,
+   lfc_adam the packing of the weights after it. */
 int fargo_profile_enable(fargo_ctx *ctx, int on);
 int fargo_timings(fargo_ctx *ctx, const char **names, int64_t *counts, double *total_ms, int cap, int *n_out,
                   void *stream);

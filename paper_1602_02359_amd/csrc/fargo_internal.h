@@ -497,10 +497,12 @@ struct DtIn {
   int nslot;
 };
 // The ring slots of a 2D mesh where they are at most DT_SLOTS, else none, with dt in the
-// device word (`scratch`: 2 * DT_GROUPS doubles).  384 x 128 zones: the source
-// step takes 5.7 us with the 128 slots and 6.2 after a kernel of 3.8 for them;
-// 3072 x 1024: 68 us with the 1024 slots, whose loads wait among those of all
-// the tiles, and 45 after 5.
+// device word (`scratch`: 2 * DT_GROUPS doubles).  A wave of the source step reads
+// them in one go, DT_SLOTS / 64 rates and shears a lane: 384 x 128 zones, 5.3 us
+// with the 128 slots, where a kernel for them alone takes 3.8.  The read is no
+// reason for the line to lie here: made wide enough for 1024 slots, a step of
+// 900 x 300 zones takes 38.8 us for 41.5 with the kernel, of 1500 x 500 53.6 for
+// 56.8, of 3072 x 1024 153.3 for 156.6, and of 384 x 128 the same 23.6.
 constexpr int DT_SLOTS = 256, DT_GROUPS = 64;
 DtIn launch_dt(Launch &L, const Mesh &m, const DevWords &w, const double *ringrate, const double *ringshear,
                double *scratch, bool in_word);

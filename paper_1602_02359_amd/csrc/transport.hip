@@ -68,7 +68,11 @@ __device__ inline float sweep_div(float n, float d) { return ring_div(n, d); }
 // The product that is a flux: rounded by itself, so that the two zones of a face
 // take the same number (contracted into one zone's difference it would not be
 // rounded there, and the sum over the zones would drift: the FP32 density of 2048
-// x 768 x 96 zones is off by 2.9e-7 after 100 steps, against 2.4e-7).
+// x 768 x 96 zones is off by up to 2.9e-7 after 100 steps, against 2.4e-7).  With
+// it the FP32 errors after 100 steps are, in the mean square, those of three
+// factors multiplied one after the other with a division for each quotient, or
+// less (1.33e-9 and 1.34e-9 here); the largest error of one run, a single zone's,
+// moves by a tenth with any change of rounding (2.26e-7 with those).
 template <typename F>
 __device__ inline F flux_of(F a, F b) {
 #pragma clang fp contract(off)
@@ -321,7 +325,7 @@ __global__ __launch_bounds__(256) void k_sweep_y(Mesh m, const F *__restrict__ r
 // Zones per lane.  The ring kernel takes two.  (Four in FP32 save lane moves and
 // halo, but cost it half its waves: the batch of 256 disks 820 us against 768.)
 // The fused Z/X pass, which also holds the window of the Z sweep, takes one in
-// FP64 (162 registers, three waves per SIMD; two needed 310, one wave) and two
+// FP64 (160 registers, three waves per SIMD; two needed 310, one wave) and two
 // in FP32.
 constexpr int RING_M = 2;
 template <typename F>
@@ -651,12 +655,11 @@ __device__ constexpr int ring_qorder(int t) { return t + 2 < NQ ? t + 2 : t + 2 
 // output is stored shifted by N zones, out of place, by `put` (e, the density
 // and v_x into the state; what becomes of Pi+-_y and Pi+-_z is put's matter).
 // RIGHT: xi >= 0.
-// Bound by its vector instructions until they went from some 1250 to 950 a wave
-// (one sign of xi per compiled form, the parabola's edges as distances, the
-// reciprocal's series, one wrap instead of a modulo, stores in pairs): the
-// 2048 x 768 x 96 disk 3.62 to 3.17 ms, where its 14 words a zone move at 5.3
-// TB/s; 1536 x 512 x 128 2.78 to 2.43; FP32 Z/X pass 3.26 to 2.88; the FP32
-// batch of 256 disks 962 to 834 us.
+// Bound by its vector instructions, which went from some 1250 to 950 a wave (one
+// sign of xi per compiled form, the parabola's edges as distances, the
+// reciprocal's series, one wrap instead of a modulo, stores in pairs): in the ring
+// pass of 3072 x 1024 zones 75 to 66 us, of 48 FP64 disks 355 to 290 and of 256 FP32
+// disks 962 to 834, in the FP32 Z/X pass of 2048 x 768 x 96 3.26 to 2.88 ms.
 template <bool RIGHT, typename F, int NQ, int M, class PUT>
 __device__ inline void ring_update_dir(const RingConst<F> &C, unsigned base, const F (&Ra)[M], F (&w)[M],
                                        const F (&Qall)[NQ][M], bool has_e, const StateT<F> &s, const PUT &put) {
@@ -883,15 +886,18 @@ __global__ __launch_bounds__(RX_W * WAVE, 4) void k_ring_x(Mesh m, const F *__re
 // quantities never go through memory.  The halo zones of the segment are
 // swept along Z as well, so segments stay independent.
 // The quotients of its slopes, as those of the X part, are those of ring_div; in
-// FP64 a zone's 1 / rho is correctly rounded.
+// FP64 a zone's 1 / rho is correctly rounded.  The error of an FP64 step against
+// extended precision is that of the separate passes with divided slopes or less
+// (80 x 72 x 60 zones, 40 states, mean square: density 7.82e-17 both, with an energy
+// 7.88e-17 both and the energy 1.236e-16 both).
 // Bound by its vector instructions (some 850 a wave and plane in FP64, 4 cycles
 // each), and yet faster than a Z sweep and a ring kernel apart, whose 29 words a
 // zone between them become 16: 2048 x 768 x 96 in FP64 3.78 + 3.19 ms apart, 5.42
-// fused, 5.2 with the stores' places formed once per ring, the half step's
+// fused, 5.25 with the stores' places formed once per ring, the half step's
 // factors once per face and the halo a lane shorter; 1536 x 512 x 128 adiabatic
-// 2.85 + 2.45, 4.61, 4.3 (at two waves per SIMD, where the three that the
-// launch bound would allow spill: 4.74); 160 x 144 x 120: 96 + 83, 143, 135 us.
-// In FP32 2.90 to 2.87 ms.  Selects in place of the branches around quotients
+// 2.85 + 2.45, 4.61, 4.36 (at two waves per SIMD, where the three that the
+// launch bound would allow spill: 4.74); 160 x 144 x 120: 96 + 83, 143, 134 us.
+// In FP32 2.8 ms.  Selects in place of the branches around quotients
 // cost registers and gained nothing, nor did two or three planes per turn of the
 // loop, which save the window's moves but spill.
 template <typename F, int NQ>
@@ -1112,9 +1118,9 @@ inline Mesh chunked(const Mesh &m, int n, int &nchunk) {
 // once).  A 2D disk of 384 x 128 zones in two 64-zone chunks is swept along Y
 // by 4 workgroups (58 us); 128 chunks of one zone take 6.2 us.  3072 x 1024:
 // 77 to 47 us (5 TB/s of its 9 words a zone); the box of 160 x 144 x 120
-// zones: Z 131 to 94 us, Y 93 to 78; the FP32 Z/X pass of 501 x 167 x 43 zones
-// 258 to 153 us.  Meshes that fill the chip with chunks of m.chunk zones (2048 x
-// 768 x 96) keep them.
+// zones 93 to 78 us; the FP32 Z/X pass of 501 x 167 x 43 zones 258 to 153 us.
+// Meshes that fill the chip with chunks of m.chunk zones (2048 x 768 x 96) keep
+// them.
 constexpr int SWEEP_OVER = 2; // zones a chunk costs beside its own (1, 2 and 4 measured alike)
 inline Mesh filled(const Mesh &m, int n, long each, long slots, int &nchunk) {
   nchunk = fill_chunks(n, m.chunk, 1, each, slots, SWEEP_OVER);
